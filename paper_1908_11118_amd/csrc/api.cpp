@@ -48,6 +48,8 @@ struct regc_ctx {
     PotDev potd{};
     hipStream_t stream = nullptr;
     int wpb = 1, split = 1, nblocks = 0, max_slab_len = 0, max_slab_scan = 0;
+    int max_halo_len = 0;   // the longest LDS slab copy with its periodic halo
+    bool halo = false, learn_halo = false;   // the sweep and the learned kernels' copies carry it
     bool cull = false;
     bool balance = false;   // walker order by cost before each one-trial sweep launch
     int batch = 1;     // trials per pass of the sweep kernel (1: one-trial kernel)
@@ -342,6 +344,7 @@ static int ctx_alloc_and_init(regc_ctx *c)
         d.inv_cw_x = h.bins ? h.ncx / h.sys.lx : 0.0;
         d.inv_cw_y = h.bins ? h.ncy / h.sys.ly : 0.0;
         max_slab_len = std::max(max_slab_len, len);
+        c->max_halo_len = std::max(c->max_halo_len, h.bins ? (h.ncx + 2) * (h.ncy + 2) * h.cap : len);
         c->max_slab_scan = std::max(c->max_slab_scan, h.bins ? 9 * h.cap : len);
     }
     c->max_slab_len = max_slab_len;
@@ -369,33 +372,38 @@ static int ctx_alloc_and_init(regc_ctx *c)
                                          : ((o.schedule == 0 && o.walkers_per_block == 0 && W <= 4 * n_cu &&
                                              c->pot.mode != REGC_MODE_IDEAL) ? 2 : 1));
     const bool cull = batch == 1 && o.cull > 0;
-    auto smem_for = [&](int wpb) {
-        if (batch > 1 && split == batch) return mw_lds(max_slab_len, nmax, batch, real).total;
-        if (batch > 1) return batch_lds(max_slab_len, nmax, wpb, real).total;
-        return lds_layout(max_slab_len, nmax, c->max_slab_scan, wpb, cull ? wpb * split : 0, real).total;
+    auto smem_for = [&](int wpb, bool halo) {
+        const int len = halo ? c->max_halo_len : max_slab_len;
+        if (batch > 1 && split == batch) return mw_lds(len, nmax, batch, real).total;
+        if (batch > 1) return batch_lds(len, nmax, wpb, real).total;
+        return lds_layout(len, nmax, c->max_slab_scan, wpb, cull ? wpb * split : 0, real).total;
+    };
+    // walkers a compute unit holds at once with workgroups of k (at most four waves per SIMD)
+    const int need = std::min(16, (W + n_cu - 1) / n_cu);
+    auto resident = [&](int k, bool halo) {
+        const size_t b = smem_for(k, halo);
+        if (b > (size_t)lds_max) return 0;
+        return std::min(need, (int)(lds_cu / b) * k);
     };
     int wpb = split > 1 ? 1 : o.walkers_per_block;
     if (wpb == 0) {
         wpb = 1;
         if (W >= 1024) {
-            // the walkers a compute unit must hold (at most four waves per SIMD), and the
-            // workgroup size that lets its LDS hold them all: 4 walkers per workgroup, or 8
-            // when a workgroup of 4 leaves too little LDS for the rest (each workgroup
-            // carries its own slab and ln k copies; measured 1.36e9 against 1.12e9 trial
-            // moves/s for the 4096-replica uneven batch, whose four-walker workgroups of
-            // 500-atom walkers fit three to a compute unit)
-            const int need = std::min(16, (W + n_cu - 1) / n_cu);
-            auto resident = [&](int k) {
-                const size_t b = smem_for(k);
-                if (b > (size_t)lds_max) return 0;
-                return std::min(need, (int)(lds_cu / b) * k);
-            };
-            wpb = resident(8) > resident(4) ? 8 : 4;
+            // the workgroup size that lets a compute unit's LDS hold all the walkers it must:
+            // 4 walkers per workgroup, or 8 when a workgroup of 4 leaves too little LDS for the
+            // rest (each workgroup carries its own slab and ln k copies; measured 1.36e9 against
+            // 1.12e9 trial moves/s for the 4096-replica uneven batch, whose four-walker
+            // workgroups of 500-atom walkers fit three to a compute unit)
+            wpb = resident(8, false) > resident(4, false) ? 8 : 4;
         }
     }
-    while (wpb > 1 && smem_for(wpb) > (size_t)lds_max) --wpb;
-    REGC_CHECK(smem_for(wpb) <= (size_t)lds_max, REGC_EUNSUPPORTED,
-               "one walker needs %zu bytes of LDS, the device allows %d", smem_for(wpb), lds_max);
+    while (wpb > 1 && smem_for(wpb, false) > (size_t)lds_max) --wpb;
+    REGC_CHECK(smem_for(wpb, false) <= (size_t)lds_max, REGC_EUNSUPPORTED,
+               "one walker needs %zu bytes of LDS, the device allows %d", smem_for(wpb, false), lds_max);
+    // the slab's periodic halo in LDS wherever it costs no resident walker (MD walks every
+    // slab entry once, so it takes the plain copy)
+    c->halo = !(o.schedule == 1 && o.md_steps > 0) && smem_for(wpb, true) <= (size_t)lds_max &&
+              resident(wpb, true) >= resident(wpb, false);
     c->wpb = wpb;
     c->split = split;
     c->cull = cull;
@@ -406,7 +414,7 @@ static int ctx_alloc_and_init(regc_ctx *c)
     // chain's latency is the limit and the extra launch only costs (1 %, 1024 walkers)
     c->balance = o.balance > 0 || (o.balance == 0 && W > 4 * n_cu);
     c->batch = batch;
-    c->smem = smem_for(wpb);
+    c->smem = smem_for(wpb, c->halo);
     if (o.schedule == 1 && o.md_steps > 0) {
         c->smem = lds_round(c->smem) + md_lds_bytes(nmax, wpb);
         REGC_CHECK(c->smem <= (size_t)lds_max, REGC_EUNSUPPORTED, "molecular dynamics needs %zu bytes of LDS",
@@ -636,7 +644,9 @@ static SweepArgs sweep_args(regc_ctx *c, int64_t sweep0, int n, bool use_clock)
     a.trace_sweep0 = c->trace_sweep0;
     a.trace_cap = c->trace_cap;
     a.trace_words = c->words;
-    a.max_slab_len = c->max_slab_len;
+    const bool halo = learned_on(c) ? c->learn_halo : c->halo;
+    a.slab_halo = halo ? 1 : 0;
+    a.max_slab_len = halo ? c->max_halo_len : c->max_slab_len;
     a.gas_stride = c->nmax_all;
     a.max_slab_scan = c->max_slab_scan;
     a.count_pairs = c->count_pairs ? 1 : 0;
@@ -1043,7 +1053,9 @@ static int set_proposal(regc_ctx *c, int cls, regc_mlp *mlp, double alpha)
     REGC_HIP(hipGetDevice(&dev));
     REGC_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     const int real = c->opts.precision == REGC_FP64 ? 8 : 4;
-    const size_t smem = learn_lds(c->max_slab_len, c->nmax_all, real).total;
+    size_t smem = learn_lds(c->max_halo_len, c->nmax_all, real).total;
+    const bool halo = smem <= (size_t)lds_max;
+    if (!halo) smem = learn_lds(c->max_slab_len, c->nmax_all, real).total;
     REGC_CHECK(smem <= (size_t)lds_max, REGC_EUNSUPPORTED, "a walker needs %zu bytes of LDS, the device allows %d",
                smem, lds_max);
     int rc;
@@ -1075,6 +1087,7 @@ static int set_proposal(regc_ctx *c, int cls, regc_mlp *mlp, double alpha)
     }
     REGC_HIP(hipStreamSynchronize(c->stream));
     c->learn_smem = smem;
+    c->learn_halo = halo;
     return REGC_OK;
 }
 

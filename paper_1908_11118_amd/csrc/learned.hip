@@ -539,7 +539,7 @@ __device__ int draw_voxel(const NetLds &S, double lse, uint32_t t, uint32_t swee
 __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
 {
     extern __shared__ __align__(32) unsigned char smem[];
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int tid = threadIdx.x, wave = scalar(tid / kWave), lane = tid % kWave;
     const int w = l.block_walker[blockIdx.x];
     const int cid = l.walker_class[w];
     const ClassDev &C = a.cls[cid];
@@ -578,17 +578,7 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
     S.norm = reinterpret_cast<double *>(S.redi + kLearnWaves);
     S.mxf = reinterpret_cast<float *>(S.norm + 1);
 
-    const int slab_len = C.slab_len;
-    for (int k = tid; k < slab_len; k += kLT) {
-#if defined(REGC_FP64)
-        const double *src = a.slab4 + 4 * (size_t)(C.slab_off + k);
-#else
-        const float *src = a.slab4f + 4 * (size_t)(C.slab_off + k);
-#endif
-        Real4 v;
-        v.x = src[0]; v.y = src[1]; v.z = src[2]; v.w = 0;
-        slab[k] = v;
-    }
+    load_slab(C, a, slab, tid, kLT);
     for (int k = tid; k < a.gas_stride + 2; k += kLT) lnk[k] = a.lnk[k];
     for (int k = tid; k < kNetNV; k += kLT) occ[k] = 0u;
 
@@ -603,7 +593,7 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
 
     const int n_max = C.n_max;
     const int K = C.trials;
-    int n = a.n[w];
+    int n = scalar(a.n[w]);
     double e = a.e[w];
     const int label = a.label[w];
     const int sg = C.state_off + label;
@@ -625,20 +615,15 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
     __syncthreads();
 
     Box b;
-    b.lx = (Real)C.lx; b.ly = (Real)C.ly; b.hx = (Real)C.half_lx; b.hy = (Real)C.half_ly;
-    b.ix = (Real)C.inv_lx; b.iy = (Real)C.inv_ly;
+    b.lx = (Real)C.lx; b.ly = (Real)C.ly;
     Pair gg, gs;
     gg.sig2 = (Real)a.pot.sig2_gg; gg.eps4 = (Real)a.pot.eps4_gg; gg.shift = (Real)a.pot.shift_gg;
     gg.rc2 = (Real)a.pot.rc2; gg.hc2 = (Real)a.pot.hc2_gg;
     gs.sig2 = (Real)a.pot.sig2_gs; gs.eps4 = (Real)a.pot.eps4_gs; gs.shift = (Real)a.pot.shift_gs;
     gs.rc2 = gg.rc2; gs.hc2 = (Real)a.pot.hc2_gs;
     const bool ideal = a.pot.ideal != 0;
-    SlabView sv;
-    sv.atoms = slab; sv.len = slab_len; sv.bins = C.bins;
-    sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
-    sv.inv_cap = C.bins ? 1.0f / (float)C.cap : 0.f;
-    sv.inv_cw_x = (Real)C.inv_cw_x; sv.inv_cw_y = (Real)C.inv_cw_y;
-    sv.top_plus_rc = (Real)(C.slab_top + sqrt(a.pot.rc2));
+    const SlabView sv = slab_view(C, a, slab);
+    const SlabLane sl = slab_lane<kLearnWaves>(sv, lane, wave);
     const double lx = C.lx, ly = C.ly, zlo = C.zlo, zhi = C.zhi, H = C.zhi - C.zlo;
     const double md = a.max_disp;
     const double tinv = 1.0 / beta;
@@ -674,7 +659,7 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
                 } else {
                     const double lnU = bcast(f3, 2 * tt + 1);
                     const double ux = bcast(f0, 2 * tt), uy = bcast(f1, 2 * tt), uz = bcast(f2, 2 * tt + 1);
-                    const int i = kind == 1 ? -1 : (int)(((uint64_t)A1 * (uint64_t)n) >> 32);
+                    const int i = kind == 1 ? -1 : (int)__umulhi(A1, (uint32_t)n);
                     const Real4 o = gas[kind == 1 ? 0 : i];
                     const int vold = kind == 1 ? -1 : vox[i];
                     double px = 0.0, py = 0.0, pz = 0.0, c = 0.0;
@@ -728,31 +713,33 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
                         const double lq = log1p(alpha * (exp(lnp) * (double)kNetNV - 1.0));
                         c = kind == 1 ? (lnzv - lnk[n + 1]) - lq : (lnk[n] - lnzv) + lq;
                     }
-                    if (wall) {
+                    if (uniform(wall)) {
                         if (wave == 0) stat += lane == 8;
                     } else {
                         const double thr = (c - lnU) * tinv;
                         const Real qx = (Real)px, qy = (Real)py, qz = (Real)pz;
                         double de = 0.0;
-                        bool core = false;
+                        uint64_t core = 0;
                         if (!ideal) {
                             Real pd;
+                            bool near;
                             if (kind == 0)
-                                pd = partial_delta<true, true, kLearnWaves, false>(gas, n, i, sv, b, gg, gs, lane, wave,
-                                                                                   qx, qy, qz, o.x, o.y, o.z, nullptr,
-                                                                                   nullptr, core, useful);
+                                pd = lane_delta<true, true, kLearnWaves, false>(gas, n, i, sv, sl, b, gg, gs, lane, wave,
+                                                                                qx, qy, qz, o.x, o.y, o.z, nullptr,
+                                                                                nullptr, core, useful, near);
                             else if (kind == 1)
-                                pd = partial_delta<true, false, kLearnWaves, false>(gas, n, -1, sv, b, gg, gs, lane,
-                                                                                    wave, qx, qy, qz, qx, qy, qz,
-                                                                                    nullptr, nullptr, core, useful);
+                                pd = lane_delta<true, false, kLearnWaves, false>(gas, n, -1, sv, sl, b, gg, gs, lane,
+                                                                                 wave, qx, qy, qz, qx, qy, qz,
+                                                                                 nullptr, nullptr, core, useful, near);
                             else
-                                pd = partial_delta<false, true, kLearnWaves, false>(gas, n, i, sv, b, gg, gs, lane,
-                                                                                    wave, o.x, o.y, o.z, o.x, o.y, o.z,
-                                                                                    nullptr, nullptr, core, useful);
+                                pd = lane_delta<false, true, kLearnWaves, false>(gas, n, i, sv, sl, b, gg, gs, lane,
+                                                                                 wave, o.x, o.y, o.z, o.x, o.y, o.z,
+                                                                                 nullptr, nullptr, core, useful, near);
+                            pd = wave_sum63(pd);
                             double *mine = xch + ((xcount & 1) * kLearnWaves + wave) * 2;
-                            if (lane == 0) {
+                            if (lane == kWave - 1) {
                                 mine[0] = (double)pd;
-                                mine[1] = core ? 1.0 : 0.0;
+                                mine[1] = core != 0 ? 1.0 : 0.0;
                             }
                             __syncthreads();
                             const double *x0 = xch + (xcount & 1) * kLearnWaves * 2;
@@ -763,12 +750,12 @@ __global__ void __launch_bounds__(kLT) learned_kernel(SweepArgs a, LearnArgs l)
                                 de += x0[2 * k];
                                 cf += x0[2 * k + 1];
                             }
-                            core = cf != 0.0;
+                            core = __ballot(cf != 0.0);
                             ++xcount;
                         }
-                        if (core && kind != 2) {
+                        if (core != 0 && kind != 2) {
                             if (wave == 0) stat += lane == 9;
-                        } else if (de <= thr) {
+                        } else if (uniform(de <= thr)) {
                             accepted = true;
                             if (wave == 0) stat += lane == 2 * kind + 1;
                             e += de;

@@ -91,6 +91,7 @@ struct SweepArgs {
     int32_t *trace_n;
     int64_t trace_sweep0, trace_cap;
     int trace_words;
+    int slab_halo;                  // the slab's LDS copy carries its periodic halo (max_slab_len includes it)
     int max_slab_len;               // LDS carve sizes of this launch
     int gas_stride;                 // LDS entries per walker (max n_max over classes)
     int max_slab_scan;              // most slab candidates one trial scans (max over classes)
@@ -165,8 +166,10 @@ struct EnergyArgs {
 };
 
 // LDS carve of the sweep kernel (byte offsets, 32-byte aligned), shared by the
-// kernel and the host launch code: class slab, ln k table, the
-// split-walker exchange slots, the walkers' gas coordinates, the pair queues.
+// kernel and the host launch code: the walkers' gas coordinates, class slab, ln k
+// table, the split-walker exchange slots, the pair queues.  The lanes of a wave read
+// whole blocks of 64 gas entries (those past a walker's particles masked), so at
+// least 64 entries stay readable after the last walker's.
 struct LdsLayout {
     size_t slab, lnk, xch, gas, queue, total;
 };
@@ -179,12 +182,13 @@ __host__ __device__ inline LdsLayout lds_layout(int max_slab_len, int gas_stride
     LdsLayout L;
     const size_t r4 = 4 * (size_t)real_size;
     size_t off = 0;
+    L.gas = off;     off = lds_round(off + (size_t)walkers * gas_stride * r4);
+    const size_t readable = off + kWave * r4;
     L.slab = off;    off = lds_round(off + (size_t)max_slab_len * r4);
     L.lnk = off;     off = lds_round(off + (size_t)(gas_stride + 2) * 8);
     L.xch = off;     off = lds_round(off + (size_t)walkers * 16 * 8);
-    L.gas = off;     off = lds_round(off + (size_t)walkers * gas_stride * r4);
     L.queue = off;   off = lds_round(off + (size_t)queue_waves * (2 * gas_stride + 2 * max_slab_scan) * real_size);
-    L.total = off;
+    L.total = off > readable ? off : readable;
     return L;
 }
 

@@ -107,11 +107,21 @@ __device__ __forceinline__ void grid_sync(const SweepArgs &a)
 // each walker publishes N and E, the workgroups meet at a grid barrier, workgroup c
 // (wave 0) runs the exchange step of class c, they meet again, and every walker
 // reads its new state.
+//
+// What bounds it: with four walkers per SIMD the vector unit's issue slots, with one the
+// latency of the chain of trials.  The chain's state (N, the decisions, the event
+// counts) is therefore kept wave-uniform in scalar registers: its branches are scalar,
+// the masks of the candidates live beside it, and the vector unit is left to the pair
+// terms (22 issue slots per 64, of them 4 for the reciprocal; 29 before).  What a trial
+// draws is decoded for 32 trials at once, one trial per pair of lanes, and read back by
+// lane.  Measured per 10-sweep launch, before and after: 1024 walkers with N <= 200 (two
+// waves each) 2.36 -> 1.72 ms, 4096 uneven walkers with N <= 500 (one wave each) 10.1 ->
+// 7.6 ms, 64 walkers in FP64 0.55 -> 0.39 ms, with the same trajectories bit for bit.
 template <int SPLIT, bool CULL, bool PERSIST>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     extern __shared__ __align__(32) unsigned char smem[];
-    const int wave = threadIdx.x / kWave;
+    const int wave = scalar((int)(threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
     const int slot = wave / SPLIT;              // walker within the block
     const int part = wave % SPLIT;              // this wave's share of the candidates
@@ -125,23 +135,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                                    CULL ? waves : 0, (int)sizeof(Real));
     Real4 *slab = reinterpret_cast<Real4 *>(smem + L.slab);
     double *lnk = reinterpret_cast<double *>(smem + L.lnk);
-    double *xch = reinterpret_cast<double *>(smem + L.xch) + slot * 16;    // [parity][part][value, core]
+    double *xch = reinterpret_cast<double *>(smem + L.xch) + slot * 16;    // two exchanges of up to four waves
     Real4 *gas = reinterpret_cast<Real4 *>(smem + L.gas) + (size_t)slot * a.gas_stride;
     Real *qgas = reinterpret_cast<Real *>(smem + L.queue) + (size_t)wave * (2 * a.gas_stride + 2 * a.max_slab_scan);
     Real *qslab = qgas + 2 * a.gas_stride;
 
     // ---- class slab and log table into LDS (shared by the block) ----
-    const int slab_len = C.slab_len;
-    for (int k = threadIdx.x; k < slab_len; k += blockDim.x) {
-#if defined(REGC_FP64)
-        const double *src = a.slab4 + 4 * (size_t)(C.slab_off + k);
-#else
-        const float *src = a.slab4f + 4 * (size_t)(C.slab_off + k);
-#endif
-        Real4 v;
-        v.x = src[0]; v.y = src[1]; v.z = src[2]; v.w = 0;
-        slab[k] = v;
-    }
+    load_slab(C, a, slab, threadIdx.x, blockDim.x);
     for (int k = threadIdx.x; k < a.gas_stride + 2; k += blockDim.x) lnk[k] = a.lnk[k];
     __syncthreads();
     if (slot >= nw) {          // (blocks with SPLIT > 1 always hold one walker)
@@ -153,12 +153,12 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         return;
     }
 
-    const int w = a.wslot ? a.wslot[a.block_w0[blk] + slot] : a.block_w0[blk] + slot;
+    const int w = scalar(a.wslot ? a.wslot[a.block_w0[blk] + slot] : a.block_w0[blk] + slot);
     const int n_max = C.n_max;
     const int K = C.trials;
 
     // ---- walker state into LDS / registers ----
-    int n = a.n[w];
+    int n = scalar(a.n[w]);
     if (SPLIT == 1 && a.wslot) {
         // one wave per walker and several walkers per SIMD (the walker order by cost is
         // on): the more atoms the walker holds relative to its class's cap, the higher its
@@ -166,12 +166,12 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         // launch, do not wait behind shorter ones (config 3: 10.89 -> 10.08 ms per launch;
         // 4096 walkers of config 2's system: 3.57 -> 3.41 ms).  With two waves per walker
         // the same rule made config 2 2.3 % slower, so it stays with one.
-        const int pn = (4 * __builtin_amdgcn_readfirstlane(n)) / (C.n_max + 1);
+        const int pn = (4 * n) / (C.n_max + 1);
         if (pn >= 3) __builtin_amdgcn_s_setprio(3);
         else if (pn == 2) __builtin_amdgcn_s_setprio(2);
         else if (pn == 1) __builtin_amdgcn_s_setprio(1);
     }
-    double e = a.e[w];
+    double e = a.e[w];         // (one wave per walker: up to date in lane 63, which records it)
     int label = a.label[w];
     int sg = C.state_off + label;
     double beta = a.beta[sg];
@@ -189,42 +189,44 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 
     Box b;
     b.lx = in_vgpr((Real)C.lx); b.ly = in_vgpr((Real)C.ly);
-    b.hx = in_vgpr((Real)C.half_lx); b.hy = in_vgpr((Real)C.half_ly);
-    b.ix = in_vgpr((Real)C.inv_lx); b.iy = in_vgpr((Real)C.inv_ly);
     Pair gg, gs;
     gg.sig2 = in_vgpr((Real)a.pot.sig2_gg); gg.eps4 = in_vgpr((Real)a.pot.eps4_gg);
     gg.shift = in_vgpr((Real)a.pot.shift_gg); gg.rc2 = in_vgpr((Real)a.pot.rc2); gg.hc2 = in_vgpr((Real)a.pot.hc2_gg);
     gs.sig2 = in_vgpr((Real)a.pot.sig2_gs); gs.eps4 = in_vgpr((Real)a.pot.eps4_gs);
     gs.shift = in_vgpr((Real)a.pot.shift_gs); gs.rc2 = gg.rc2; gs.hc2 = in_vgpr((Real)a.pot.hc2_gs);
     const bool ideal = a.pot.ideal != 0;
-    SlabView sv;
-    sv.atoms = slab; sv.len = slab_len; sv.bins = C.bins;
-    sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
-    sv.inv_cap = in_vgpr(C.bins ? 1.0f / (float)C.cap : 0.f);
-    sv.inv_cw_x = in_vgpr((Real)C.inv_cw_x); sv.inv_cw_y = in_vgpr((Real)C.inv_cw_y);
-    sv.top_plus_rc = in_vgpr((Real)(C.slab_top + sqrt(a.pot.rc2)));
+    SlabView sv = slab_view(C, a, slab);
+    sv.inv_cw_x = in_vgpr(sv.inv_cw_x); sv.inv_cw_y = in_vgpr(sv.inv_cw_y);
+    sv.top_plus_rc = in_vgpr(sv.top_plus_rc);
+    const SlabLane sl = slab_lane<SPLIT>(sv, lane, part);
     // The proposal is computed in the pair terms' precision: FP64 in the FP64 build
-    // (the oracle's arithmetic, below), FP32 with FP32 pair terms -- one broadcast per
-    // uniform instead of two and FP32 instead of FP64 operations on the trial's chain
-    // (config 2: 2.51 -> 2.43 ms per launch).  The acceptance test is FP64 in both.
-    // The FP64 constants are declared in both builds: the FP32 build measured 1.5 %
-    // faster with them present than without (register allocation of the trial loop).
-    const double lx = in_vgpr(C.lx), ly = in_vgpr(C.ly), zlo = in_vgpr(C.zlo), zhi = in_vgpr(C.zhi);
-    const double H = in_vgpr(C.zhi - C.zlo);
-    const double md = in_vgpr(a.max_disp);
+    // (the oracle's arithmetic, below), FP32 with FP32 pair terms.  The acceptance test
+    // is FP64 in both.
+    const Real zlo = in_vgpr((Real)C.zlo), zhi = in_vgpr((Real)C.zhi), H = in_vgpr((Real)(C.zhi - C.zlo));
+    const Real md = in_vgpr((Real)a.max_disp);
     double tinv = in_vgpr(1.0 / beta);
-#if !defined(REGC_FP64)
-    const float mdf = in_vgpr((float)a.max_disp), zlof = in_vgpr((float)C.zlo), zhif = in_vgpr((float)C.zhi);
-    const float Hf = in_vgpr((float)(C.zhi - C.zlo));
-#endif
-    const int slab_scan = C.bins ? 9 * C.cap : slab_len;
+    const bool all_disp = (a.th_disp >> 32) != 0, all_ins = (a.th_ins >> 32) != 0;
+    const uint32_t th_disp = (uint32_t)a.th_disp, th_ins = (uint32_t)a.th_ins;
 
-    uint32_t stat = 0;     // lane k < kNStat holds counter k
-    uint32_t useful = 0;   // per lane: evaluated pairs inside the cutoff
-    uint64_t cand = 0;     // wave-uniform: candidate pairs of all parts
+    struct alignas(8) Part {   // what a wave gives the others: its sum and whether it met a hard core
+        Real de;
+        uint32_t core;
+    };
+    uint32_t stat = 0;     // lane k < kNStat holds counter k (kept as masks over a batch until its end)
+    uint32_t useful = 0;   // evaluated pairs inside the cutoff
+    uint64_t cand = 0;     // candidate pairs of all parts
     uint32_t xcount = 0;   // exchanges so far: consecutive exchanges use alternate slots
 
+    auto flush_counts = [&]() {
+        if (lane < kNStat && stat) atomicAdd(a.stats + (size_t)sg * kNStat + lane, (unsigned long long)stat);
+        stat = 0;
+    };
+
     const int64_t sweep_first = a.clock ? a.clock[0] + a.sweep0 : a.sweep0;
+    // sweeps until the next sample and the next resynchronisation (64-bit remainders once
+    // per launch, not per sweep)
+    int to_sample = a.sample_every > 0 ? (int)(a.sample_every - sweep_first % a.sample_every) : 0;
+    int to_resync = a.resync_every > 0 ? (int)(a.resync_every - sweep_first % a.resync_every) : 0;
     for (int it = 0; it < a.n_sweeps; ++it) {
         const int64_t sweep = sweep_first + it;
         const bool tracing = a.trace_bits != nullptr && (sweep - a.trace_sweep0) < a.trace_cap &&
@@ -237,218 +239,217 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             const uint4 R = philox4x32_10(
                 make_uint4((uint32_t)(t0 + (lane >> 1)), (uint32_t)sweep, (uint32_t)w, (uint32_t)(lane & 1)),
                 a.key0, a.key1);
-            // FP64 uniforms of the batch, lane-parallel: on A lanes f0, f1 are the x, y
-            // uniforms (A2, A3); on B lanes f2 is the z uniform (B0) and f3 = ln U (B1, B2).
-            const double f0 = uniform_open(R.z), f1 = uniform_open(R.w), f2 = uniform_open(R.x);
-            const double f3 = log(uniform53(R.y, R.z));
-#if !defined(REGC_FP64)
-            const float g0 = (float)f0, g1 = (float)f1, g2 = (float)f2;     // FP32 build: x, y, z uniforms
-#endif
             const int tn = K - t0 < 32 ? K - t0 : 32;
+            // move type of the lane's trial: 0 displacement, 1 insertion, 2 removal (word A0,
+            // which a B lane takes from the lane before it)
+            const uint32_t A0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)R.x, 0xA0, 0xF, 0xF, true);   // quad_perm [0,0,2,2]
+            const int kl = all_disp || A0 < th_disp ? 0 : (all_ins || A0 < th_ins ? 1 : 2);
+            // the trials' masks use the A lane's bit, 2 tt
+            const uint64_t even = tn == 32 ? 0x5555555555555555ull : (0x5555555555555555ull & ((1ull << (2 * tn)) - 1));
+            const uint64_t is_ins = __ballot(kl == 1) & even, is_del = __ballot(kl == 2) & even;
+            const uint64_t is_disp = even & ~(is_ins | is_del);
+            // uniforms in (0, 1): on A lanes x and y (A2, A3), on B lanes z (B0) and ln U (B1, B2).
+            // A displacement uses 2 u - 1, an insertion the point itself.
+            const double f0 = uniform_open((lane & 1) ? R.x : R.z), f1 = uniform_open(R.w);
+            const double lnU = log(uniform53(R.y, R.z));
+            Real vx, vy;            // A lanes: x, y; B lanes: vx = z
+            {
+                const Real u0 = (Real)f0, u1 = (Real)f1;
+#if defined(REGC_FP64)
+                const Real dx = md * (2.0 * u0 - 1.0), dy = md * (2.0 * u1 - 1.0);
+                const Real px = (lane & 1) ? zlo + H * u0 : b.lx * u0, py = b.ly * u1;
+#else
+                const Real dx = __builtin_fmaf(u0, 2.f, -1.f), dy = __builtin_fmaf(u1, 2.f, -1.f);
+                const Real px = (lane & 1) ? __builtin_fmaf(u0, H, zlo) : b.lx * u0, py = b.ly * u1;
+#endif
+                vx = kl == 0 ? dx : px;
+                vy = kl == 0 ? dy : py;
+            }
+            // accept iff dE <= (ln prefactor - ln U) / beta (U <= min(1, A)); a displacement's
+            // prefactor is 1
+            const double tl = kl == 0 ? (0.0 - lnU) * tinv : lnU;
+            uint64_t accm = 0, nonem = 0, wallm = 0, corem = 0;    // accepted; at the cap / empty; wall; hard core
             if (SPLIT >= 2) __builtin_amdgcn_s_setprio(2);
-            uint32_t bits = 0;
-            for (int tt = 0; tt < tn; ++tt) {
-                const uint32_t A0 = bcast(R.x, 2 * tt), A1 = bcast(R.y, 2 * tt);
-                // one wave per walker: the first step's gas atoms are read at the top of the
-                // trial, their LDS round trip overlapping the proposal (4 % faster with one
-                // wave per walker at 1024 walkers, 2 % at 4096)
+            for (int t2 = 0; t2 < 2 * tn; t2 += 2) {
+                const uint64_t bit = 1ull << t2;
                 Real4 pre[2];
                 if (SPLIT == 1) {
-                    pre[0] = gas[lane < n ? lane : 0];
-                    pre[1] = gas[lane + kWave < n ? lane + kWave : 0];
+                    // one wave per walker: the first step's gas atoms are read at the top of the
+                    // trial, their LDS round trip overlapping the proposal (4 % faster with one
+                    // wave per walker at 1024 walkers, 2 % at 4096)
+                    pre[0] = gas[lane];
+                    if (n > kWave) pre[1] = gas[lane + kWave];
+                } else if (part * kWave < n) {
+                    pre[0] = gas[part * kWave + lane];
                 }
-                // move type: 0 displacement, 1 insertion, 2 removal
-                const int kind = (uint64_t)A0 < a.th_disp ? 0 : ((uint64_t)A0 < a.th_ins ? 1 : 2);
-                stat += lane == 2 * kind;
-                bool accepted = false;
-                if (kind == 1 ? n >= n_max : n == 0) {
-                    stat += lane == (kind == 1 ? 6 : 7);          // cap / empty
-                } else {
-                    const double lnU = bcast(f3, 2 * tt + 1);
-#if defined(REGC_FP64)
-                    const double ux = bcast(f0, 2 * tt), uy = bcast(f1, 2 * tt), uz = bcast(f2, 2 * tt + 1);
-                    const int i = kind == 1 ? -1 : (int)(((uint64_t)A1 * (uint64_t)n) >> 32);
-                    const Real4 o = gas[kind == 1 ? 0 : i];
-                    // two waves per walker: the last particle too (moved into slot i by
-                    // an accepted removal), read together with particle i, off the chain
-                    // of an accepted move
-                    Real4 last = o;
-                    if (SPLIT == 2) last = gas[n > 0 ? n - 1 : 0];
-                    double px = 0.0, py = 0.0, pz = 0.0, c;
-                    bool wall = false;
-                    if (kind == 0) {
-                        px = (double)o.x + md * (2.0 * ux - 1.0);
-                        py = (double)o.y + md * (2.0 * uy - 1.0);
-                        pz = (double)o.z + md * (2.0 * uz - 1.0);
-                        if (px < 0.0) px += lx; else if (px >= lx) px -= lx;
-                        if (py < 0.0) py += ly; else if (py >= ly) py -= ly;
-                        wall = pz < zlo || pz > zhi;
-                        c = 0.0;
-                    } else if (kind == 1) {
-                        px = lx * ux;
-                        py = ly * uy;
-                        pz = zlo + H * uz;
-                        c = lnzv - lnk[n + 1];                    // ln z V / (N+1)
-                    } else {
-                        c = lnk[n] - lnzv;                        // ln N / (z V)
+                // the decision on this wave's sum pd against the threshold: accepted or not, and
+                // the energy change (one wave per walker: in lane 63)
+                double de = 0.0;
+                auto decide = [&](Real pd, uint64_t core, double thr, bool can_overlap) {
+                    if (ideal) return uniform(0.0 <= thr);
+                    if (SPLIT >= 2) __builtin_amdgcn_s_setprio(2);
+                    pd = wave_sum63(pd);
+                    if (SPLIT == 1) {
+                        if (can_overlap && core != 0) {
+                            corem |= bit;
+                            return false;
+                        }
+                        de = (double)pd;
+                        return (int64_t)__ballot(de <= thr) < 0;
                     }
-#else
-                    // the same trial in FP32 (particle, last particle and prefactors as above)
-                    const float ux = bcast(g0, 2 * tt), uy = bcast(g1, 2 * tt), uz = bcast(g2, 2 * tt + 1);
-                    const int i = kind == 1 ? -1 : (int)(((uint64_t)A1 * (uint64_t)n) >> 32);
-                    const Real4 o = gas[kind == 1 ? 0 : i];
-                    Real4 last = o;
-                    if (SPLIT == 2) last = gas[n > 0 ? n - 1 : 0];
-                    float px = 0.f, py = 0.f, pz = 0.f;
-                    double c;
-                    bool wall = false;
-                    if (kind == 0) {
-                        px = o.x + mdf * (2.f * ux - 1.f);
-                        py = o.y + mdf * (2.f * uy - 1.f);
-                        pz = o.z + mdf * (2.f * uz - 1.f);
-                        if (px < 0.f) px += b.lx; else if (px >= b.lx) px -= b.lx;
-                        if (py < 0.f) py += b.ly; else if (py >= b.ly) py -= b.ly;
-                        wall = pz < zlof || pz > zhif;
-                        c = 0.0;
-                    } else if (kind == 1) {
-                        px = b.lx * ux;
-                        py = b.ly * uy;
-                        pz = zlof + Hf * uz;
-                        c = lnzv - lnk[n + 1];
-                    } else {
-                        c = lnk[n] - lnzv;
-                    }
-#endif
-                    if (wall) {
-                        stat += lane == 8;
-                    } else {
-                        // accept iff ln U <= ln prefactor - beta dE (U <= min(1, A))
-                        const double thr = (c - lnU) * tinv;
-                        const Real qx = (Real)px, qy = (Real)py, qz = (Real)pz;
-                        double de = 0.0;
-                        bool core = false;
-                        if (!ideal) {
-                            Real pd;
-                            // two waves per walker: the pair loop at the lowest issue priority,
-                            // the rest of the trial (the reduction, the exchange between the
-                            // waves, the decision, the update and the next proposal) at a higher
-                            // one, so that where two walkers share a SIMD the one on its serial
-                            // path issues first (config 2: 2.43 -> 2.38 ms per launch; four waves
-                            // per walker: 2.93 -> 2.71 ms)
-                            if (SPLIT >= 2) __builtin_amdgcn_s_setprio(0);
-                            if (kind == 0)
-                                pd = partial_delta<true, true, SPLIT, CULL, SPLIT == 1>(gas, n, i, sv, b, gg, gs, lane, part, qx,
-                                                                            qy, qz, o.x, o.y, o.z, qgas, qslab, core,
-                                                                            useful, pre);
-                            else if (kind == 1)
-                                pd = partial_delta<true, false, SPLIT, CULL, SPLIT == 1>(gas, n, -1, sv, b, gg, gs, lane, part,
-                                                                             qx, qy, qz, qx, qy, qz, qgas, qslab,
-                                                                             core, useful, pre);
-                            else
-                                pd = partial_delta<false, true, SPLIT, CULL, SPLIT == 1>(gas, n, i, sv, b, gg, gs, lane, part,
-                                                                             o.x, o.y, o.z, o.x, o.y, o.z, qgas,
-                                                                             qslab, core, useful, pre);
-                            if (SPLIT == 4) __builtin_amdgcn_s_setprio(2);   // (two waves: from the reduction on)
-                            if (SPLIT == 1) {
-                                de = (double)pd;
-                            } else {
-                                // alternate slots: exchange k+2 reuses the slot of exchange k
-                                // only after every wave passed the barrier of exchange k+1
-                                double *mine = xch + ((xcount & 1) * SPLIT + part) * 2;
-                                if (lane == 0) {
-                                    mine[0] = (double)pd;
-                                    mine[1] = core ? 1.0 : 0.0;
-                                }
-                                __syncthreads();
-                                const double *x0 = xch + (xcount & 1) * SPLIT * 2;
-                                de = x0[0];
-                                double cf = x0[1];
+                    // alternate slots: exchange k+2 reuses the slot of exchange k
+                    // only after every wave passed the barrier of exchange k+1
+                    Part *x0 = reinterpret_cast<Part *>(xch) + (xcount & 1) * SPLIT;
+                    if (lane == kWave - 1) x0[part] = Part{pd, core != 0 ? 1u : 0u};
+                    ++xcount;
+                    __syncthreads();
+                    uint32_t cf = x0[0].core;
+                    de = (double)x0[0].de;
 #pragma unroll
-                                for (int q = 1; q < SPLIT; ++q) {
-                                    de += x0[2 * q];
-                                    cf += x0[2 * q + 1];
-                                }
-                                core = cf != 0.0;
-                                ++xcount;
-                            }
-                            const uint64_t mult = kind == 0 ? 2 : 1;
-                            const Real zmin = kind == 0 ? (qz < o.z ? qz : o.z) : (kind == 1 ? qz : o.z);
-                            cand += mult * (uint64_t)((kind == 1 ? n : n - 1) +
-                                                      (zmin < sv.top_plus_rc ? slab_scan : 0));
-                        }
-                        if (core && kind != 2) {
-                            stat += lane == 9;
-                        } else if (de <= thr) {
-                            accepted = true;
-                            stat += lane == 2 * kind + 1;
-                            e += de;
-                            // every wave of the walker writes the update into the shared
-                            // LDS copy itself (the same value), so a wave needs only its own
-                            // write to be visible.  Across waves, the exchange barrier of
-                            // this trial ordered all reads before these writes, and that of
-                            // the next trial orders these writes before any later one.  The
-                            // ideal gas has no exchange: its barrier here keeps the other
-                            // wave's read of this trial's particle before the writes, and the
-                            // one below keeps the writes before the next trial's reads.
-                            if (SPLIT > 1 && ideal) __syncthreads();
-                            if (SPLIT == 2) {
-                                // one store for every move type: the new position into slot
-                                // i (displacement) or n (insertion), the last particle into
-                                // slot i (removal; the same value again when i is the last).
-                                // Measured 1.4 % faster with two waves per walker at 1024
-                                // walkers, 2-3 % slower with one (hence the two forms).
-                                Real4 v;
-                                v.x = kind == 2 ? last.x : qx;
-                                v.y = kind == 2 ? last.y : qy;
-                                v.z = kind == 2 ? last.z : qz;
-                                v.w = 0;
-                                if (lane == 0) gas[kind == 1 ? n : i] = v;
-                                n += kind == 1 ? 1 : (kind == 2 ? -1 : 0);
-                            } else if (kind == 0) {
-                                if (lane == 0) {
-                                    Real4 v; v.x = qx; v.y = qy; v.z = qz; v.w = 0;
-                                    gas[i] = v;
-                                }
-                            } else if (kind == 1) {
-                                if (lane == 0) {
-                                    Real4 v; v.x = qx; v.y = qy; v.z = qz; v.w = 0;
-                                    gas[n] = v;
-                                }
-                                n += 1;
-                            } else {
-                                if (lane == 0 && i != n - 1) gas[i] = gas[n - 1];
-                                n -= 1;
-                            }
-                        }
+                    for (int q = 1; q < SPLIT; ++q) {
+                        de += (double)x0[q].de;
+                        cf |= x0[q].core;
                     }
-                }
-                if (accepted) {
-                    bits |= 1u << tt;
+                    if (can_overlap && uniform(cf != 0)) {
+                        corem |= bit;
+                        return false;
+                    }
+                    return uniform(de <= thr);
+                };
+                // An accepted move.  Every wave of the walker writes the update into the shared
+                // LDS copy itself (the same value), so a wave needs only its own write to be
+                // visible.  Across waves, the exchange barrier of this trial ordered all reads
+                // before these writes, and that of the next trial orders these writes before any
+                // later one.  The ideal gas has no exchange: its barrier here keeps the other
+                // wave's read of this trial's particle before the writes, and the one below keeps
+                // the writes before the next trial's reads.
+                auto accept = [&](int at, Real4 v) {
+                    accm |= bit;
+                    e += de;
+                    if (SPLIT > 1 && ideal) __syncthreads();
+                    if (lane == 0) gas[at] = v;
                     if (SPLIT == 1 || !ideal) wave_sync(); else __syncthreads();
+                };
+                // several waves per walker: the pair loop at the lowest issue priority, the rest
+                // of the trial (the reduction, the exchange between the waves, the decision, the
+                // update and the next proposal) at a higher one, so that where two walkers share a
+                // SIMD the one on its serial path issues first (config 2: 2.43 -> 2.38 ms per
+                // launch; four waves per walker: 2.93 -> 2.71 ms)
+                if (is_ins & bit) {
+                    if (n >= n_max) {
+                        nonem |= bit;
+                        continue;
+                    }
+                    Real4 v;
+                    v.x = bcast_real(vx, t2); v.y = bcast_real(vy, t2); v.z = bcast_real(vx, t2 + 1); v.w = 0;
+                    const double thr = ((lnzv - lnk[n + 1]) - bcast(tl, t2 + 1)) * tinv;     // ln z V / (N+1)
+                    Real pd = 0;
+                    uint64_t core = 0;
+                    if (!ideal) {
+                        if (SPLIT >= 2) __builtin_amdgcn_s_setprio(0);
+                        bool near = false;
+                        pd = lane_delta<true, false, SPLIT, CULL, true>(gas, n, -1, sv, sl, b, gg, gs, lane, part, v.x, v.y,
+                                                                        v.z, v.x, v.y, v.z, qgas, qslab, core, useful, near,
+                                                                        pre);
+                        cand += (uint32_t)(n + (near ? sv.len : 0));
+                    }
+                    if (!decide(pd, core, thr, true)) continue;
+                    accept(n, v);
+                    n += 1;
+                    continue;
                 }
+                if (n == 0) {
+                    nonem |= bit;
+                    continue;
+                }
+                const int i = (int)__umulhi(bcast(R.y, t2), (uint32_t)n);
+                const Real4 o = gas[i];
+                if (is_del & bit) {
+                    const Real4 last = gas[n - 1];       // into slot i when accepted (its own value if i is the last)
+                    const double thr = ((lnk[n] - lnzv) - bcast(tl, t2 + 1)) * tinv;         // ln N / (z V)
+                    Real pd = 0;
+                    uint64_t core = 0;
+                    if (!ideal) {
+                        if (SPLIT >= 2) __builtin_amdgcn_s_setprio(0);
+                        bool near = false;
+                        pd = lane_delta<false, true, SPLIT, CULL, true>(gas, n, i, sv, sl, b, gg, gs, lane, part, o.x, o.y,
+                                                                        o.z, o.x, o.y, o.z, qgas, qslab, core, useful, near,
+                                                                        pre);
+                        cand += (uint32_t)(n - 1 + (near ? sv.len : 0));
+                    }
+                    if (!decide(pd, core, thr, false)) continue;
+                    accept(i, last);
+                    n -= 1;
+                    continue;
+                }
+                Real4 v;
+                v.x = bcast_real(vx, t2); v.y = bcast_real(vy, t2); v.z = bcast_real(vx, t2 + 1); v.w = 0;
+#if defined(REGC_FP64)
+                v.x = o.x + v.x; v.y = o.y + v.y; v.z = o.z + v.z;
+#else
+                v.x = __builtin_fmaf(md, v.x, o.x); v.y = __builtin_fmaf(md, v.y, o.y); v.z = __builtin_fmaf(md, v.z, o.z);
+#endif
+                const Real xl = v.x + b.lx, xh = v.x - b.lx, yl = v.y + b.ly, yh = v.y - b.ly;
+                v.x = v.x < Real(0) ? xl : (v.x >= b.lx ? xh : v.x);
+                v.y = v.y < Real(0) ? yl : (v.y >= b.ly ? yh : v.y);
+                if (uniform(v.z < zlo || v.z > zhi)) {
+                    wallm |= bit;
+                    continue;
+                }
+                const double thr = bcast(tl, t2 + 1);
+                Real pd = 0;
+                uint64_t core = 0;
+                if (!ideal) {
+                    if (SPLIT >= 2) __builtin_amdgcn_s_setprio(0);
+                    bool near = false;
+                    pd = lane_delta<true, true, SPLIT, CULL, true>(gas, n, i, sv, sl, b, gg, gs, lane, part, v.x, v.y, v.z,
+                                                                   o.x, o.y, o.z, qgas, qslab, core, useful, near, pre);
+                    cand += 2u * (uint32_t)(n - 1 + (near ? sv.len : 0));
+                }
+                if (!decide(pd, core, thr, true)) continue;
+                accept(i, v);
             }
-            if (tracing && part == 0 && lane == 0)
-                a.trace_bits[((size_t)(sweep - a.trace_sweep0) * a.n_walkers + w) * a.trace_words + (t0 >> 5)] = bits;
+            // the batch's events, counter k in lane k
+            const uint32_t ev[kNStat] = {(uint32_t)__popcll(is_disp), (uint32_t)__popcll(accm & is_disp), (uint32_t)__popcll(is_ins), (uint32_t)__popcll(accm & is_ins),
+                                    (uint32_t)__popcll(is_del), (uint32_t)__popcll(accm & is_del), (uint32_t)__popcll(nonem & is_ins),
+                                    (uint32_t)__popcll(nonem & ~is_ins), (uint32_t)__popcll(wallm), (uint32_t)__popcll(corem)};
+#pragma unroll
+            for (int k = 0; k < kNStat; ++k) stat += lane == k ? ev[k] : 0u;
+            if (tracing && part == 0) {
+                // one bit per trial from the A lanes' bits
+                const uint32_t bits = (uint32_t)__ballot(lane < 32 && ((accm >> (2 * (lane & 31))) & 1));
+                if (lane == 0)
+                    a.trace_bits[((size_t)(sweep - a.trace_sweep0) * a.n_walkers + w) * a.trace_words + (t0 >> 5)] = bits;
+            }
         }
         // ---- end of sweep: running energy resynchronised, trace N, sample record ----
-        if (a.resync_every > 0 && (sweep + 1) % a.resync_every == 0 && !ideal) {
+        bool resync = false, sample = false;
+        if (a.resync_every > 0 && --to_resync == 0) {
+            resync = true;
+            to_resync = a.resync_every;
+        }
+        if (a.sample_every > 0 && --to_sample == 0) {
+            sample = true;
+            to_sample = a.sample_every;
+        }
+        if (resync && !ideal) {
             const double pe = full_energy_part<SPLIT>(gas, n, sv, b, gg, gs, lane, part);
             if (SPLIT == 1) {
                 e = pe;
             } else {
-                double *mine = xch + ((xcount & 1) * SPLIT + part) * 2;
-                if (lane == 0) mine[0] = pe;
+                constexpr int PW = (int)(sizeof(Part) / sizeof(double));
+                double *x0 = reinterpret_cast<double *>(reinterpret_cast<Part *>(xch) + (xcount & 1) * SPLIT);
+                if (lane == 0) x0[PW * part] = pe;
                 __syncthreads();
-                const double *x0 = xch + (xcount & 1) * SPLIT * 2;
                 e = x0[0];
 #pragma unroll
-                for (int q = 1; q < SPLIT; ++q) e += x0[2 * q];
+                for (int q = 1; q < SPLIT; ++q) e += x0[PW * q];
                 ++xcount;
             }
         }
-        if (part == 0 && lane == 0) {
+        if (part == 0 && lane == kWave - 1) {
             if (tracing) a.trace_n[(size_t)(sweep - a.trace_sweep0) * a.n_walkers + w] = n;
-            if (a.sample_every > 0 && (sweep + 1) % a.sample_every == 0) {
+            if (sample) {
                 const int64_t rec = (sweep + 1) / a.sample_every - 1 - a.rec_base;
                 const size_t idx = (size_t)rec * a.n_walkers + w;
                 a.samp_e[idx] = e;
@@ -460,14 +461,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         if (PERSIST && (sweep + 1) % a.swap_every == 0) {
             // ---- the exchange step inside the launch ----
             if (part == 0) {
-                if (lane < kNStat && stat) atomicAdd(a.stats + (size_t)sg * kNStat + lane, (unsigned long long)stat);
-                if (lane == 0) {
+                flush_counts();
+                if (lane == kWave - 1) {
                     a.n[w] = n;
                     a.e[w] = e;
                 }
                 __threadfence();       // this wave's stores visible to every workgroup
             }
-            stat = 0;
             grid_sync(a);
             if (blk < a.n_class && threadIdx.x < kWave) {
                 swap_class<true>(a.sw, blk, (sweep + 1) / a.swap_every - 1, lane, kWave);
@@ -492,18 +492,13 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             dst[3 * k] = (double)v.x; dst[3 * k + 1] = (double)v.y; dst[3 * k + 2] = (double)v.z;
         }
     }
-    {
-        uint32_t u = useful;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) u += __shfl_xor(u, o);
-        if (lane == 0 && a.pairs) {
-            if (part == 0) atomicAdd(a.pairs, (unsigned long long)cand);
-            atomicAdd(a.pairs + 1, (unsigned long long)u);
-        }
+    if (lane == 0 && a.pairs) {
+        if (part == 0) atomicAdd(a.pairs, (unsigned long long)cand);
+        atomicAdd(a.pairs + 1, (unsigned long long)useful);
     }
     if (part == 0) {
-        if (lane < kNStat && stat) atomicAdd(a.stats + (size_t)sg * kNStat + lane, (unsigned long long)stat);
-        if (lane == 0) {
+        flush_counts();
+        if (lane == kWave - 1) {
             a.n[w] = n;
             a.e[w] = e;
         }
@@ -573,17 +568,7 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) batch_kernel(Swee
     Real4 *gas = reinterpret_cast<Real4 *>(smem + L.gas) + (size_t)wave * a.gas_stride;
     Real *eslab = reinterpret_cast<Real *>(smem + L.eslab) + (size_t)wave * a.gas_stride;
 
-    const int slab_len = C.slab_len;
-    for (int k = threadIdx.x; k < slab_len; k += blockDim.x) {
-#if defined(REGC_FP64)
-        const double *src = a.slab4 + 4 * (size_t)(C.slab_off + k);
-#else
-        const float *src = a.slab4f + 4 * (size_t)(C.slab_off + k);
-#endif
-        Real4 v;
-        v.x = src[0]; v.y = src[1]; v.z = src[2]; v.w = 0;
-        slab[k] = v;
-    }
+    load_slab(C, a, slab, threadIdx.x, blockDim.x);
     for (int k = threadIdx.x; k < a.gas_stride + 2; k += blockDim.x) lnk[k] = a.lnk[k];
     __syncthreads();
     if (wave >= nw) return;
@@ -602,26 +587,23 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) batch_kernel(Swee
     // wave-uniform constants kept in VGPRs: the loop holds more uniform values than
     // there are SGPRs, and spilled SGPRs cost a lane read per use
     Box b;
-    b.lx = in_vgpr((Real)C.lx); b.ly = in_vgpr((Real)C.ly); b.hx = in_vgpr((Real)C.half_lx);
-    b.hy = in_vgpr((Real)C.half_ly); b.ix = in_vgpr((Real)C.inv_lx); b.iy = in_vgpr((Real)C.inv_ly);
+    b.lx = in_vgpr((Real)C.lx); b.ly = in_vgpr((Real)C.ly);
     Pair gg, gs;
     gg.sig2 = in_vgpr((Real)a.pot.sig2_gg); gg.eps4 = in_vgpr((Real)a.pot.eps4_gg);
     gg.shift = in_vgpr((Real)a.pot.shift_gg); gg.rc2 = in_vgpr((Real)a.pot.rc2); gg.hc2 = in_vgpr((Real)a.pot.hc2_gg);
     gs.sig2 = in_vgpr((Real)a.pot.sig2_gs); gs.eps4 = in_vgpr((Real)a.pot.eps4_gs);
     gs.shift = in_vgpr((Real)a.pot.shift_gs); gs.rc2 = gg.rc2; gs.hc2 = in_vgpr((Real)a.pot.hc2_gs);
     const bool ideal = a.pot.ideal != 0;
-    SlabView sv;
-    sv.atoms = slab; sv.len = slab_len; sv.bins = C.bins;
-    sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
-    sv.inv_cap = in_vgpr(C.bins ? 1.0f / (float)C.cap : 0.f);
-    sv.inv_cw_x = in_vgpr((Real)C.inv_cw_x); sv.inv_cw_y = in_vgpr((Real)C.inv_cw_y);
-    sv.top_plus_rc = in_vgpr((Real)(C.slab_top + sqrt(a.pot.rc2)));
+    SlabView sv = slab_view(C, a, slab);
+    sv.inv_cap = in_vgpr(sv.inv_cap);
+    sv.inv_cw_x = in_vgpr(sv.inv_cw_x); sv.inv_cw_y = in_vgpr(sv.inv_cw_y);
+    sv.top_plus_rc = in_vgpr(sv.top_plus_rc);
     const double lx = in_vgpr(C.lx), ly = in_vgpr(C.ly), zlo = in_vgpr(C.zlo), zhi = in_vgpr(C.zhi);
     const double H = in_vgpr(C.zhi - C.zlo);
     const double md = in_vgpr(a.max_disp);
     const double tinv = in_vgpr(1.0 / beta);
     const double lnzv_v = in_vgpr(lnzv);
-    const int slab_scan = C.bins ? 9 * C.cap : slab_len;
+    const int slab_scan = sv.len;
     Real4 far;                      // a position beyond the cutoff of every atom: absent P or Q
     far.x = 0; far.y = 0; far.z = (Real)1.0e4; far.w = 0;
 
@@ -635,9 +617,9 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) batch_kernel(Swee
             Real es = 0;
             if (!ideal && v.z < sv.top_plus_rc) {
                 int cx = 0, cy = 0;
-                if (sv.bins) column_of_lanes(sv, v.x, v.y, cx, cy);
+                if (sv.mode != kSlabAll) column_of(sv, v.x, v.y, cx, cy);
                 for (int q = 0; q < slab_scan; ++q)
-                    es += lj(dist2(b, v.x, v.y, v.z, sv.atoms[sv.bins ? block_entry(sv, cx, cy, q) : q]), gs);
+                    es += lj(dist2(b, v.x, v.y, v.z, sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, q) : q]), gs);
             }
             eslab[k] = es;
         }
@@ -718,12 +700,12 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) batch_kernel(Swee
                     // slab terms at the new position only (the old one's are cached)
                     if (__any(need_slab)) {
                         int cx = 0, cy = 0;
-                        if (sv.bins) column_of_lanes(sv, P.x, P.y, cx, cy);
+                        if (sv.mode != kSlabAll) column_of(sv, P.x, P.y, cx, cy);
                         for (int k0 = 0; k0 < slab_scan; k0 += G) {
                             const int k = k0 + gl;
                             const bool v = need_slab && k < slab_scan;
                             const int kk = k < slab_scan ? k : 0;
-                            const Real4 s4 = sv.atoms[sv.bins ? block_entry(sv, cx, cy, kk) : kk];
+                            const Real4 s4 = sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, kk) : kk];
                             const Real r2p = dist2(b, P.x, P.y, P.z, s4);
                             core |= v && r2p < gs.hc2;
                             if (COUNT) use += (uint32_t)(v && r2p < gs.rc2);
@@ -947,14 +929,14 @@ __device__ __forceinline__ void mw_terms(const Real4 *gas, int n, int ex, const 
     }
     // slab at the new position only (the old one's is cached)
     if (NEW && slab_new) {
-        const int total = sv.bins ? 9 * sv.cap : sv.len;
+        const int total = sv.len;
         int cx = 0, cy = 0;
-        if (sv.bins) column_of(sv, P.x, P.y, cx, cy);
+        if (sv.mode != kSlabAll) column_of(sv, P.x, P.y, cx, cy);
         for (int k0 = 0; k0 < total; k0 += 2 * kWave) {
             const int ka = k0 + lane, kb = ka + kWave;
             const bool va = ka < total, vb = kb < total;
-            const Real4 sa = sv.atoms[sv.bins ? block_entry(sv, cx, cy, va ? ka : 0) : (va ? ka : 0)];
-            const Real4 sb = sv.atoms[sv.bins ? block_entry(sv, cx, cy, vb ? kb : 0) : (vb ? kb : 0)];
+            const Real4 sa = sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, va ? ka : 0) : (va ? ka : 0)];
+            const Real4 sb = sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, vb ? kb : 0) : (vb ? kb : 0)];
             const Real ra = dist2(b, P.x, P.y, P.z, sa), rb = dist2(b, P.x, P.y, P.z, sb);
             core |= (va && ra < gs.hc2) || (vb && rb < gs.hc2);
             if (COUNT) use += (uint32_t)(va && ra < gs.rc2) + (uint32_t)(vb && rb < gs.rc2);
@@ -982,17 +964,7 @@ __global__ void __launch_bounds__(kWave * B, kSweepWavesPerSimd) mw_kernel(Sweep
     Real *eslab = reinterpret_cast<Real *>(smem + L.eslab) + (size_t)h * a.gas_stride;
     double *rec = reinterpret_cast<double *>(smem + L.rec);     // [parity][wave][kMwRecDoubles]
 
-    const int slab_len = C.slab_len;
-    for (int k = threadIdx.x; k < slab_len; k += blockDim.x) {
-#if defined(REGC_FP64)
-        const double *src = a.slab4 + 4 * (size_t)(C.slab_off + k);
-#else
-        const float *src = a.slab4f + 4 * (size_t)(C.slab_off + k);
-#endif
-        Real4 v;
-        v.x = src[0]; v.y = src[1]; v.z = src[2]; v.w = 0;
-        slab[k] = v;
-    }
+    load_slab(C, a, slab, threadIdx.x, blockDim.x);
     for (int k = threadIdx.x; k < a.gas_stride + 2; k += blockDim.x) lnk[k] = a.lnk[k];
     __syncthreads();
 
@@ -1007,26 +979,23 @@ __global__ void __launch_bounds__(kWave * B, kSweepWavesPerSimd) mw_kernel(Sweep
     const double lnz = a.lnz[sg];
 
     Box b;
-    b.lx = in_vgpr((Real)C.lx); b.ly = in_vgpr((Real)C.ly); b.hx = in_vgpr((Real)C.half_lx);
-    b.hy = in_vgpr((Real)C.half_ly); b.ix = in_vgpr((Real)C.inv_lx); b.iy = in_vgpr((Real)C.inv_ly);
+    b.lx = in_vgpr((Real)C.lx); b.ly = in_vgpr((Real)C.ly);
     Pair gg, gs;
     gg.sig2 = in_vgpr((Real)a.pot.sig2_gg); gg.eps4 = in_vgpr((Real)a.pot.eps4_gg);
     gg.shift = in_vgpr((Real)a.pot.shift_gg); gg.rc2 = in_vgpr((Real)a.pot.rc2); gg.hc2 = in_vgpr((Real)a.pot.hc2_gg);
     gs.sig2 = in_vgpr((Real)a.pot.sig2_gs); gs.eps4 = in_vgpr((Real)a.pot.eps4_gs);
     gs.shift = in_vgpr((Real)a.pot.shift_gs); gs.rc2 = gg.rc2; gs.hc2 = in_vgpr((Real)a.pot.hc2_gs);
     const bool ideal = a.pot.ideal != 0;
-    SlabView sv;
-    sv.atoms = slab; sv.len = slab_len; sv.bins = C.bins;
-    sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
-    sv.inv_cap = in_vgpr(C.bins ? 1.0f / (float)C.cap : 0.f);
-    sv.inv_cw_x = in_vgpr((Real)C.inv_cw_x); sv.inv_cw_y = in_vgpr((Real)C.inv_cw_y);
-    sv.top_plus_rc = in_vgpr((Real)(C.slab_top + sqrt(a.pot.rc2)));
+    SlabView sv = slab_view(C, a, slab);
+    sv.inv_cap = in_vgpr(sv.inv_cap);
+    sv.inv_cw_x = in_vgpr(sv.inv_cw_x); sv.inv_cw_y = in_vgpr(sv.inv_cw_y);
+    sv.top_plus_rc = in_vgpr(sv.top_plus_rc);
     const double lx = in_vgpr(C.lx), ly = in_vgpr(C.ly), zlo = in_vgpr(C.zlo), zhi = in_vgpr(C.zhi);
     const double H = in_vgpr(C.zhi - C.zlo);
     const double md = in_vgpr(a.max_disp);
     const double tinv = in_vgpr(1.0 / beta);
     const double lnzv_v = in_vgpr(lnz + C.lnv);
-    const int slab_scan = C.bins ? 9 * C.cap : slab_len;
+    const int slab_scan = sv.len;
     Real4 far;                      // a position beyond the cutoff of every atom: absent P or Q
     far.x = 0; far.y = 0; far.z = (Real)1.0e4; far.w = 0;
 
@@ -1041,9 +1010,9 @@ __global__ void __launch_bounds__(kWave * B, kSweepWavesPerSimd) mw_kernel(Sweep
             Real es = 0;
             if (!ideal && v.z < sv.top_plus_rc) {
                 int cx = 0, cy = 0;
-                if (sv.bins) column_of_lanes(sv, v.x, v.y, cx, cy);
+                if (sv.mode != kSlabAll) column_of(sv, v.x, v.y, cx, cy);
                 for (int q = 0; q < slab_scan; ++q)
-                    es += lj(dist2(b, v.x, v.y, v.z, sv.atoms[sv.bins ? block_entry(sv, cx, cy, q) : q]), gs);
+                    es += lj(dist2(b, v.x, v.y, v.z, sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, q) : q]), gs);
             }
             eslab[k] = es;
         }
@@ -1345,7 +1314,7 @@ __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const P
                 fx += g * dx; fy += g * dy; fz += g * dz;
                 ei += 0.5 * (pot.eps4_gg * (s6 * s6 - s6) - pot.shift_gg);
             }
-            const int ns = sv.bins ? sv.ncx * sv.ncy * sv.cap : sv.len;
+            const int ns = sv.mode != kSlabAll ? sv.ncx * sv.ncy * sv.cap : sv.len;    // (no halo with MD)
             for (int k = 0; k < ns; ++k) {
                 const Real4 sa = sv.atoms[k];
                 const double dx = md_min_image(xi - (double)sa.x, lx);
@@ -1442,7 +1411,7 @@ __device__ double md_run(Real4 *gas, double *v, double *f, int n, double T, cons
 __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(SweepArgs a, PaperArgs pa)
 {
     extern __shared__ __align__(32) unsigned char smem[];
-    const int wave = threadIdx.x / kWave;
+    const int wave = scalar((int)(threadIdx.x / kWave));
     const int lane = threadIdx.x % kWave;
     const int waves = blockDim.x / kWave;
     const int blk = blockIdx.x;
@@ -1458,17 +1427,7 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
     double *mdv = reinterpret_cast<double *>(smem + lds_round(L.total)) + (size_t)wave * a.gas_stride * 6;
     double *mdf = mdv + (size_t)a.gas_stride * 3;
 
-    const int slab_len = C.slab_len;
-    for (int k = threadIdx.x; k < slab_len; k += blockDim.x) {
-#if defined(REGC_FP64)
-        const double *src = a.slab4 + 4 * (size_t)(C.slab_off + k);
-#else
-        const float *src = a.slab4f + 4 * (size_t)(C.slab_off + k);
-#endif
-        Real4 v;
-        v.x = src[0]; v.y = src[1]; v.z = src[2]; v.w = 0;
-        slab[k] = v;
-    }
+    load_slab(C, a, slab, threadIdx.x, blockDim.x);
     for (int k = threadIdx.x; k < a.gas_stride + 2; k += blockDim.x) lnk[k] = a.lnk[k];
     __syncthreads();
     if (wave >= nw) return;
@@ -1476,7 +1435,7 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
     const int w = a.block_w0[blk] + wave;
     double tv = use_md ? pa.tv[w] : 0.0;
     const int n_max = C.n_max;
-    int n = a.n[w];
+    int n = scalar(a.n[w]);
     double e = a.e[w];
     const int label = a.label[w];
     const int sg = C.state_off + label;
@@ -1496,24 +1455,19 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
     wave_sync();
 
     Box b;
-    b.lx = (Real)C.lx; b.ly = (Real)C.ly; b.hx = (Real)C.half_lx; b.hy = (Real)C.half_ly;
-    b.ix = (Real)C.inv_lx; b.iy = (Real)C.inv_ly;
+    b.lx = (Real)C.lx; b.ly = (Real)C.ly;
     Pair gg, gs;
     gg.sig2 = (Real)a.pot.sig2_gg; gg.eps4 = (Real)a.pot.eps4_gg; gg.shift = (Real)a.pot.shift_gg;
     gg.rc2 = (Real)a.pot.rc2; gg.hc2 = (Real)a.pot.hc2_gg;
     gs.sig2 = (Real)a.pot.sig2_gs; gs.eps4 = (Real)a.pot.eps4_gs; gs.shift = (Real)a.pot.shift_gs;
     gs.rc2 = gg.rc2; gs.hc2 = (Real)a.pot.hc2_gs;
     const bool ideal = a.pot.ideal != 0;
-    SlabView sv;
-    sv.atoms = slab; sv.len = slab_len; sv.bins = C.bins;
-    sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
-    sv.inv_cap = C.bins ? 1.0f / (float)C.cap : 0.f;
-    sv.inv_cw_x = (Real)C.inv_cw_x; sv.inv_cw_y = (Real)C.inv_cw_y;
-    sv.top_plus_rc = (Real)(C.slab_top + sqrt(a.pot.rc2));
+    const SlabView sv = slab_view(C, a, slab);
+    const SlabLane sl = slab_lane<1>(sv, lane, 0);
     const double lx = C.lx, ly = C.ly, zlo = C.zlo, zhi = C.zhi, H = C.zhi - C.zlo;
     const double md = a.max_disp;
     const double tinv = 1.0 / beta;
-    const int slab_scan = C.bins ? 9 * C.cap : slab_len;
+    const int slab_scan = sv.len;
 
     uint32_t stat = 0;
     uint32_t useful = 0;
@@ -1566,7 +1520,7 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
                 } else {
                     const double lnU = bcast(f3, 2 * tt + 1);
                     const double ux = bcast(f0, 2 * tt), uy = bcast(f1, 2 * tt), uz = bcast(f2, 2 * tt + 1);
-                    const int i = kind == 1 ? -1 : (int)(((uint64_t)A1 * (uint64_t)n) >> 32);
+                    const int i = kind == 1 ? -1 : (int)__umulhi(A1, (uint32_t)n);
                     const Real4 o = gas[kind == 1 ? 0 : i];
                     double px = 0.0, py = 0.0, pz = 0.0, c;
                     bool wall = false;
@@ -1586,36 +1540,35 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
                     } else {
                         c = lnk[n] - lnzv;
                     }
-                    if (wall) {
+                    if (uniform(wall)) {
                         stat += lane == 8;
                     } else {
                         const double thr = (c - lnU) * tinv;
                         const Real qx = (Real)px, qy = (Real)py, qz = (Real)pz;
                         double de = 0.0;
-                        bool core = false;
+                        uint64_t core = 0;
                         if (!ideal) {
                             Real pd;
+                            bool near = false;
                             if (kind == 0)
-                                pd = partial_delta<true, true, 1, false>(gas, n, i, sv, b, gg, gs, lane, 0, qx, qy, qz,
-                                                                         o.x, o.y, o.z, nullptr, nullptr, core,
-                                                                         useful);
+                                pd = lane_delta<true, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, qx, qy, qz,
+                                                                      o.x, o.y, o.z, nullptr, nullptr, core, useful,
+                                                                      near);
                             else if (kind == 1)
-                                pd = partial_delta<true, false, 1, false>(gas, n, -1, sv, b, gg, gs, lane, 0, qx, qy,
-                                                                          qz, qx, qy, qz, nullptr, nullptr, core,
-                                                                          useful);
+                                pd = lane_delta<true, false, 1, false>(gas, n, -1, sv, sl, b, gg, gs, lane, 0, qx, qy,
+                                                                       qz, qx, qy, qz, nullptr, nullptr, core, useful, near);
                             else
-                                pd = partial_delta<false, true, 1, false>(gas, n, i, sv, b, gg, gs, lane, 0, o.x, o.y,
-                                                                          o.z, o.x, o.y, o.z, nullptr, nullptr, core,
-                                                                          useful);
+                                pd = lane_delta<false, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, o.x, o.y,
+                                                                       o.z, o.x, o.y, o.z, nullptr, nullptr, core,
+                                                                       useful, near);
+                            pd = wave_sum(pd);
                             de = (double)pd;
                             const uint64_t mult = kind == 0 ? 2 : 1;
-                            const Real zmin = kind == 0 ? (qz < o.z ? qz : o.z) : (kind == 1 ? qz : o.z);
-                            cand += mult * (uint64_t)((kind == 1 ? n : n - 1) +
-                                                      (zmin < sv.top_plus_rc ? slab_scan : 0));
+                            cand += mult * (uint64_t)((kind == 1 ? n : n - 1) + (near ? slab_scan : 0));
                         }
-                        if (core && kind != 2) {
+                        if (core != 0 && kind != 2) {
                             stat += lane == 9;
-                        } else if (de <= thr) {
+                        } else if (uniform(de <= thr)) {
                             accepted = true;
                             stat += lane == 2 * kind + 1;
                             e += de;
@@ -1711,8 +1664,7 @@ __global__ void __launch_bounds__(256) ENERGY_KERNEL(EnergyArgs a)
     const int cid = a.walker_class[w];
     const ClassDev &C = a.cls[cid];
     Box b;
-    b.lx = (Real)C.lx; b.ly = (Real)C.ly; b.hx = (Real)C.half_lx; b.hy = (Real)C.half_ly;
-    b.ix = (Real)C.inv_lx; b.iy = (Real)C.inv_ly;
+    b.lx = (Real)C.lx; b.ly = (Real)C.ly;
     Pair gg, gs;
     gg.sig2 = (Real)a.pot.sig2_gg; gg.eps4 = (Real)a.pot.eps4_gg; gg.shift = (Real)a.pot.shift_gg;
     gg.rc2 = (Real)a.pot.rc2; gg.hc2 = (Real)a.pot.hc2_gg;
