@@ -47,6 +47,9 @@ struct DevBuf {
         n = count;
         return REGC_OK;
     }
+    // at least `count` elements, their contents undefined; an allocation that is large
+    // enough stays
+    int reserve(size_t count) { return p && n >= count ? REGC_OK : alloc(count); }
     void release()
     {
         if (p) (void)hipFree(p);

@@ -575,6 +575,495 @@ __global__ void rep_sd(int B, int K, const double *rep, double *sd)
     sd[k] = sqrt(v / (double)(B - 1));
 }
 
+// ---- the iteration on bounded exponents ----
+// With c = the middle of the inverse temperatures and E0(N) the middle of the energies
+// sampled at N, every sample's softmax is that of
+//     -(beta_l - c)(E - E0) + [log A_l(N) - beta_l E0 - shift(N)],
+// the bracket at most 0 by the choice of shift(N).  When no |beta_l - c| |E - E0|
+// exceeds kMaxExponent (checked once per set of samples), the exponentials
+// X_l = exp(-(beta_l - c)(E - E0)) and their sum with the weights a_l = exp(bracket) stay
+// in range without a maximum per sample, and
+//     sum_{n at N} e^{-beta_l E_n} / D_n = e^{-beta_l E0 - shift} Q_l(N),  Q_l(N) = sum_n X_l / sum_k a_k X_k,
+// is what the new free energies need.  Samples outside that range take mbar_chunk.
+constexpr double kMaxExponent = 300.0;
+
+// exp(x) for |x| <= 708: x = k ln 2 + r (Cody and Waite's reduction, the product fused),
+// the Taylor series of exp(r) to r^13 / 13! (|r| <= 0.35: below 5e-18 relative), 2^k by
+// the exponent.  Within one unit in the last place, like the library's, without its
+// checks for overflow.
+__device__ __forceinline__ double exp_bounded(double x)
+{
+    const double k = rint(x * 1.4426950408889634);
+    const double r = fma(k, -2.3190468138462996e-17, fma(k, -0.6931471805599453, x));
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return __builtin_amdgcn_ldexp(p, (int)k);
+}
+
+// 1 / x of a normal positive x: the hardware's estimate and two Newton steps (within one
+// unit in the last place).
+__device__ __forceinline__ double recip(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(fma(-x, y, 1.0), y, y);
+    return fma(fma(-x, y, 1.0), y, y);
+}
+
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
+// sum over each quad of lanes, in every lane of the quad
+__device__ __forceinline__ double quad_total(double v)
+{
+    v += dpp_move<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
+    v += dpp_move<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
+    return v;
+}
+
+// wave total (fixed order) as a wave-uniform value
+__device__ __forceinline__ double wave_total(double v)
+{
+    v = quad_total(v);
+    v += dpp_move<0x141, 0xF>(v);   // row_half_mirror
+    v += dpp_move<0x140, 0xF>(v);   // row_mirror
+    v += dpp_move<0x142, 0xA>(v);   // row_bcast:15 into rows 1, 3
+    v += dpp_move<0x143, 0xC>(v);   // row_bcast:31 into rows 2, 3
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), 63),
+                            __builtin_amdgcn_readlane(__double2loint(v), 63));
+}
+
+// Middle and half width of the energies sampled at each N (block).
+__global__ void __launch_bounds__(kMbarThreads) mbar_range(const double *e, const int *chunk_b, const int *chunk_e,
+                                                        const int *seg_c0, const int *seg_c1, double *mid, double *half)
+{
+    __shared__ double lo_s[kMbarThreads / 64], hi_s[kMbarThreads / 64];
+    const int N = blockIdx.x, c0 = seg_c0[N], c1 = seg_c1[N];
+    double lo = INFINITY, hi = -INFINITY, bad = 0.0;
+    if (c1 > c0)
+        for (int i = chunk_b[c0] + threadIdx.x; i < chunk_e[c1 - 1]; i += blockDim.x) {
+            const double E = e[i];
+            bad += E - E;             // NaN when an energy is not finite
+            lo = fmin(lo, E);
+            hi = fmax(hi, E);
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o));
+        hi = fmax(hi, __shfl_xor(hi, o));
+        bad += __shfl_xor(bad, o);
+    }
+    if (threadIdx.x % 64 == 0) {
+        lo_s[threadIdx.x / 64] = lo + bad;
+        hi_s[threadIdx.x / 64] = hi + bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        bool nan = false;
+        for (int k = 0; k < kMbarThreads / 64; ++k) {
+            nan |= !(lo_s[k] == lo_s[k]) || !(hi_s[k] == hi_s[k]);
+            lo = fmin(lo, lo_s[k]);
+            hi = fmax(hi, hi_s[k]);
+        }
+        mid[N] = c1 > c0 ? 0.5 * lo + 0.5 * hi : 0.0;
+        half[N] = nan ? NAN : (c1 > c0 ? 0.5 * hi - 0.5 * lo : 0.0);
+    }
+}
+
+// What the kernels of an iteration share; problem b of a batch has its own weights,
+// iterate and state.
+struct SolveState {
+    int done, conv, it, plain_left;
+    int hist, head;                  // differences' history: entries, slot of the oldest
+    int gauge, memory;               // first sampled state; at most this many differences
+    double delta, d_prev;
+};
+
+constexpr int kMaxMemory = 8;        // differences the device's least squares holds
+constexpr int kMaxStepStates = 4096; // states it holds (4 per thread of 1024)
+
+struct SolveArgs {
+    int L, M, S, nN, nchunks, sub, rows;       // rows = nchunks * sub partial sums per temperature
+    const double *beta_l, *lnz;
+    double beta_c;
+    const double *e, *mid;
+    const int *chunk_n, *chunk_b, *chunk_e, *seg_c0, *seg_c1;
+    const double *lnomega;                     // [B][S]
+    double *f, *fnew, *good;                   // [B][S]
+    double *hist_r, *hist_g;                   // [B][kMaxMemory + 1][S]
+    double *shift;                             // [B][nN]
+    double *partial;                           // [B][L][rows]
+    SolveState *st;                            // [B]
+    int method, max_iter;
+    double tol;
+    unsigned int *arrived;                     // [0] blocks of a step launch done with it, [1] step launches done
+    volatile int *host;                        // host memory: [0] step launches done, [1] problems done
+};
+
+// log A_l(N) - beta_l E0(N) of every temperature into la [L] (LDS), block-wide, 256
+// threads: G threads per temperature take its chemical potentials.
+__device__ __forceinline__ void weights_log(const SolveArgs &p, const double *lnomega, const double *f, int N, double *la)
+{
+    const int G = p.L <= 8 ? 32 : (p.L <= 16 ? 16 : (p.L <= 32 ? 8 : 4));
+    const int l = threadIdx.x / G, g = threadIdx.x % G;
+    double mx = -INFINITY, sum = 0.0;
+    if (l < p.L)
+        for (int m = g; m < p.M; m += G) {
+            const int s = l * p.M + m;
+            const double v = lnomega[s] + f[s] + (double)N * p.lnz[s];
+            if (lnomega[s] == -INFINITY) continue;
+            mx = v > mx ? v : mx;
+        }
+    for (int o = G / 2; o > 0; o >>= 1) {
+        const double t = __shfl_xor(mx, o);
+        mx = t > mx ? t : mx;
+    }
+    if (l < p.L && mx != -INFINITY)
+        for (int m = g; m < p.M; m += G) {
+            const int s = l * p.M + m;
+            if (lnomega[s] == -INFINITY) continue;
+            sum += exp(lnomega[s] + f[s] + (double)N * p.lnz[s] - mx);
+        }
+    for (int o = G / 2; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if (l < p.L && g == 0) la[l] = mx == -INFINITY ? -INFINITY : mx + log(sum) - p.beta_l[l] * p.mid[N];
+    __syncthreads();
+}
+
+// One pass over the samples for one problem: the weights a_l of the chunk's N, then per
+// sample its L exponentials and their sum.  Four lanes share a sample, each with every
+// fourth temperature (J of them), so that their weights, exponents and sums stay in
+// registers; a thread with all temperatures of a sample needed 256 registers and left
+// the unit waiting (1.02e6 samples x 32 temperatures: 87 us, this 45 us).  Bound: FP64
+// issue, about 22 operations per sample and temperature (18 us of it).
+// Writes Q_l of its part of the chunk, or (LOGD) log D of its samples.
+template <int J, bool LOGD>
+__global__ void __launch_bounds__(kMbarThreads) mbar_pass(SolveArgs p, double *logd)
+{
+    __shared__ double la[kMaxL];
+    __shared__ double red[kMbarThreads / 64][4 * J];
+    if (!LOGD && p.st[0].done) return;
+    const int c = blockIdx.x / p.sub, part = blockIdx.x % p.sub;
+    const int N = p.chunk_n[c];
+    weights_log(p, p.lnomega, p.f, N, la);
+    double shift = -INFINITY;
+    for (int l = 0; l < p.L; ++l) shift = la[l] > shift ? la[l] : shift;
+    if (!LOGD && part == 0 && threadIdx.x == 0) p.shift[N] = shift;
+    const int q = threadIdx.x & 3;
+    double a[J], db[J], acc[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int l = q + 4 * j;
+        a[j] = l < p.L ? exp(la[l] - shift) : 0.0;
+        db[j] = l < p.L ? p.beta_c - p.beta_l[l] : 0.0;
+        acc[j] = 0.0;
+    }
+    const double mid = p.mid[N];
+    const int step = p.sub * (kMbarThreads / 4);
+    const int end = p.chunk_e[c];
+    for (int i = p.chunk_b[c] + part * (kMbarThreads / 4) + (int)(threadIdx.x >> 2); i < end; i += step) {
+        const double t = p.e[i] - mid;
+        double x[J], d = 0.0;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            x[j] = exp_bounded(db[j] * t);
+            d = fma(a[j], x[j], d);
+        }
+        d = quad_total(d);
+        if (LOGD) {
+            if (q == 0) logd[i] = shift - p.beta_c * t + log(d);
+        } else {
+            const double inv = recip(d);
+#pragma unroll
+            for (int j = 0; j < J; ++j) acc[j] = fma(x[j], inv, acc[j]);
+        }
+    }
+    if (LOGD) return;
+    // the quads' sums: across the lanes of a wave that hold the same temperatures, then
+    // the waves in order
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        double v = acc[j];
+#pragma unroll
+        for (int o = 4; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        if (lane < 4) red[wave][lane + 4 * j] = v;
+    }
+    __syncthreads();
+    for (int l = threadIdx.x; l < p.L; l += blockDim.x) {
+        double v = 0.0;
+        for (int wv = 0; wv < kMbarThreads / 64; ++wv) v += red[wv][l];
+        p.partial[(size_t)l * p.rows + blockIdx.x] = v;
+    }
+}
+
+// New free energies of problem blockIdx.y, temperature blockIdx.x: the partial sums of
+// each N (threads), then a wave per chemical potential sums over N.
+constexpr int kFnewThreads = 512;
+
+__global__ void __launch_bounds__(kFnewThreads) mbar_fnew_q(SolveArgs p)
+{
+    extern __shared__ double logB[];
+    const int l = blockIdx.x, b = blockIdx.y;
+    if (p.st[b].done) return;
+    const double *part = p.partial + ((size_t)b * p.L + l) * p.rows;
+    const double *lnomega = p.lnomega + (size_t)b * p.S + (size_t)l * p.M;
+    // a temperature without samples has no weight A_l at any N: its states get no value
+    int any = 0;
+    for (int m = threadIdx.x; m < p.M; m += blockDim.x) any |= lnomega[m] != -INFINITY;
+    any = __syncthreads_or(any);
+    for (int N = threadIdx.x; N < p.nN; N += blockDim.x) {
+        double Q = 0.0;
+        for (int c = p.seg_c0[N] * p.sub; c < p.seg_c1[N] * p.sub; ++c) Q += part[c];
+        logB[N] = any && Q > 0.0 ? log(Q) - p.beta_l[l] * p.mid[N] - p.shift[(size_t)b * p.nN + N] : -INFINITY;
+    }
+    __syncthreads();
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    for (int m = wave; m < p.M; m += kFnewThreads / 64) {
+        const double lz = p.lnz[l * p.M + m];
+        double mx = -INFINITY;
+        for (int N = lane; N < p.nN; N += 64) mx = fmax(mx, fma((double)N, lz, logB[N]));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+        double sum = 0.0;
+        if (mx != -INFINITY)
+            for (int N = lane; N < p.nN; N += 64) sum += exp(fma((double)N, lz, logB[N]) - mx);
+        sum = wave_total(sum);
+        if (lane == 0) p.fnew[(size_t)b * p.S + l * p.M + m] = -(mx + log(sum));
+    }
+}
+
+// Sums of the values first .. NV - 1 over a block of T threads, in every thread.
+template <int T, int NV>
+__device__ __forceinline__ void block_sums(double (&v)[NV], double (*red)[NV], int first)
+{
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+#pragma unroll
+    for (int k = first; k < NV; ++k) v[k] = wave_total(v[k]);
+    if (T > 64) {
+        __syncthreads();              // earlier readers of red are done
+#pragma unroll
+        for (int k = first; k < NV; ++k)
+            if (lane == 0) red[wave][k] = v[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = first; k < NV; ++k) {
+            v[k] = 0.0;
+#pragma unroll
+            for (int w = 0; w < T / 64; ++w) v[k] += red[w][k];
+        }
+    }
+}
+
+// The rest of an iteration for problem blockIdx.x: gauge, convergence, and the next
+// iterate -- the map's value (method 0), or Anderson's mixture of the last map values
+// (method 1; see solve_core).  One block of T threads with R states each: the least
+// squares is a modified Gram-Schmidt whose columns stay in registers, one block-wide
+// reduction per column.  On the host it cost a copy each way, a synchronisation and the
+// host's own sums every iteration (70 us of 230 at 1024 states).
+template <int T, int R>
+__global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
+{
+    constexpr int K = kMaxMemory;
+    __shared__ double red[T / 64][K + 1];
+    __shared__ double Rs[K][K], qs[K];       // the triangular factor and Q^T r
+    const int b = blockIdx.x, tid = threadIdx.x;
+    SolveState &st = p.st[b];
+    if (!st.done) {
+        const double *lnomega = p.lnomega + (size_t)b * p.S, *fnew = p.fnew + (size_t)b * p.S;
+        double *f = p.f + (size_t)b * p.S, *good = p.good + (size_t)b * p.S;
+        double *hr = p.hist_r + (size_t)b * (K + 1) * p.S, *hg = p.hist_g + (size_t)b * (K + 1) * p.S;
+        const double f0 = fnew[st.gauge];
+        const int it = st.it + 1;
+        double g[R], r[R], d = 0.0;
+        bool on[R];
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int s = tid + T * k;
+            const bool in = s < p.S;
+            on[k] = in && lnomega[s] != -INFINITY;
+            g[k] = in ? fnew[s] - f0 : 0.0;
+            r[k] = on[k] ? g[k] - f[s] : 0.0;
+            const double a = fabs(r[k]);
+            d = (a > d || a != a) ? a : d;           // a NaN propagates: the solve must see it
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double t = __shfl_xor(d, o);
+            d = (t > d || t != t) ? t : d;
+        }
+        if (T > 64) {
+            if (tid % 64 == 0) red[tid / 64][0] = d;
+            __syncthreads();
+            d = 0.0;
+            for (int w = 0; w < T / 64; ++w) {
+                const double t = red[w][0];
+                d = (t > d || t != t) ? t : d;
+            }
+        }
+        // every thread takes the same decisions from the same values
+        int done = 0, conv = 0, hist = st.hist, head = st.head, plain_left = st.plain_left;
+        double d_prev = st.d_prev;
+        const int slots = st.memory + 1;
+        const bool finite = d <= 1e300;
+        if (p.method == 0 || (!finite && it == 1) || (finite && d < p.tol)) {
+            // plain step, or the end: f is the map's value
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (tid + T * k < p.S) f[tid + T * k] = g[k];
+            const bool check = p.method == 1 || it % 10 == 0 || it == p.max_iter;
+            conv = check && finite && d < p.tol;
+            done = check && (conv || !finite);
+        } else if (!finite) {
+            // back to the last finite map value, plain steps for a while
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (tid + T * k < p.S) f[tid + T * k] = good[tid + T * k];
+            hist = 0;
+            plain_left = 5;
+            d_prev = INFINITY;
+        } else {
+            if (d > 10.0 * d_prev) hist = 0;
+            d_prev = d;
+            // the new residual and map value take a free slot, or the oldest's
+            if (hist == slots) head = (head + 1) % slots;
+            else ++hist;
+            const int now = (head + hist - 1) % slots;
+            const int mk = hist - 1;
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                const int s = tid + T * k;
+                if (s < p.S) {
+                    hr[(size_t)now * p.S + s] = r[k];
+                    hg[(size_t)now * p.S + s] = g[k];
+                    good[s] = g[k];
+                }
+            }
+            double gamma[K] = {};
+            const bool mix = plain_left == 0 && mk > 0;
+            if (mix) {
+                // columns: consecutive differences of the residuals, oldest first
+                double q[K][R];
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int k = 0; k < R; ++k) {
+                        const int s = tid + T * k;
+                        q[j][k] = 0.0;
+                        if (j < mk && on[k]) {
+                            const double lo = hr[(size_t)((head + j) % slots) * p.S + s];
+                            const double hi = j + 1 == mk ? r[k] : hr[(size_t)((head + j + 1) % slots) * p.S + s];
+                            q[j][k] = hi - lo;
+                        }
+                    }
+                double norm0[K + 1] = {};
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+#pragma unroll
+                    for (int i = 0; i < K; ++i) norm0[i] = fma(q[i][k], q[i][k], norm0[i]);
+                block_sums<T>(norm0, red, 0);
+                unsigned keep = 0;
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    if (j >= mk) break;
+                    // column j against itself, the later columns and the residual
+                    double v[K + 1] = {};
+#pragma unroll
+                    for (int k = 0; k < R; ++k) {
+#pragma unroll
+                        for (int i = j; i < K; ++i) v[i] = fma(q[j][k], q[i][k], v[i]);
+                        v[K] = fma(q[j][k], r[k], v[K]);
+                    }
+                    block_sums<T>(v, red, j);
+                    const double nn = v[j];
+                    // a column that depends on earlier ones is left out
+                    if (!(nn > 1e-24 * (norm0[j] + 1e-300))) continue;
+                    keep |= 1u << j;
+                    const double len = sqrt(nn);
+                    if (tid == 0) {
+                        qs[j] = v[K] / len;
+                        Rs[j][j] = len;
+                    }
+#pragma unroll
+                    for (int i = j + 1; i < K; ++i) {
+                        if (tid == 0) Rs[j][i] = v[i] / len;
+                        const double c = v[i] / nn;
+#pragma unroll
+                        for (int k = 0; k < R; ++k) q[i][k] = fma(-c, q[j][k], q[i][k]);
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = K - 1; j >= 0; --j) {
+                    if (!((keep >> j) & 1u)) continue;
+                    double v = qs[j];
+#pragma unroll
+                    for (int i = j + 1; i < K; ++i) v = fma(-Rs[j][i], gamma[i], v);    // (0 where left out)
+                    gamma[j] = v / Rs[j][j];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                const int s = tid + T * k;
+                if (s >= p.S) continue;
+                double v = g[k];
+                if (mix && on[k]) {
+                    double lo = hg[(size_t)head * p.S + s];
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        if (j >= mk) break;
+                        const double hi = j + 1 == mk ? g[k] : hg[(size_t)((head + j + 1) % slots) * p.S + s];
+                        v = fma(-gamma[j], hi - lo, v);
+                        lo = hi;
+                    }
+                }
+                f[s] = v;
+            }
+            if (plain_left > 0) --plain_left;
+        }
+        if (it >= p.max_iter) done = 1;
+        __syncthreads();              // every thread has read the state
+        if (tid == 0) {
+            st.done = done; st.conv = conv; st.it = it; st.plain_left = plain_left;
+            st.hist = hist; st.head = head;
+            st.delta = d; st.d_prev = d_prev;
+        }
+    }
+    // the last block of the launch tells the host how far the batch is
+    if (tid == 0) {
+        __threadfence();
+        if (atomicAdd(p.arrived, 1u) == gridDim.x - 1) {
+            *p.arrived = 0u;
+            __threadfence();
+            int it = 0, done = 0;
+            for (int k = 0; k < (int)gridDim.x; ++k) {
+                const SolveState *o = p.st + k;
+                it = max(it, __hip_atomic_load(&o->it, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                done += __hip_atomic_load(&o->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            p.host[1] = done;
+            __threadfence_system();
+            p.host[0] = (int)++p.arrived[1];
+            __threadfence_system();
+        }
+    }
+}
+
 }  // namespace regc
 
 using namespace regc;
@@ -600,6 +1089,19 @@ struct regc_mbar {
     DevBuf<int32_t> n_orig_d, s_orig_d;   // N and state of the samples in the order given
     DevBuf<double> wgt_d;                 // bootstrap multiplicities in sorted order
     bool weighted = false;
+    // the device-resident iteration
+    double beta_c = 0.0, beta_half = 0.0; // middle and half width of the inverse temperatures
+    DevBuf<double> mid_d, half_d;         // middle and half width of the energies sampled at each N
+    bool bounded = false;                 // the exponents around them stay below kMaxExponent
+    int sub = 1;                          // blocks per chunk of a pass
+    DevBuf<double> shift_d, q_d, hist_r_d, hist_g_d, good_d;
+    DevBuf<SolveState> state_d;
+    DevBuf<unsigned int> arrived_d;
+    int *progress = nullptr;              // host memory the step kernel writes (SolveArgs::host)
+    ~regc_mbar()
+    {
+        if (progress) (void)hipHostFree(progress);
+    }
 };
 
 static double lnz_of(double T, double mu, double lambda1)
@@ -624,11 +1126,15 @@ extern "C" int regc_mbar_create(const regc_grid *grid, double lambda1, int n_max
         mb->beta_l.push_back(1.0 / mb->t[l]);
         for (int m = 0; m < mb->M; ++m) mb->lnz.push_back(lnz_of(mb->t[l], mb->mu[m], lambda1));
     }
+    const auto ends = std::minmax_element(mb->beta_l.begin(), mb->beta_l.end());
+    mb->beta_c = 0.5 * (*ends.first + *ends.second);
+    mb->beta_half = 0.5 * (*ends.second - *ends.first);
     int rc;
     if ((rc = mb->beta_d.alloc(mb->L)) || (rc = mb->lnz_d.alloc(mb->S)) || (rc = mb->lnomega_d.alloc(mb->S)) ||
         (rc = mb->f_d.alloc(mb->S)) || (rc = mb->fnew_d.alloc(mb->S)) ||
         (rc = mb->logA_d.alloc((size_t)mb->L * mb->nN)) || (rc = mb->delta_d.alloc(1)) ||
-        (rc = mb->seg_c0_d.alloc(mb->nN)) || (rc = mb->seg_c1_d.alloc(mb->nN))) {
+        (rc = mb->seg_c0_d.alloc(mb->nN)) || (rc = mb->seg_c1_d.alloc(mb->nN)) || (rc = mb->mid_d.alloc(mb->nN)) ||
+        (rc = mb->half_d.alloc(mb->nN))) {
         delete mb;
         return rc;
     }
@@ -739,7 +1245,17 @@ extern "C" int regc_mbar_set_samples(regc_mbar *mb, int64_t ns, const double *e,
             if (mb->gauge < 0) mb->gauge = k;
         }
     REGC_HIP(hipMemcpyAsync(mb->lnomega_d.p, mb->lnomega.data(), sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(mbar_range, dim3(mb->nN), dim3(kMbarThreads), 0, s, mb->e_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p,
+                       mb->seg_c0_d.p, mb->seg_c1_d.p, mb->mid_d.p, mb->half_d.p);
+    REGC_HIP(hipGetLastError());
+    std::vector<double> half(mb->nN);
+    REGC_HIP(hipMemcpyAsync(half.data(), mb->half_d.p, sizeof(double) * mb->nN, hipMemcpyDeviceToHost, s));
     REGC_HIP(hipStreamSynchronize(s));
+    mb->bounded = true;
+    for (double h : half) mb->bounded = mb->bounded && mb->beta_half * h <= kMaxExponent;    // (false on a NaN)
+    // blocks per chunk: a few per compute unit (each carries the weights of its N, about as
+    // much work as 100 samples, so never below 256 samples a block)
+    mb->sub = (int)std::min<int64_t>(kChunk / 256, std::max<int64_t>(1, (1024 + mb->nchunks - 1) / mb->nchunks));
     mb->ns = ns;
     mb->have_samples = true;
     return REGC_OK;
@@ -782,6 +1298,156 @@ static hipError_t mbar_iteration(regc_mbar *mb)
     hipLaunchKernelGGL(mbar_gauge, dim3(1), dim3(1024), 0, s, mb->S, mb->gauge, mb->lnomega_d.p, mb->fnew_d.p,
                        mb->f_d.p, mb->delta_d.p);
     return hipGetLastError();
+}
+
+// ---- the device-resident solve ----
+// Whether the problem fits the device's iteration: energies in range of its exponents,
+// states and differences within the step kernel's registers (else the general iteration,
+// driven by the host).
+static bool device_solve(const regc_mbar *mb)
+{
+    return mb->bounded && !mb->weighted && mb->S <= kMaxStepStates && (mb->method == 0 || mb->memory <= kMaxMemory);
+}
+
+static SolveArgs solve_args(regc_mbar *mb)
+{
+    SolveArgs p{};
+    p.L = mb->L; p.M = mb->M; p.S = mb->S; p.nN = mb->nN;
+    p.nchunks = mb->nchunks; p.sub = mb->sub; p.rows = mb->nchunks * mb->sub;
+    p.beta_l = mb->beta_d.p; p.lnz = mb->lnz_d.p; p.beta_c = mb->beta_c;
+    p.e = mb->e_d.p; p.mid = mb->mid_d.p;
+    p.chunk_n = mb->chunk_n_d.p; p.chunk_b = mb->chunk_b_d.p; p.chunk_e = mb->chunk_e_d.p;
+    p.seg_c0 = mb->seg_c0_d.p; p.seg_c1 = mb->seg_c1_d.p;
+    p.lnomega = mb->lnomega_d.p;
+    p.f = mb->f_d.p; p.fnew = mb->fnew_d.p; p.good = mb->good_d.p;
+    p.hist_r = mb->hist_r_d.p; p.hist_g = mb->hist_g_d.p;
+    p.shift = mb->shift_d.p; p.partial = mb->q_d.p; p.st = mb->state_d.p;
+    p.arrived = mb->arrived_d.p; p.host = mb->progress;
+    p.method = mb->method;
+    return p;
+}
+
+// Workspace for B problems, kept with the handle and grown when a larger one is asked for.
+static int solve_workspace(regc_mbar *mb, int B)
+{
+    int rc;
+    const size_t hist = (size_t)B * (kMaxMemory + 1) * mb->S;
+    if ((rc = mb->shift_d.reserve((size_t)B * mb->nN)) || (rc = mb->q_d.reserve((size_t)B * mb->L * mb->nchunks * mb->sub)) ||
+        (rc = mb->hist_r_d.reserve(hist)) || (rc = mb->hist_g_d.reserve(hist)) ||
+        (rc = mb->good_d.reserve((size_t)B * mb->S)) || (rc = mb->state_d.reserve(B)) || (rc = mb->arrived_d.reserve(2)))
+        return rc;
+    if (!mb->progress) REGC_HIP(hipHostMalloc((void **)&mb->progress, 2 * sizeof(int), hipHostMallocDefault));
+    return REGC_OK;
+}
+
+static hipError_t launch_pass(regc_mbar *mb, const SolveArgs &p, double *logd)
+{
+    const dim3 grid(p.rows), block(kMbarThreads);
+#define PASS_CASE(J)                                                                                          \
+    do {                                                                                                      \
+        if (logd) hipLaunchKernelGGL((mbar_pass<J, true>), grid, block, 0, mb->stream, p, logd);              \
+        else hipLaunchKernelGGL((mbar_pass<J, false>), grid, block, 0, mb->stream, p, logd);                  \
+    } while (0)
+    if (p.L <= 8) PASS_CASE(2);
+    else if (p.L <= 16) PASS_CASE(4);
+    else if (p.L <= 32) PASS_CASE(8);
+    else PASS_CASE(16);
+#undef PASS_CASE
+    return hipGetLastError();
+}
+
+static hipError_t launch_step(regc_mbar *mb, const SolveArgs &p, int B)
+{
+    if (p.S <= 64) hipLaunchKernelGGL((mbar_step<64, 1>), dim3(B), dim3(64), 0, mb->stream, p);
+    else if (p.S <= 256) hipLaunchKernelGGL((mbar_step<256, 1>), dim3(B), dim3(256), 0, mb->stream, p);
+    else if (p.S <= 1024) hipLaunchKernelGGL((mbar_step<256, 4>), dim3(B), dim3(256), 0, mb->stream, p);
+    else hipLaunchKernelGGL((mbar_step<1024, 4>), dim3(B), dim3(1024), 0, mb->stream, p);
+    return hipGetLastError();
+}
+
+// Runs iterations (enqueued by `iteration`) until every one of B problems has set its
+// state's done.  The step kernel reports to host memory; the host keeps a few iterations
+// enqueued ahead of the report (those past the end return at once) and never waits for
+// the stream.
+template <typename F>
+static int run_iterations(regc_mbar *mb, int B, int max_iter, F iteration)
+{
+    constexpr int kAhead = 6;
+    volatile int *host = mb->progress;
+    int sent = 0;
+    while (host[1] < B && sent < max_iter) {
+        if (sent - host[0] < kAhead) {
+            REGC_HIP(iteration());
+            ++sent;
+            continue;
+        }
+        // (a stream with nothing left to do while its iterations are unreported has failed)
+        const int seen = host[0];
+        for (int k = 0; k < 4096 && host[0] == seen; ++k) __builtin_ia32_pause();
+        if (host[0] == seen) {
+            const hipError_t e = hipStreamQuery(mb->stream);
+            if (e == hipErrorNotReady) continue;
+            REGC_HIP(e);
+            REGC_CHECK(host[0] != seen, REGC_EHIP, "the reweighting iteration stopped reporting");
+        }
+    }
+    return REGC_OK;
+}
+
+// solve_core on the device: same iteration, same decisions.
+static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta)
+{
+    hipStream_t s = mb->stream;
+    int rc;
+    if ((rc = solve_workspace(mb, 1))) return rc;
+    SolveArgs p = solve_args(mb);
+    p.max_iter = max_iter;
+    p.tol = tol;
+    int n = 0;
+    for (double v : mb->lnomega) n += v != -INFINITY;
+    SolveState st{};
+    st.gauge = mb->gauge;
+    st.memory = std::min(mb->memory, std::max(n - 2, 0));
+    st.delta = st.d_prev = INFINITY;
+    mb->progress[0] = mb->progress[1] = 0;
+    const std::vector<double> zero(start ? 0 : mb->S, 0.0);
+    const unsigned int none[2] = {0u, 0u};
+    REGC_HIP(hipMemcpyAsync(mb->f_d.p, start ? start : zero.data(), sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
+    REGC_HIP(hipMemcpyAsync(mb->good_d.p, start ? start : zero.data(), sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
+    REGC_HIP(hipMemcpyAsync(mb->state_d.p, &st, sizeof st, hipMemcpyHostToDevice, s));
+    REGC_HIP(hipMemcpyAsync(mb->arrived_d.p, none, sizeof none, hipMemcpyHostToDevice, s));
+    ScopedEvent e0, e1;
+    REGC_HIP(e0.create());
+    REGC_HIP(e1.create());
+    REGC_HIP(hipEventRecord(e0.e, s));
+    rc = run_iterations(mb, 1, max_iter, [&]() {
+        hipError_t e = launch_pass(mb, p, nullptr);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(mbar_fnew_q, dim3(p.L, 1), dim3(kFnewThreads), sizeof(double) * p.nN, s, p);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return launch_step(mb, p, 1);
+    });
+    if (rc) {
+        (void)hipStreamSynchronize(s);      // nothing writes the progress words after a failure
+        return rc;
+    }
+    REGC_HIP(hipEventRecord(e1.e, s));
+    // f_d holds g of the last iterate; log D consistent with it
+    REGC_HIP(launch_pass(mb, p, mb->logd_d.p));
+    REGC_HIP(hipMemcpyAsync(&st, mb->state_d.p, sizeof st, hipMemcpyDeviceToHost, s));
+    REGC_HIP(hipStreamSynchronize(s));
+    float ms = 0.f;
+    REGC_HIP(hipEventElapsedTime(&ms, e0.e, e1.e));
+    mb->ms_iter = ms;
+    mb->n_iter = st.it;
+    if (iters) *iters = st.it;
+    if (delta) *delta = st.delta;
+    mb->solved = true;
+    if (!st.conv) {
+        set_error("reweighting did not converge: max |delta f| = %g after %d iterations", st.delta, st.it);
+        return REGC_ENOCONV;
+    }
+    return REGC_OK;
 }
 
 // Least-squares coefficients gamma minimising || r - dR gamma ||_2 (dR: n x m,
@@ -849,6 +1515,7 @@ extern "C" int regc_mbar_set_solver(regc_mbar *mb, int method, int memory)
 // start: NULL (f = 0) or the starting iterate [S] (host).
 static int solve_core(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta)
 {
+    if (device_solve(mb)) return solve_on_device(mb, tol, max_iter, start, iters, delta);
     hipStream_t s = mb->stream;
     if (start) REGC_HIP(hipMemcpyAsync(mb->f_d.p, start, sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
     else REGC_HIP(hipMemsetAsync(mb->f_d.p, 0, sizeof(double) * mb->S, s));
