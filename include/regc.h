@@ -359,7 +359,11 @@ int regc_mbar_set_samples(regc_mbar *mb, int64_t ns, const double *e, const int3
 int regc_mbar_load_run(regc_mbar *mb, regc_ctx *ctx, int cls, int64_t skip_records);
 
 /* Fixed-point solver of regc_mbar_solve: method 0 plain iteration, 1 (default)
- * Anderson acceleration with `memory` past iterates (1..32, default 8). */
+ * Anderson acceleration with `memory` past iterates (1..32, default 8).  Method 1
+ * begins at an estimate from the states' mean E and N and preconditions the iteration
+ * with the map's Jacobian, taken once near the solution, on grids of at most 1024 states
+ * and 32 temperatures whose samples determine the solution; elsewhere, and in method 0,
+ * it begins at f = 0 and iterates the map itself. */
 int regc_mbar_set_solver(regc_mbar *mb, int method, int memory);
 
 /* Solves the self-consistent equations (Eq. (9)) for the free energies f_s =
@@ -421,7 +425,7 @@ typedef struct {
 
 void regc_default_reweight_opts(regc_reweight_opts *o);
 
-/* Solves (as regc_mbar_solve, from f = 0) and returns, on the target grid t =
+/* Solves (as regc_mbar_solve) and returns, on the target grid t =
  * l*n_mu' + m: mean_n, se_n (bootstrap), phase (as regc_mbar_targets), coverage and
  * se_coverage, heat_cap and se_heat_cap, p_n [t][n_max+1]; on the sampled grid:
  * f_states [S], mean_state_n and se_state_n [S] (batch means).  Any output may be

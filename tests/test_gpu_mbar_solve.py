@@ -76,6 +76,23 @@ def test_solution_is_the_oracles_fixed_point(n_t, n_mu, n_max, per_state):
     check_solution(t, mu, n_max, e, n, s, tol=1e-10, max_iter=5000)
 
 
+@pytest.mark.parametrize("n_t,n_mu,n_max", [(2, 2, 120), (4, 4, 120)])
+def test_states_that_hardly_overlap(n_t, n_mu, n_max):
+    """Too few states for their samples to connect them: the preconditioned solve gives
+    way to the plain iteration from f = 0, whose end is still a fixed point."""
+    t, mu = W.linear_grid(0.5, 2.0, n_t), W.linear_grid(-8.0, -2.0, n_mu)
+    e, n, s = fluid_samples(t, mu, n_max, 200, seed=3)
+    w = W.ideal_gas().replace(t=t, mu=mu, n_max=n_max)
+    mb = regc.Mbar(t, mu, n_max)
+    mb.set_samples(e, n, s)
+    f, conv, _, _ = mb.solve(tol=1e-10, max_iter=5000, allow_noconv=True)
+    mb.close()
+    beta, lnz = oracle.state_arrays(w)
+    g, _ = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=len(beta)), e, n, f)
+    if conv:
+        assert np.max(np.abs(g - g[0] - f)) < 1e-8
+
+
 @pytest.mark.parametrize("memory", [1, 8, 12])
 def test_solver_memory(memory):
     t, mu = W.linear_grid(0.9, 1.8, 6), W.linear_grid(-5.0, -2.5, 6)
