@@ -118,3 +118,30 @@ def test_energies_outside_the_bounded_range():
     e = rng.normal(0.0, 1.0, 1500)
     e[:40] += 120.0
     check_solution(t, mu, 5, e, n, s, tol=1e-9, max_iter=20000)
+
+
+@pytest.mark.parametrize("n_t,n_mu,n_boot,n_tgt", [(2, 3, 2, 1), (3, 4, 16, 3), (18, 3, 17, 17), (5, 9, 65, 2)])
+def test_bootstrap_of_all_replicates_together(n_t, n_mu, n_boot, n_tgt):
+    """Column tiles of 16 replicates and their remainders, one and two row tiles of
+    temperatures and of targets: the errors are the oracle's, whose replicates are solved
+    one after the other."""
+    t, mu = W.linear_grid(1.2, 1.5, n_t), W.linear_grid(-3.4, -3.0, n_mu)
+    n_max, recs = 24, 30
+    w = W.ideal_gas().replace(t=t, mu=mu, n_max=n_max)
+    e, n, s = fluid_samples(t, mu, n_max, recs, seed=n_boot)
+    order = np.argsort(s, kind="stable").reshape(n_t * n_mu, recs).T.ravel()      # whole records
+    e, n, s = e[order], n[order], s[order]
+    tt, tm = W.linear_grid(1.22, 1.48, n_tgt), [-3.3, -3.1]
+    mb = regc.Mbar(t, mu, n_max)
+    mb.set_samples(e, n, s)
+    got = mb.reweight(tt, tm, tol=1e-12, n_boot=n_boot, seed=5, n_sites=8.0)
+    mb.close()
+    beta, lnz = oracle.state_arrays(w)
+    f, _, ok, _, _ = oracle.mbar_solve(beta, lnz, np.bincount(s, minlength=len(beta)), e, n, tol=1e-12, max_iter=100000)
+    tb, tz = np.repeat(1.0 / tt, 2), np.array([oracle.state_lnz(a, b) for a in tt for b in tm])
+    se_n, se_c, _, _, conv = oracle.mbar_bootstrap(beta, lnz, e, n, s, n_t * n_mu, max(1, recs // 20), n_boot, 5, f, tb, tz,
+                                                  n_max, tol=1e-12)
+    assert ok and conv and got["converged"]
+    assert np.allclose(got["se_n"], se_n, rtol=1e-5, atol=0)
+    assert np.allclose(got["se_coverage"], se_n / 8.0, rtol=1e-5, atol=0)
+    assert np.allclose(got["se_heat_cap"], se_c, rtol=1e-4, atol=0)
