@@ -769,6 +769,7 @@ struct SolveArgs {
     int method, max_iter;
     double tol, tol_switch;                    // tol_switch > 0: stop below it too (conv = 2)
     const double *y;                           // [B][S] preconditioned residuals, or null
+    double *hinv;                              // 1 / sum_k a_k X_k of every sample (with log D)
     unsigned int *arrived;                     // [0] blocks of a step launch done with it, [1] step launches done
     unsigned long long *host;                  // host memory: step launches done | problems done << 32
 };
@@ -808,7 +809,7 @@ __device__ __forceinline__ void weights_log(const SolveArgs &p, const double *ln
 // registers; a thread with all temperatures of a sample needed 256 registers and left
 // the unit waiting (1.02e6 samples x 32 temperatures: 87 us, this 45 us).  Bound: FP64
 // issue, about 22 operations per sample and temperature (18 us of it).
-// Writes Q_l of its part of the chunk, or (LOGD) log D of its samples.
+// Writes Q_l of its part of the chunk, or (LOGD) log D and 1 / sum_k a_k X_k of its samples.
 template <int J, bool LOGD>
 __global__ void __launch_bounds__(kMbarThreads) mbar_pass(SolveArgs p, double *logd)
 {
@@ -820,7 +821,7 @@ __global__ void __launch_bounds__(kMbarThreads) mbar_pass(SolveArgs p, double *l
     weights_log(p, p.lnomega, p.f, N, la);
     double shift = -INFINITY;
     for (int l = 0; l < p.L; ++l) shift = la[l] > shift ? la[l] : shift;
-    if (!LOGD && part == 0 && threadIdx.x == 0) p.shift[N] = shift;
+    if (part == 0 && threadIdx.x == 0) p.shift[N] = shift;
     const int q = threadIdx.x & 3;
     double a[J], db[J], acc[J];
 #pragma unroll
@@ -847,7 +848,10 @@ __global__ void __launch_bounds__(kMbarThreads) mbar_pass(SolveArgs p, double *l
         }
         d = quad_total(d);
         if (LOGD) {
-            if (q == 0) logd[i] = shift - p.beta_c * t + log(d);
+            if (q == 0) {
+                logd[i] = shift - p.beta_c * t + log(d);
+                p.hinv[i] = recip(d);
+            }
         } else {
             const double inv = recip(d);
 #pragma unroll
@@ -1784,6 +1788,225 @@ __global__ void __launch_bounds__(256) boot_target_eval(BootArgs g, int nT, int 
     }
 }
 
+// ---- averages at target temperatures on bounded exponents ----
+// With h = 1 / sum_k a_k X_k of the solution (mbar_pass) a sample's weight at a target
+// temperature is e^{-beta_t E - log D} = e^{-beta_t E0 - shift} exp(-(beta_t - c)(E - E0)) h,
+// so a chunk's sums need one exponential per sample and target, no running maximum, and
+// the moments are those of E - E0.  Four lanes share a sample as in mbar_pass.  64
+// targets x 1.02e6 samples: 540 -> 80 us.  Output [chunk][target][4] (three used).
+template <int J>
+__global__ void __launch_bounds__(kMbarThreads) mbar_target_pass(SolveArgs p, int nT, const double *tb, double *tpart)
+{
+    __shared__ double red[kMbarThreads / 64][4 * J][3];
+    const int c = blockIdx.x, t0 = blockIdx.y * 4 * J, q = threadIdx.x & 3;
+    double db[J], a0[J], a1[J], a2[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        const int t = t0 + q + 4 * j;
+        db[j] = t < nT ? p.beta_c - tb[t] : 0.0;
+        a0[j] = a1[j] = a2[j] = 0.0;
+    }
+    const double mid = p.mid[p.chunk_n[c]];
+    const int end = p.chunk_e[c];
+    int i = p.chunk_b[c] + (int)(threadIdx.x >> 2);
+    double ne = i < end ? p.e[i] : 0.0, nh = i < end ? p.hinv[i] : 0.0;
+    for (; i < end; i += kMbarThreads / 4) {
+        const double d = ne - mid, h = nh;
+        if (i + kMbarThreads / 4 < end) {
+            ne = p.e[i + kMbarThreads / 4];
+            nh = p.hinv[i + kMbarThreads / 4];
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const double w = exp_bounded(db[j] * d) * h, wd = w * d;
+            a0[j] += w;
+            a1[j] += wd;
+            a2[j] = fma(wd, d, a2[j]);
+        }
+    }
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        double v[3] = {a0[j], a1[j], a2[j]};
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+#pragma unroll
+            for (int o = 4; o < 64; o <<= 1) v[k] += __shfl_xor(v[k], o);
+            if (lane < 4) red[wave][lane + 4 * j][k] = v[k];
+        }
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < 12 * J; x += blockDim.x) {
+        const int t = x / 3, k = x % 3;
+        if (t0 + t >= nT) continue;
+        double v = 0.0;
+        for (int w = 0; w < kMbarThreads / 64; ++w) v += red[w][t][k];
+        tpart[((size_t)c * nT + t0 + t) * 4 + k] = v;
+    }
+}
+
+// The averages at target temperature blockIdx.x from the chunks' sums: G(N) and the
+// moments of E at each N (threads), then a wave per chemical potential (a thread each and
+// every p(N) in turn: 90 us for 64 x 64 targets and 512 N; 46 us).
+constexpr int kEvalThreads = 512;
+
+__global__ void __launch_bounds__(kEvalThreads) mbar_target_eval_q(SolveArgs p, int nT, int nMu, const double *tb,
+                                                                const double *tpart, const double *tlnz, double *f,
+                                                                double *mean_n, double *mean_e, double *mean_e2, double *p_n,
+                                                                int32_t *phase)
+{
+    extern __shared__ double sh[];
+    double *G = sh, *E1 = sh + p.nN, *E2 = sh + 2 * p.nN;
+    const int t = blockIdx.x;
+    for (int N = threadIdx.x; N < p.nN; N += blockDim.x) {
+        double m0 = 0.0, m1 = 0.0, m2 = 0.0;
+        for (int c = p.seg_c0[N]; c < p.seg_c1[N]; ++c) {
+            const double *o = tpart + ((size_t)c * nT + t) * 4;
+            m0 += o[0]; m1 += o[1]; m2 += o[2];
+        }
+        const double mid = p.mid[N], d1 = m0 > 0.0 ? m1 / m0 : 0.0, d2 = m0 > 0.0 ? m2 / m0 : 0.0;
+        G[N] = m0 > 0.0 ? log(m0) - tb[t] * mid - p.shift[N] : -INFINITY;
+        E1[N] = m0 > 0.0 ? mid + d1 : 0.0;
+        E2[N] = m0 > 0.0 ? fma(mid, mid, fma(2.0 * mid, d1, d2)) : 0.0;
+    }
+    __syncthreads();
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    for (int m = wave; m < nMu; m += kEvalThreads / 64) {
+        const int k = t * nMu + m;
+        const double lz = tlnz[k];
+        double mx = -INFINITY;
+        int best = 0;
+        for (int N = lane; N < p.nN; N += 64) {
+            const double v = fma((double)N, lz, G[N]);
+            if (v > mx) { mx = v; best = N; }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double v = __shfl_xor(mx, o);
+            const int b = __shfl_xor(best, o);
+            if (v > mx || (v == mx && b < best)) { mx = v; best = b; }     // the smallest N on ties
+        }
+        double s0 = 0.0, sn = 0.0, se = 0.0, se2 = 0.0;
+        for (int N = lane; N < p.nN; N += 64) {
+            const double w = G[N] == -INFINITY ? 0.0 : exp(fma((double)N, lz, G[N]) - mx);
+            s0 += w;
+            sn = fma(w, (double)N, sn);
+            se = fma(w, E1[N], se);
+            se2 = fma(w, E2[N], se2);
+        }
+        s0 = wave_total(s0);
+        sn = wave_total(sn);
+        se = wave_total(se);
+        se2 = wave_total(se2);
+        if (p_n) {
+            const double inv = 1.0 / s0;
+            for (int N = lane; N < p.nN; N += 64)
+                p_n[(size_t)k * p.nN + N] = G[N] == -INFINITY ? 0.0 : exp(fma((double)N, lz, G[N]) - mx) * inv;
+        }
+        if (lane == 0) {
+            if (f) f[k] = -(mx + log(s0));
+            mean_n[k] = sn / s0;
+            if (mean_e) mean_e[k] = se / s0;
+            if (mean_e2) mean_e2[k] = se2 / s0;
+            if (phase) phase[k] = best;
+        }
+    }
+}
+
+// Observables on bounded exponents: sums over a chunk's part (block x of rows) of
+// w_t obs_k for 16 target temperatures (block z) and all observables, and of w_t (column
+// n_obs), a matrix product on the FP64 matrix unit: rows t, columns k, four samples per
+// step.  A wave takes four tiles of 16 columns.  The records are read once, not once per
+// temperature (2.05e5 samples x 221 x 16: 360 -> 177 us).  out [row][nT][n_obs + 1].
+__global__ void __launch_bounds__(kMbarThreads) mbar_obs_pass(SolveArgs p, int nT, int n_obs, const double *tb,
+                                                           const uint32_t *obs, double *out)
+{
+    const int c = blockIdx.x / p.sub, part = blockIdx.x % p.sub;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, r = lane % 16, k = lane / 16;
+    const int t = blockIdx.z * 16 + r, col0 = (blockIdx.y * (kMbarThreads / 64) + wave) * 64;
+    if (col0 > n_obs) return;
+    const double db = t < nT ? p.beta_c - tb[t] : 0.0;
+    const double mid = p.mid[p.chunk_n[c]];
+    const int b = p.chunk_b[c], cnt = p.chunk_e[c] - b;
+    const int lo = b + (int)((int64_t)cnt * part / p.sub), end = b + (int)((int64_t)cnt * (part + 1) / p.sub);
+    f64x4 acc[4] = {};
+    // sixteen samples per round: all their loads are in flight before the first product
+    for (int i0 = lo; i0 < end; i0 += 16) {
+        uint32_t v[4][4];
+        double d[4], h[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + 4 * u + k, ic = i < end ? i : lo;
+            const uint32_t *o = obs + (size_t)ic * n_obs;
+            d[u] = p.e[ic];
+            h[u] = i < end ? p.hinv[ic] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int col = col0 + 16 * q + r;
+                v[u][q] = col < n_obs ? o[col] : 1u;      // (columns past n_obs are not written)
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double w = exp_bounded(db * (d[u] - mid)) * h[u];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] = mfma64(w, (double)v[u][q], acc[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int to = blockIdx.z * 16 + k + 4 * e, col = col0 + 16 * q + r;
+            if (to < nT && col <= n_obs) out[((size_t)blockIdx.x * nT + to) * (n_obs + 1) + col] = acc[q][e];
+        }
+}
+
+// cond[t][N][k] and G[t][N] from the parts, block (N, t).
+__global__ void __launch_bounds__(256) mbar_obs_cond(SolveArgs p, int nT, int n_obs, const double *tb, const double *part,
+                                                  double *cond, double *G)
+{
+    const int N = blockIdx.x, t = blockIdx.y;
+    const int c0 = p.seg_c0[N] * p.sub, c1 = p.seg_c1[N] * p.sub;
+    const size_t stride = (size_t)nT * (n_obs + 1);
+    const double *src = part + (size_t)t * (n_obs + 1);
+    double s0 = 0.0;
+    for (int c = c0; c < c1; ++c) s0 += src[c * stride + n_obs];
+    if (threadIdx.x == 0) G[(size_t)t * p.nN + N] = s0 > 0.0 ? log(s0) - tb[t] * p.mid[N] - p.shift[N] : -INFINITY;
+    for (int k = threadIdx.x; k < n_obs; k += blockDim.x) {
+        double a = 0.0;
+        for (int c = c0; c < c1; ++c) a += src[c * stride + k];
+        cond[((size_t)t * p.nN + N) * n_obs + k] = s0 > 0.0 ? a / s0 : 0.0;
+    }
+}
+
+// mean[t][mu][k] = sum_N p(N) cond[t][N][k], block (mu, t) (a block per t with mu in turn:
+// 6.4 ms for 16 x 16 targets x 221; 16 x 16 blocks: 30 us).
+__global__ void __launch_bounds__(256) mbar_obs_mean(int nMu, int nN, int n_obs, const double *G, const double *tlnz,
+                                                  const double *cond, double *mean)
+{
+    extern __shared__ double P[];
+    const int m = blockIdx.x, t = blockIdx.y, lane = threadIdx.x % 64;
+    const double lz = tlnz[t * nMu + m];
+    const double *g = G + (size_t)t * nN;
+    double mx = -INFINITY, sum = 0.0;              // (every wave for itself)
+    for (int N = lane; N < nN; N += 64) mx = fmax(mx, fma((double)N, lz, g[N]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+    for (int N = lane; N < nN; N += 64) sum += g[N] == -INFINITY ? 0.0 : exp(fma((double)N, lz, g[N]) - mx);
+    sum = wave_total(sum);
+    for (int N = threadIdx.x; N < nN; N += blockDim.x)
+        P[N] = g[N] == -INFINITY ? 0.0 : exp(fma((double)N, lz, g[N]) - mx) / sum;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n_obs; k += blockDim.x) {
+        double acc = 0.0;
+        const double *c = cond + (size_t)t * nN * n_obs + k;
+#pragma unroll 8
+        for (int N = 0; N < nN; ++N) acc = fma(P[N], c[(size_t)N * n_obs], acc);
+        mean[((size_t)t * nMu + m) * n_obs + k] = acc;
+    }
+}
+
 }  // namespace regc
 
 using namespace regc;
@@ -1814,6 +2037,8 @@ struct regc_mbar {
     DevBuf<double> mid_d, half_d;         // middle and half width of the energies sampled at each N
     bool bounded = false;                 // the exponents around them stay below kMaxExponent
     double half_max = 0.0;                // the largest half width
+    DevBuf<double> hinv_d;                // 1 / sum of every sample at the solution
+    bool hinv_valid = false;              // hinv_d and shift_d are those of the solution in f_d
     int sub = 1;                          // blocks per chunk of a pass
     DevBuf<double> shift_d, q_d, hist_r_d, hist_g_d, good_d;
     DevBuf<SolveState> state_d;
@@ -1904,6 +2129,7 @@ extern "C" int regc_mbar_set_samples(regc_mbar *mb, int64_t ns, const double *e,
     // handle holds no samples (a failed call leaves it empty, not half updated)
     mb->have_samples = false;
     mb->solved = false;
+    mb->hinv_valid = false;
     mb->n_obs = 0;
     hipStream_t s = mb->stream;
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
@@ -2090,7 +2316,7 @@ static SolveArgs solve_args(regc_mbar *mb)
     p.lnomega = mb->lnomega_d.p;
     p.f = mb->f_d.p; p.fnew = mb->fnew_d.p; p.good = mb->good_d.p;
     p.hist_r = mb->hist_r_d.p; p.hist_g = mb->hist_g_d.p;
-    p.shift = mb->shift_d.p; p.partial = mb->q_d.p; p.st = mb->state_d.p;
+    p.shift = mb->shift_d.p; p.partial = mb->q_d.p; p.st = mb->state_d.p; p.hinv = mb->hinv_d.p;
     p.arrived = mb->arrived_d.p; p.host = mb->progress;
     p.method = mb->method;
     return p;
@@ -2101,7 +2327,7 @@ static int solve_workspace(regc_mbar *mb, int B)
 {
     int rc;
     const size_t hist = (size_t)B * (kMaxMemory + 1) * mb->S;
-    if ((rc = mb->shift_d.reserve((size_t)B * mb->nN)) || (rc = mb->q_d.reserve((size_t)B * mb->L * mb->nchunks * mb->sub)) ||
+    if ((rc = mb->hinv_d.reserve(mb->ns)) || (rc = mb->shift_d.reserve((size_t)B * mb->nN)) || (rc = mb->q_d.reserve((size_t)B * mb->L * mb->nchunks * mb->sub)) ||
         (rc = mb->hist_r_d.reserve(hist)) || (rc = mb->hist_g_d.reserve(hist)) ||
         (rc = mb->good_d.reserve((size_t)B * mb->S)) || (rc = mb->state_d.reserve(B)) || (rc = mb->arrived_d.reserve(2)))
         return rc;
@@ -2352,6 +2578,7 @@ static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double
     REGC_HIP(hipEventRecord(e1.e, s));
     // f_d holds g of the last iterate; log D consistent with it
     REGC_HIP(launch_pass(mb, p, mb->logd_d.p));
+    mb->hinv_valid = true;
     if (!solved) REGC_HIP(hipMemcpyAsync(&st, mb->state_d.p, sizeof st, hipMemcpyDeviceToHost, s));
     REGC_HIP(hipStreamSynchronize(s));
     float ms = 0.f;
@@ -2433,7 +2660,7 @@ extern "C" int regc_mbar_set_solver(regc_mbar *mb, int method, int memory)
 // start: NULL (f = 0) or the starting iterate [S] (host).
 static int solve_core(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta)
 {
-    mb->inverse_valid = false;
+    mb->inverse_valid = mb->hinv_valid = false;
     if (device_solve(mb)) return solve_on_device(mb, tol, max_iter, start, iters, delta);
     hipStream_t s = mb->stream;
     if (start) REGC_HIP(hipMemcpyAsync(mb->f_d.p, start, sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
@@ -2561,6 +2788,42 @@ static int target_grid(regc_mbar *mb, const regc_grid *targets, TargetDev &T)
     return REGC_OK;
 }
 
+// Whether exponents around the samples' energies stay bounded at inverse temperatures tb.
+static bool bounded_targets(const regc_mbar *mb, const double *tb, int nT)
+{
+    double far = 0.0;
+    for (int t = 0; t < nT; ++t) far = std::max(far, std::fabs(tb[t] - mb->beta_c));
+    return mb->bounded && far * mb->half_max <= kMaxExponent;
+}
+
+// The chunks' sums and the averages at the targets on the handle's stream: on bounded
+// exponents where the solution and the targets allow, else with a running maximum.  part:
+// [nchunks][nT][4]; tb: the targets' inverse temperatures (host), tb_d, tz_d (device).
+static hipError_t launch_targets(regc_mbar *mb, int nT, int nMu, const double *tb, const double *tb_d, const double *tz_d,
+                                 double *part, double *f, double *mn, double *me, double *me2, double *pn, int32_t *ph)
+{
+    hipStream_t s = mb->stream;
+    const size_t lds = sizeof(double) * 3 * mb->nN;
+    if (mb->hinv_valid && !mb->weighted && nT <= 1 << 20 && bounded_targets(mb, tb, nT)) {
+        const SolveArgs p = solve_args(mb);
+        if (nT <= 8)
+            hipLaunchKernelGGL((mbar_target_pass<2>), dim3(mb->nchunks, 1), dim3(kMbarThreads), 0, s, p, nT, tb_d, part);
+        else if (nT <= 16)
+            hipLaunchKernelGGL((mbar_target_pass<4>), dim3(mb->nchunks, 1), dim3(kMbarThreads), 0, s, p, nT, tb_d, part);
+        else
+            hipLaunchKernelGGL((mbar_target_pass<8>), dim3(mb->nchunks, (nT + 31) / 32), dim3(kMbarThreads), 0, s, p, nT,
+                               tb_d, part);
+        hipLaunchKernelGGL(mbar_target_eval_q, dim3(nT), dim3(kEvalThreads), lds, s, p, nT, nMu, tb_d, part, tz_d, f, mn, me,
+                           me2, pn, ph);
+    } else {
+        hipLaunchKernelGGL(mbar_target_chunk, dim3(mb->nchunks), dim3(kMbarThreads), 0, s, nT, tb_d, mb->e_d.p,
+                           mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, part, mb->weighted ? mb->wgt_d.p : nullptr);
+        hipLaunchKernelGGL(mbar_target_eval, dim3(nT), dim3(256), lds, s, nT, nMu, mb->nN, part, mb->seg_c0_d.p,
+                           mb->seg_c1_d.p, tz_d, f, mn, me, me2, pn, ph);
+    }
+    return hipGetLastError();
+}
+
 // Reweighted averages at the targets into device arrays (any may be NULL but mn).
 static int targets_dev(regc_mbar *mb, const TargetDev &T, double *f, double *mn, double *me, double *me2,
                        double *pn, int32_t *ph)
@@ -2569,12 +2832,7 @@ static int targets_dev(regc_mbar *mb, const TargetDev &T, double *f, double *mn,
     DevBuf<double> tpart;
     int rc;
     if ((rc = tpart.alloc((size_t)mb->nchunks * T.nT * 4))) return rc;
-    hipLaunchKernelGGL(mbar_target_chunk, dim3(mb->nchunks), dim3(kMbarThreads), 0, s, T.nT, T.tb_d.p, mb->e_d.p,
-                       mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, tpart.p, mb->weighted ? mb->wgt_d.p : nullptr);
-    REGC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(mbar_target_eval, dim3(T.nT), dim3(256), sizeof(double) * 3 * mb->nN, s, T.nT, T.nMu, mb->nN,
-                       tpart.p, mb->seg_c0_d.p, mb->seg_c1_d.p, T.tz_d.p, f, mn, me, me2, pn, ph);
-    REGC_HIP(hipGetLastError());
+    REGC_HIP(launch_targets(mb, T.nT, T.nMu, T.tb.data(), T.tb_d.p, T.tz_d.p, tpart.p, f, mn, me, me2, pn, ph));
     REGC_HIP(hipStreamSynchronize(s));     // tpart is freed on return
     return REGC_OK;
 }
@@ -2664,12 +2922,7 @@ extern "C" int regc_mbar_targets_static(regc_mbar *mb, const regc_grid *targets,
     REGC_HIP(hipMemcpyAsync(tb_d, tb, sizeof(double) * nT, hipMemcpyHostToDevice, s));
     REGC_HIP(hipMemcpyAsync(tz_d, tz, sizeof(double) * nK, hipMemcpyHostToDevice, s));
     // every partial and output entry read below is written by these two kernels
-    hipLaunchKernelGGL(mbar_target_chunk, dim3(mb->nchunks), dim3(kMbarThreads), 0, s, nT, tb_d, mb->e_d.p,
-                       mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, part, mb->weighted ? mb->wgt_d.p : nullptr);
-    REGC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(mbar_target_eval, dim3(nT), dim3(256), sizeof(double) * 3 * mb->nN, s, nT, nMu, mb->nN, part,
-                       mb->seg_c0_d.p, mb->seg_c1_d.p, tz_d, f_d, mn_d, me_d, me2_d, nullptr, ph_d);
-    REGC_HIP(hipGetLastError());
+    REGC_HIP(launch_targets(mb, nT, nMu, tb, tb_d, tz_d, part, f_d, mn_d, me_d, me2_d, nullptr, ph_d));
     if (f) REGC_HIP(hipMemcpyAsync(f, f_d, sizeof(double) * nK, hipMemcpyDeviceToHost, s));
     REGC_HIP(hipMemcpyAsync(mean_n, mn_d, sizeof(double) * nK, hipMemcpyDeviceToHost, s));
     if (mean_e) REGC_HIP(hipMemcpyAsync(mean_e, me_d, sizeof(double) * nK, hipMemcpyDeviceToHost, s));
@@ -2716,18 +2969,38 @@ extern "C" int regc_mbar_observables(regc_mbar *mb, const regc_grid *targets, do
         for (int m = 0; m < nMu; ++m) tz[l * nMu + m] = lnz_of(targets->t[l], targets->mu[m], mb->lambda1);
     }
     hipStream_t s = mb->stream;
-    DevBuf<double> tb_d, tz_d, part, cond_d, mean_d;
+    const bool fast = mb->hinv_valid && bounded_targets(mb, tb.data(), nT);
+    SolveArgs p{};
+    if (fast) {
+        p = solve_args(mb);
+        // parts of chunks while their sums stay below 64 MiB
+        const size_t row = sizeof(double) * (size_t)nT * (no + 1) * p.nchunks;
+        p.sub = (int)std::min<size_t>(p.sub, std::max<size_t>(1, ((size_t)64 << 20) / row));
+        p.rows = p.nchunks * p.sub;
+    }
+    DevBuf<double> tb_d, tz_d, part, cond_d, mean_d, g_d;
     int rc;
-    if ((rc = tb_d.alloc(nT)) || (rc = tz_d.alloc(nK)) || (rc = part.alloc((size_t)mb->nchunks * nT * (no + 2))) ||
-        (rc = cond_d.alloc((size_t)nT * mb->nN * no)) || (rc = mean_d.alloc(mean ? (size_t)nK * no : 1)))
+    if ((rc = tb_d.alloc(nT)) || (rc = tz_d.alloc(nK)) ||
+        (rc = part.alloc(fast ? (size_t)p.rows * nT * (no + 1) : (size_t)mb->nchunks * nT * (no + 2))) ||
+        (rc = cond_d.alloc((size_t)nT * mb->nN * no)) || (rc = mean_d.alloc(mean ? (size_t)nK * no : 1)) ||
+        (rc = g_d.alloc((size_t)nT * mb->nN)))
         return rc;
     REGC_HIP(hipMemcpyAsync(tb_d.p, tb.data(), sizeof(double) * nT, hipMemcpyHostToDevice, s));
     REGC_HIP(hipMemcpyAsync(tz_d.p, tz.data(), sizeof(double) * nK, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(mbar_obs_chunk, dim3(mb->nchunks, nT), dim3(kMbarThreads), 0, s, nT, no, tb_d.p, mb->e_d.p,
-                       mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, mb->obs_d.p, part.p);
-    REGC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(mbar_obs_eval, dim3(nT), dim3(256), 2 * sizeof(double) * mb->nN, s, nT, nMu, mb->nN, no,
-                       part.p, mb->seg_c0_d.p, mb->seg_c1_d.p, tz_d.p, cond_d.p, mean ? mean_d.p : nullptr);
+    if (fast) {
+        const int cols = 64 * (kMbarThreads / 64);        // columns per block
+        hipLaunchKernelGGL(mbar_obs_pass, dim3(p.rows, (no + cols) / cols, (nT + 15) / 16), dim3(kMbarThreads), 0, s, p, nT,
+                           no, tb_d.p, mb->obs_d.p, part.p);
+        hipLaunchKernelGGL(mbar_obs_cond, dim3(mb->nN, nT), dim3(256), 0, s, p, nT, no, tb_d.p, part.p, cond_d.p, g_d.p);
+        if (mean)
+            hipLaunchKernelGGL(mbar_obs_mean, dim3(nMu, nT), dim3(256), sizeof(double) * mb->nN, s, nMu, mb->nN, no, g_d.p,
+                               tz_d.p, cond_d.p, mean_d.p);
+    } else {
+        hipLaunchKernelGGL(mbar_obs_chunk, dim3(mb->nchunks, nT), dim3(kMbarThreads), 0, s, nT, no, tb_d.p, mb->e_d.p,
+                           mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, mb->obs_d.p, part.p);
+        hipLaunchKernelGGL(mbar_obs_eval, dim3(nT), dim3(256), 2 * sizeof(double) * mb->nN, s, nT, nMu, mb->nN, no,
+                           part.p, mb->seg_c0_d.p, mb->seg_c1_d.p, tz_d.p, cond_d.p, mean ? mean_d.p : nullptr);
+    }
     REGC_HIP(hipGetLastError());
     REGC_HIP(hipStreamSynchronize(s));
     if (cond) REGC_HIP(hipMemcpy(cond, cond_d.p, sizeof(double) * (size_t)nT * mb->nN * no, hipMemcpyDeviceToHost));
@@ -2746,14 +3019,6 @@ extern "C" int regc_mbar_timing(regc_mbar *mb, double *ms_iter_total, int64_t *n
 extern "C" void regc_mbar_destroy(regc_mbar *mb) { delete mb; }
 
 // ---------------------------------------------------------------------------
-// Whether exponents around the samples' energies stay bounded at inverse temperatures tb.
-static bool bounded_targets(const regc_mbar *mb, const double *tb, int nT)
-{
-    double far = 0.0;
-    for (int t = 0; t < nT; ++t) far = std::max(far, std::fabs(tb[t] - mb->beta_c));
-    return mb->bounded && far * mb->half_max <= kMaxExponent;
-}
-
 // All bootstrap replicates b0 .. b0 + B - 1 together: their solutions from the full one
 // (f_d) by Anderson's iteration preconditioned with the full data's inverse Jacobian, then
 // <N> and the heat capacity at the targets into rep_n, rep_c [B][targets] (device).  `ok`

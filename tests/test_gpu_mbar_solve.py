@@ -145,3 +145,36 @@ def test_bootstrap_of_all_replicates_together(n_t, n_mu, n_boot, n_tgt):
     assert np.allclose(got["se_n"], se_n, rtol=1e-5, atol=0)
     assert np.allclose(got["se_coverage"], se_n / 8.0, rtol=1e-5, atol=0)
     assert np.allclose(got["se_heat_cap"], se_c, rtol=1e-4, atol=0)
+
+
+@pytest.mark.parametrize("n_tgt,n_mu,n_obs", [(1, 1, 1), (8, 2, 15), (9, 3, 64), (16, 9, 65), (17, 2, 255), (33, 7, 256)])
+@pytest.mark.parametrize("t0", [1.1, 0.002])
+def test_averages_at_targets_and_observables(n_tgt, n_mu, n_obs, t0):
+    """Tiles of targets (8, 16, 32) and of columns (16, 64, 256) and their remainders, with
+    targets inside the range of the bounded exponents and (t0 = 0.002) outside."""
+    t, mu = W.linear_grid(1.0, 1.4, 5), W.linear_grid(-3.4, -3.0, 4)
+    n_max = 70
+    w = W.ideal_gas().replace(t=t, mu=mu, n_max=n_max)
+    e, n, s = fluid_samples(t, mu, n_max, 150, seed=n_obs)
+    obs = np.random.default_rng(n_tgt).integers(0, 2 ** 32, (len(e), n_obs), dtype=np.uint64).astype(np.uint32)
+    tt, tm = W.linear_grid(t0, 1.5, n_tgt), W.linear_grid(-3.5, -2.9, n_mu)
+    mb = regc.Mbar(t, mu, n_max)
+    mb.set_samples(e, n, s)
+    mb.set_observables(obs)
+    f, conv, _, _ = mb.solve(tol=1e-11)
+    got = mb.targets(tt, tm)
+    mean, cond = mb.observables(tt, tm, n_obs)
+    mb.close()
+    assert conv
+    beta, lnz = oracle.state_arrays(w)
+    _, logd = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=len(beta)), e, n, f)
+    tb, tz = np.repeat(1.0 / np.array(tt), n_mu), np.array([oracle.state_lnz(a, b) for a in tt for b in tm])
+    ref = oracle.mbar_targets(tb, tz, e, n, logd, n_max)
+    mean_ref, cond_ref = oracle.mbar_observables(tb, tz, e, n, logd, n_max, obs)
+    assert np.allclose(got["mean_n"], ref["mean_n"], rtol=1e-8, atol=1e-10)
+    assert np.allclose(got["mean_e"], ref["mean_e"], rtol=1e-8, atol=1e-9)
+    assert np.allclose(got["p_n"], ref["p_n"], rtol=1e-7, atol=1e-12)
+    assert np.array_equal(got["phase"], ref["phase"])
+    assert np.allclose(np.asarray(mean).reshape(len(tb), n_obs), mean_ref, rtol=1e-8)
+    seen = ref["p_n"][::n_mu] > 0                  # (the oracle leaves the others at 0)
+    assert np.allclose(np.asarray(cond).reshape(n_tgt, n_max + 1, n_obs)[seen], cond_ref[::n_mu][seen], rtol=1e-8)
