@@ -24,6 +24,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <deque>
 #include <mutex>
 #include <vector>
@@ -485,9 +486,239 @@ __global__ void mbar_obs_eval(int nT, int nMu, int nN, int n_obs, const double *
 }
 
 // ---- errors of the estimates ----
-// Batch means: per-state series position of every sample (samples sorted stably by
-// state), batch b = floor(rank B / n_s), integer sums of N per (state, batch).
-// bad when a state is out of range or an N negative
+// Batch means: a sample's rank among its state's samples, in the order given, decides its
+// batch: batch b of a state with c samples holds ranks [b c / B, (b + 1) c / B).  Sums of N are integers
+// (exact in any order).
+//
+// Ranks come without a sort: blocks of consecutive samples count their states in LDS
+// (bm_count), a scan over the blocks gives each block's first rank per state (bm_scan), and a
+// second pass ranks 64 samples at a time by matching their states' bits (bm_sum) and adds N:
+// in LDS while a state stays in the batch that it starts the block in, else in memory.  What
+// bounds it is the atomic sums that leave the blocks, so blocks are few and large.  The radix sort that
+// this replaces took 26 launches and 12 allocations (1.02e6 samples of 1024 states: 453 us,
+// now 74).  It stays for more states than LDS holds counters of.
+constexpr int kBmBlocks = 128, kBmThreads = 512;
+
+// LDS of bm_sum with W waves: per state a sum (64 bits), its batch, the count, a counter per wave
+__host__ __device__ inline size_t bm_bytes(int S, int W) { return (size_t)S * (16 + 4 * W); }
+
+struct BmArgs {
+    int64_t ns;
+    const int32_t *st, *n;
+    int S, B, blocks;
+    uint32_t *hist;                // [blocks][S]: counts, then first ranks
+    uint32_t *count;               // [S]
+    unsigned long long *sum;       // [S][B]
+    int *bad;                      // [blocks]
+    double *mean, *se;             // [S]
+    int *any_bad;
+    __device__ int64_t begin(int b) const { return ns * b / blocks; }
+};
+
+// a state out of range or a negative N
+__device__ __forceinline__ bool bm_bad(const BmArgs &p, int s, int n) { return (s < 0) | (s >= p.S) | (n < 0); }
+
+// Samples [i0, i1) by `lanes` threads, eight of each with all their loads first: f(state, N)
+// by every thread, state -1 without a sample and -2 for a bad one.
+template <typename F>
+__device__ __forceinline__ void bm_each(const BmArgs &p, int64_t i0, int64_t i1, int lanes, F f)
+{
+    const int lane = threadIdx.x % lanes;
+    for (; i0 < i1; i0 += 8 * lanes) {
+        int s[8], n[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t i = i0 + lanes * q + lane, in = i < i1 ? i : i1 - 1;
+            s[q] = p.st[in];
+            n[q] = p.n[in];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i0 + lanes * q < i1) {
+                const int k = bm_bad(p, s[q], n[q]) ? -2 : s[q];
+                f(i0 + lanes * q + lane < i1 ? k : -1, n[q]);
+            }
+    }
+}
+
+__global__ void __launch_bounds__(kBmThreads) bm_count(BmArgs p)
+{
+    extern __shared__ __align__(16) unsigned char bm_lds[];
+    uint32_t *c = reinterpret_cast<uint32_t *>(bm_lds);
+    const int b = blockIdx.x;
+    for (int s = threadIdx.x; s < p.S; s += kBmThreads) c[s] = 0u;
+    for (int64_t k = b * (int64_t)kBmThreads + threadIdx.x; k < (int64_t)p.S * p.B; k += (int64_t)p.blocks * kBmThreads)
+        p.sum[k] = 0ull;
+    __syncthreads();
+    bool bad = false;
+    bm_each(p, p.begin(b), p.begin(b + 1), kBmThreads, [&](int s, int) {
+        if (s >= 0) atomicAdd(c + s, 1u);
+        bad |= s == -2;
+    });
+    const bool any = __syncthreads_or(bad);
+    if (threadIdx.x == 0) p.bad[b] = any;
+    for (int s = threadIdx.x; s < p.S; s += kBmThreads) p.hist[(size_t)b * p.S + s] = c[s];
+}
+
+// 64 states per block, the blocks' counts in 16 groups of consecutive ones
+__global__ void __launch_bounds__(1024) bm_scan(BmArgs p)
+{
+    constexpr int kEach = kBmBlocks / 16;
+    __shared__ uint32_t group[16][64];
+    const int c = threadIdx.x % 64, g = threadIdx.x / 64, s = blockIdx.x * 64 + c;
+    uint32_t v[kEach], mine = 0;
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+        const int b = g * kEach + q;
+        v[q] = s < p.S && b < p.blocks ? p.hist[(size_t)b * p.S + s] : 0u;
+        mine += v[q];
+    }
+    group[g][c] = mine;
+    __syncthreads();
+    uint32_t at = 0;
+    for (int q = 0; q < g; ++q) at += group[q][c];
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+        const int b = g * kEach + q;
+        if (s < p.S && b < p.blocks) p.hist[(size_t)b * p.S + s] = at;
+        at += v[q];
+    }
+    if (g == 15 && s < p.S) p.count[s] = at;
+    if (blockIdx.x == 0) {
+        const bool any = __syncthreads_or(threadIdx.x < p.blocks && p.bad[threadIdx.x]);
+        if (threadIdx.x == 0) *p.any_bad = any;
+    }
+}
+
+// floor(((rank + 1) B - 1) / c): the batch whose range holds the rank
+__device__ __forceinline__ uint32_t bm_batch(uint32_t rank, int B, uint32_t c)
+{
+    const uint64_t x = ((uint64_t)rank + 1) * (uint64_t)B - 1;
+    if (x >> 52) return (uint32_t)(x / c);
+    const int64_t f = (int64_t)((double)x / (double)c);    // off by one at most
+    const int64_t rest = (int64_t)x - f * (int64_t)c;
+    return (uint32_t)(rest < 0 ? f - 1 : rest >= (int64_t)c ? f + 1 : f);
+}
+
+template <int W>
+__global__ void __launch_bounds__(64 * W) bm_sum(BmArgs p)
+{
+    extern __shared__ __align__(16) unsigned char bm_lds[];
+    unsigned long long *acc = reinterpret_cast<unsigned long long *>(bm_lds);
+    uint32_t *first = reinterpret_cast<uint32_t *>(acc + p.S), *count = first + p.S, *all = count + p.S;
+    const int b = blockIdx.x, wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    uint32_t *mine = all + (size_t)wave * p.S;
+    for (int s = threadIdx.x; s < p.S * W; s += 64 * W) all[s] = 0u;
+    __syncthreads();
+    // the waves' consecutive shares of the block's samples
+    const int64_t lo = p.begin(b), cnt = p.begin(b + 1) - lo;
+    const int64_t w0 = lo + cnt * wave / W, w1 = lo + cnt * (wave + 1) / W;
+    bm_each(p, w0, w1, 64, [&](int s, int) { if (s >= 0) atomicAdd(mine + s, 1u); });
+    __syncthreads();
+#pragma unroll 4
+    for (int s = threadIdx.x; s < p.S; s += 64 * W) {
+        uint32_t at = p.hist[(size_t)b * p.S + s];
+        const uint32_t total = p.count[s];
+        acc[s] = 0ull;
+        count[s] = total;
+        first[s] = total ? bm_batch(at < total ? at : total - 1, p.B, total) : 0u;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t here = all[(size_t)w * p.S + s];
+            all[(size_t)w * p.S + s] = at;
+            at += here;
+        }
+    }
+    __syncthreads();
+    int bits = 0;
+    while ((1 << bits) < p.S) ++bits;
+    volatile uint32_t *c = mine;
+    bm_each(p, w0, w1, 64, [&](int s, int n) {
+        uint64_t same = __ballot(s >= 0);
+        for (int q = 0; q < bits; ++q) {
+            const uint64_t set = __ballot((s >> q) & 1);
+            same &= (s >> q) & 1 ? set : ~set;
+        }
+        if (s >= 0) {
+            const uint32_t before = (uint32_t)__popcll(same & ((1ull << lane) - 1));
+            const uint32_t rank = c[s] + before;
+            __builtin_amdgcn_wave_barrier();
+            if (before == 0) c[s] = rank + (uint32_t)__popcll(same);
+            const uint32_t batch = bm_batch(rank, p.B, count[s]);
+            if (batch == first[s]) atomicAdd(acc + s, (unsigned long long)n);
+            else atomicAdd(p.sum + (size_t)s * p.B + batch, (unsigned long long)n);
+        }
+    });
+    __syncthreads();
+    for (int s = threadIdx.x; s < p.S; s += 64 * W)
+        if (acc[s]) atomicAdd(p.sum + (size_t)s * p.B + first[s], acc[s]);
+}
+
+// floor(b c / B), where batch b of a state with c samples starts
+__device__ __forceinline__ int64_t bm_first(int b, int64_t c, int B)
+{
+    const int64_t x = b * c;
+    if (x >> 52) return x / B;
+    int64_t f = (int64_t)((double)x / (double)B);          // off by one at most
+    const int64_t rest = x - f * B;
+    return rest < 0 ? f - 1 : rest >= B ? f + 1 : f;
+}
+
+// Mean and SE of each state (a wave) from its batch sums (NaN below B samples); batch b's mean
+// is its sum / its count, SE = sqrt(sum (m_b - mean(m))^2 / ((B - 1) B)), batches in order.
+// sum(b): the sum of batch b, by lane b % 64.
+template <typename F>
+__device__ __forceinline__ void bm_estimate(int B, int64_t cnt, F sum, double *mean, double *se)
+{
+    const int lane = threadIdx.x % 64;
+    if (cnt < B) {
+        if (lane == 0) *mean = *se = NAN;
+        return;
+    }
+    auto from = [](double v, int l) {
+        const long long bits = __double_as_longlong(v);
+        return __longlong_as_double((long long)(uint32_t)__builtin_amdgcn_readlane((int)bits, l) |
+                                    (long long)__builtin_amdgcn_readlane((int)(bits >> 32), l) << 32);
+    };
+    double tot = 0.0, mb = 0.0, own = 0.0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int b = b0 + lane < B ? b0 + lane : B - 1;
+        const int64_t lo = bm_first(b, cnt, B), hi = bm_first(b + 1, cnt, B);
+        const double v = (double)sum(b);
+        own = v / (double)(hi - lo);
+        for (int l = 0; l < 64 && b0 + l < B; ++l) {
+            tot += from(v, l);
+            mb += from(own, l);
+        }
+    }
+    mb /= B;
+    double v = 0.0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        if (B > 64) {
+            const int b = b0 + lane < B ? b0 + lane : B - 1;
+            const int64_t lo = bm_first(b, cnt, B), hi = bm_first(b + 1, cnt, B);
+            own = (double)sum(b) / (double)(hi - lo);
+        }
+        const double d = own - mb;
+        for (int l = 0; l < 64 && b0 + l < B; ++l) {
+            const double x = from(d, l);
+            v += x * x;
+        }
+    }
+    if (lane == 0) {
+        *mean = tot / (double)cnt;
+        *se = sqrt(v / (double)(B - 1) / (double)B);
+    }
+}
+
+__global__ void __launch_bounds__(256) bm_finish(BmArgs p)
+{
+    const int s = blockIdx.x * 4 + (int)threadIdx.x / 64;
+    if (s < p.S)
+        bm_estimate(p.B, p.count[s], [&](int b) { return p.sum[(size_t)s * p.B + b]; }, p.mean + s, p.se + s);
+}
+
+// The same from samples sorted by state.
 __global__ void bm_check(int64_t ns, const int32_t *st, const int32_t *n, int S, int *bad)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < ns; i += (int64_t)gridDim.x * blockDim.x) {
@@ -518,7 +749,7 @@ __global__ void bm_bounds(int64_t ns, int S, const uint32_t *sorted_state, int64
 // One workgroup per (state, batch): the batch is a contiguous range of the sorted
 // order, its sum of N a block reduction of integers (exact in any order).
 __global__ void bm_segments(int B, const int32_t *sorted_idx, const int32_t *n_orig, const int64_t *state_start,
-                            const int64_t *state_count, unsigned long long *bsum, unsigned long long *bcnt)
+                            const int64_t *state_count, unsigned long long *bsum)
 {
     __shared__ unsigned long long part[4];
     const int bin = blockIdx.x, s = bin / B, b = bin % B;
@@ -530,37 +761,14 @@ __global__ void bm_segments(int B, const int32_t *sorted_idx, const int32_t *n_o
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
     if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        bsum[bin] = part[0] + part[1] + part[2] + part[3];
-        bcnt[bin] = (unsigned long long)(hi - lo);
-    }
+    if (threadIdx.x == 0) bsum[bin] = part[0] + part[1] + part[2] + part[3];
 }
 
-// mean and SE of each state from its batch sums (NaN below B samples); batch b's mean
-// is bsum / bcnt, SE = sqrt(sum (m_b - mean(m))^2 / ((B - 1) B)), batches in order.
-__global__ void bm_finish(int S, int B, const unsigned long long *bsum, const unsigned long long *bcnt,
-                          const int64_t *state_count, double *mean, double *se)
+__global__ void __launch_bounds__(256) bm_finish_sorted(int S, int B, const unsigned long long *sum, const int64_t *count,
+                                                     double *mean, double *se)
 {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= S) return;
-    if (state_count[s] < B) {
-        mean[s] = NAN;
-        se[s] = NAN;
-        return;
-    }
-    double tot = 0.0, mb = 0.0;
-    for (int b = 0; b < B; ++b) {
-        tot += (double)bsum[(size_t)s * B + b];
-        mb += (double)bsum[(size_t)s * B + b] / (double)bcnt[(size_t)s * B + b];
-    }
-    mb /= B;
-    double v = 0.0;
-    for (int b = 0; b < B; ++b) {
-        const double d = (double)bsum[(size_t)s * B + b] / (double)bcnt[(size_t)s * B + b] - mb;
-        v += d * d;
-    }
-    mean[s] = tot / (double)state_count[s];
-    se[s] = sqrt(v / (double)(B - 1) / (double)B);
+    const int s = blockIdx.x * 4 + (int)threadIdx.x / 64;
+    if (s < S) bm_estimate(B, count[s], [&](int b) { return sum[(size_t)s * B + b]; }, mean + s, se + s);
 }
 
 // Moving-block bootstrap, replicate b: block j (of ceil(R / block)) starts at record
@@ -3143,20 +3351,21 @@ static int refresh_logd(regc_mbar *mb)
 }
 
 // Per-state mean of N and its batch-means SE of ns samples (state, n) in the order
-// given, device arrays; outputs device arrays [S].  EINVAL on a state outside 0..S-1
+// given, device arrays; outputs host arrays [S].  EINVAL on a state outside 0..S-1
 // or a negative N.
-static int batch_means_dev(hipStream_t s, int64_t ns, const int32_t *st_d, const int32_t *n_d, int S, int B,
-                           double *mean_d, double *se_d)
+static int batch_means_sorted(hipStream_t s, int64_t ns, const int32_t *st_d, const int32_t *n_d, int S, int B,
+                              std::vector<double> &out)
 {
     DevBuf<uint32_t> keys, keys_out;
     DevBuf<int32_t> idx, idx_out;
     DevBuf<int64_t> start_d, count_d;
-    DevBuf<unsigned long long> bsum, bcnt;
+    DevBuf<unsigned long long> bsum;
+    DevBuf<double> out_d;
     DevBuf<int> bad;
     int rc;
     if ((rc = keys.alloc(ns)) || (rc = keys_out.alloc(ns)) || (rc = idx.alloc(ns)) || (rc = idx_out.alloc(ns)) ||
         (rc = start_d.alloc(S)) || (rc = count_d.alloc(S)) || (rc = bsum.alloc((size_t)S * B)) ||
-        (rc = bcnt.alloc((size_t)S * B)) || (rc = bad.alloc(1)))
+        (rc = out_d.alloc(2 * (size_t)S)) || (rc = bad.alloc(1)))
         return rc;
     const int grid = (int)std::min<int64_t>((ns + 255) / 256, 4096);
     // the inputs are checked before they are used as sort keys
@@ -3181,13 +3390,54 @@ static int batch_means_dev(hipStream_t s, int64_t ns, const int32_t *st_d, const
                                                 end_bit, s));
     hipLaunchKernelGGL(bm_bounds, dim3((S + 255) / 256), dim3(256), 0, s, ns, S, keys_out.p, start_d.p, count_d.p);
     REGC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(bm_segments, dim3(S * B), dim3(256), 0, s, B, idx_out.p, n_d, start_d.p, count_d.p, bsum.p,
-                       bcnt.p);
+    hipLaunchKernelGGL(bm_segments, dim3(S * B), dim3(256), 0, s, B, idx_out.p, n_d, start_d.p, count_d.p, bsum.p);
     REGC_HIP(hipGetLastError());
-    hipLaunchKernelGGL(bm_finish, dim3((S + 255) / 256), dim3(256), 0, s, S, B, bsum.p, bcnt.p, count_d.p, mean_d,
-                       se_d);
+    hipLaunchKernelGGL(bm_finish_sorted, dim3((S + 3) / 4), dim3(256), 0, s, S, B, bsum.p, count_d.p, out_d.p, out_d.p + S);
     REGC_HIP(hipGetLastError());
+    REGC_HIP(hipMemcpyAsync(out.data(), out_d.p, sizeof(double) * 2 * S, hipMemcpyDeviceToHost, s));
     REGC_HIP(hipStreamSynchronize(s));
+    return REGC_OK;
+}
+
+static int batch_means_dev(hipStream_t s, int64_t ns, const int32_t *st_d, const int32_t *n_d, int S, int B, double *mean,
+                           double *se)
+{
+    std::vector<double> out(2 * (size_t)S + 1);
+    int rc;
+    // waves per block: as many as there is LDS for
+    constexpr size_t kLds = (size_t)64 << 10;
+    const int W = bm_bytes(S, 8) <= kLds ? 8 : bm_bytes(S, 2) <= kLds ? 2 : 0;
+    if (!W) {
+        if ((rc = batch_means_sorted(s, ns, st_d, n_d, S, B, out))) return rc;
+    } else {
+        BmArgs p{};
+        p.ns = ns; p.st = st_d; p.n = n_d; p.S = S; p.B = B;
+        p.blocks = (int)std::min<int64_t>((ns + 255) / 256, kBmBlocks);
+        // one allocation: batch sums | mean, se, the flag | first ranks | counts | the blocks' flags
+        DevBuf<unsigned long long> work;
+        const size_t bins = (size_t)S * B;
+        if ((rc = work.alloc(bins + 2 * (size_t)S + 1 + ((size_t)(p.blocks + 1) * S + p.blocks + 1) / 2))) return rc;
+        p.sum = work.p;
+        p.mean = reinterpret_cast<double *>(work.p + bins);
+        p.se = p.mean + S;
+        p.any_bad = reinterpret_cast<int *>(p.se + S);
+        p.hist = reinterpret_cast<uint32_t *>(p.se + S + 1);
+        p.count = p.hist + (size_t)p.blocks * S;
+        p.bad = reinterpret_cast<int *>(p.count + S);
+        hipLaunchKernelGGL(bm_count, dim3(p.blocks), dim3(kBmThreads), sizeof(uint32_t) * S, s, p);
+        hipLaunchKernelGGL(bm_scan, dim3((S + 63) / 64), dim3(1024), 0, s, p);
+        if (W == 8) hipLaunchKernelGGL((bm_sum<8>), dim3(p.blocks), dim3(512), bm_bytes(S, 8), s, p);
+        else hipLaunchKernelGGL((bm_sum<2>), dim3(p.blocks), dim3(128), bm_bytes(S, 2), s, p);
+        hipLaunchKernelGGL(bm_finish, dim3((S + 3) / 4), dim3(256), 0, s, p);
+        REGC_HIP(hipGetLastError());
+        REGC_HIP(hipMemcpyAsync(out.data(), p.mean, sizeof(double) * out.size(), hipMemcpyDeviceToHost, s));
+        REGC_HIP(hipStreamSynchronize(s));
+        int bad;
+        memcpy(&bad, &out[2 * (size_t)S], sizeof bad);
+        REGC_CHECK(!bad, REGC_EINVAL, "a sample's state is outside 0..%d or its N is negative", S - 1);
+    }
+    std::copy(out.begin(), out.begin() + S, mean);
+    std::copy(out.begin() + S, out.begin() + 2 * (size_t)S, se);
     return REGC_OK;
 }
 
@@ -3199,9 +3449,7 @@ extern "C" int regc_batch_means(int64_t ns, const int32_t *state, const int32_t 
     REGC_CHECK(n_states > 0 && n_batches >= 2, REGC_EINVAL, "n_states must be positive and n_batches >= 2");
     hipStream_t s = static_cast<hipStream_t>(stream);
     DevBuf<int32_t> st_in, n_in;
-    DevBuf<double> m_d, se_d;
     int rc;
-    if ((rc = m_d.alloc(n_states)) || (rc = se_d.alloc(n_states))) return rc;
     const int32_t *st_d = state, *n_d = n;
     if (!on_device) {
         if ((rc = st_in.alloc(ns)) || (rc = n_in.alloc(ns))) return rc;
@@ -3210,10 +3458,7 @@ extern "C" int regc_batch_means(int64_t ns, const int32_t *state, const int32_t 
         st_d = st_in.p;
         n_d = n_in.p;
     }
-    if ((rc = batch_means_dev(s, ns, st_d, n_d, n_states, n_batches, m_d.p, se_d.p))) return rc;
-    REGC_HIP(hipMemcpy(mean, m_d.p, sizeof(double) * n_states, hipMemcpyDeviceToHost));
-    REGC_HIP(hipMemcpy(se, se_d.p, sizeof(double) * n_states, hipMemcpyDeviceToHost));
-    return REGC_OK;
+    return batch_means_dev(s, ns, st_d, n_d, n_states, n_batches, mean, se);
 }
 
 extern "C" int regc_reweight(regc_mbar *mb, const regc_grid *targets, double tol, int max_iter,
@@ -3249,18 +3494,18 @@ extern "C" int regc_reweight(regc_mbar *mb, const regc_grid *targets, double tol
     TargetDev T;
     if ((rc = target_grid(mb, targets, T))) return rc;
     const int nK = T.nK;
-    DevBuf<double> mn, me, me2, pn, heat, cov, smean, sse;
+    DevBuf<double> mn, me, me2, pn, heat, cov;
+    std::vector<double> state_mean(mb->S), state_se(mb->S);
     DevBuf<int32_t> ph;
     if ((rc = mn.alloc(nK)) || (rc = me.alloc(nK)) || (rc = me2.alloc(nK)) || (rc = ph.alloc(nK)) ||
-        (rc = pn.alloc(p_n ? (size_t)nK * mb->nN : 1)) || (rc = heat.alloc(nK)) || (rc = cov.alloc(nK)) ||
-        (rc = smean.alloc(mb->S)) || (rc = sse.alloc(mb->S)))
+        (rc = pn.alloc(p_n ? (size_t)nK * mb->nN : 1)) || (rc = heat.alloc(nK)) || (rc = cov.alloc(nK)))
         return rc;
     if ((rc = targets_dev(mb, T, nullptr, mn.p, me.p, me2.p, p_n ? pn.p : nullptr, ph.p))) return rc;
     hipLaunchKernelGGL(heat_cov, dim3((nK + 255) / 256), dim3(256), 0, s, T.nT, T.nMu, T.tb_d.p, mn.p, me.p, me2.p,
                        o.n_sites > 0 ? o.n_sites : 1.0, heat.p, cov.p);
     REGC_HIP(hipGetLastError());
-    if ((rc = batch_means_dev(mb->stream, mb->ns, mb->s_orig_d.p, mb->n_orig_d.p, mb->S, o.n_batches, smean.p,
-                              sse.p)))
+    if ((rc = batch_means_dev(s, mb->ns, mb->s_orig_d.p, mb->n_orig_d.p, mb->S, o.n_batches, state_mean.data(),
+                              state_se.data())))
         return rc;
     REGC_HIP(hipStreamSynchronize(s));
     if (mean_n) REGC_HIP(hipMemcpy(mean_n, mn.p, sizeof(double) * nK, hipMemcpyDeviceToHost));
@@ -3268,8 +3513,8 @@ extern "C" int regc_reweight(regc_mbar *mb, const regc_grid *targets, double tol
     if (p_n) REGC_HIP(hipMemcpy(p_n, pn.p, sizeof(double) * nK * mb->nN, hipMemcpyDeviceToHost));
     if (heat_cap) REGC_HIP(hipMemcpy(heat_cap, heat.p, sizeof(double) * nK, hipMemcpyDeviceToHost));
     if (coverage) REGC_HIP(hipMemcpy(coverage, cov.p, sizeof(double) * nK, hipMemcpyDeviceToHost));
-    if (mean_state_n) REGC_HIP(hipMemcpy(mean_state_n, smean.p, sizeof(double) * mb->S, hipMemcpyDeviceToHost));
-    if (se_state_n) REGC_HIP(hipMemcpy(se_state_n, sse.p, sizeof(double) * mb->S, hipMemcpyDeviceToHost));
+    if (mean_state_n) std::copy(state_mean.begin(), state_mean.end(), mean_state_n);
+    if (se_state_n) std::copy(state_se.begin(), state_se.end(), se_state_n);
     const bool want_boot = se_n || se_coverage || se_heat_cap;
     if (!want_boot || o.n_boot == 0) {
         const double nan = NAN;
