@@ -49,6 +49,7 @@ struct regc_ctx {
     hipStream_t stream = nullptr;
     int wpb = 1, split = 1, nblocks = 0, max_slab_len = 0, max_slab_scan = 0;
     int max_halo_len = 0;   // the longest LDS slab copy with its periodic halo
+    int binned = 0;         // classes with a column grid: 0 none, 1 all, 2 some
     bool halo = false, learn_halo = false;   // the sweep and the learned kernels' copies carry it
     bool cull = false;
     bool balance = false;   // walker order by cost before each one-trial sweep launch
@@ -344,6 +345,7 @@ static int ctx_alloc_and_init(regc_ctx *c)
         d.inv_cw_x = h.bins ? h.ncx / h.sys.lx : 0.0;
         d.inv_cw_y = h.bins ? h.ncy / h.sys.ly : 0.0;
         max_slab_len = std::max(max_slab_len, len);
+        c->binned = k == 0 ? h.bins : (c->binned == (int)h.bins ? c->binned : 2);
         c->max_halo_len = std::max(c->max_halo_len, h.bins ? (h.ncx + 2) * (h.ncy + 2) * h.cap : len);
         c->max_slab_scan = std::max(c->max_slab_scan, h.bins ? 9 * h.cap : len);
     }
@@ -646,6 +648,10 @@ static SweepArgs sweep_args(regc_ctx *c, int64_t sweep0, int n, bool use_clock)
     a.trace_words = c->words;
     const bool halo = learned_on(c) ? c->learn_halo : c->halo;
     a.slab_halo = halo ? 1 : 0;
+    a.slab_mode = c->pot.mode == REGC_MODE_IDEAL || c->binned == 2 ? kSlabAny
+                  : !c->binned                                     ? kSlabAll
+                  : halo                                           ? kSlabHalo
+                                                                   : kSlabWrap;
     a.max_slab_len = halo ? c->max_halo_len : c->max_slab_len;
     a.gas_stride = c->nmax_all;
     a.max_slab_scan = c->max_slab_scan;

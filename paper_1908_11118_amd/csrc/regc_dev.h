@@ -55,6 +55,9 @@ struct SwapArgs {
     int S_total;
 };
 
+// Slab access of a class (sweep_dev.h says how each reads the LDS copy).
+enum { kSlabAny = -1, kSlabAll = 0, kSlabHalo = 1, kSlabWrap = 2 };
+
 struct SweepArgs {
     const ClassDev *cls;
     const int *block_class;      // per block
@@ -92,6 +95,7 @@ struct SweepArgs {
     int64_t trace_sweep0, trace_cap;
     int trace_words;
     int slab_halo;                  // the slab's LDS copy carries its periodic halo (max_slab_len includes it)
+    int slab_mode;                  // every class's slab access in this launch, kSlabAny when they differ or for an ideal gas
     int max_slab_len;               // LDS carve sizes of this launch
     int gas_stride;                 // LDS entries per walker (max n_max over classes)
     int max_slab_scan;              // most slab candidates one trial scans (max over classes)

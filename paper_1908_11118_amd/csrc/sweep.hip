@@ -117,7 +117,10 @@ __device__ __forceinline__ void grid_sync(const SweepArgs &a)
 // lane.  Measured per 10-sweep launch, before and after: 1024 walkers with N <= 200 (two
 // waves each) 2.36 -> 1.72 ms, 4096 uneven walkers with N <= 500 (one wave each) 10.1 ->
 // 7.6 ms, 64 walkers in FP64 0.55 -> 0.39 ms, with the same trajectories bit for bit.
-template <int SPLIT, bool CULL, bool PERSIST>
+// MODE: how the slab is read, fixed where every class of the launch reads it alike and the
+// gas interacts (kSlabAny: decided as it runs).  A trial's path has about thirty branches, each a few
+// issue slots of the one or two waves that a SIMD has; fixing it takes out a third: MEASURED.
+template <int SPLIT, bool CULL, bool PERSIST, int MODE = kSlabAny>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     extern __shared__ __align__(32) unsigned char smem[];
@@ -194,8 +197,8 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     gg.shift = in_vgpr((Real)a.pot.shift_gg); gg.rc2 = in_vgpr((Real)a.pot.rc2); gg.hc2 = in_vgpr((Real)a.pot.hc2_gg);
     gs.sig2 = in_vgpr((Real)a.pot.sig2_gs); gs.eps4 = in_vgpr((Real)a.pot.eps4_gs);
     gs.shift = in_vgpr((Real)a.pot.shift_gs); gs.rc2 = gg.rc2; gs.hc2 = in_vgpr((Real)a.pot.hc2_gs);
-    const bool ideal = a.pot.ideal != 0;
-    SlabView sv = slab_view(C, a, slab);
+    const bool ideal = MODE == kSlabAny && a.pot.ideal != 0;
+    SlabView sv = slab_view<MODE>(C, a, slab);
     sv.inv_cw_x = in_vgpr(sv.inv_cw_x); sv.inv_cw_y = in_vgpr(sv.inv_cw_y);
     sv.top_plus_rc = in_vgpr(sv.top_plus_rc);
     const SlabLane sl = slab_lane<SPLIT>(sv, lane, part);
@@ -505,11 +508,11 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     }
 }
 
-template <int SPLIT, bool CULL>
+template <int SPLIT, bool CULL, int MODE = kSlabAny>
 __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock, SPLIT != 2 ? kSweepWavesPerSimd : 1)
     sweep_kernel(SweepArgs a)
 {
-    sweep_body<SPLIT, CULL, false>(a);
+    sweep_body<SPLIT, CULL, false, MODE>(a);
 }
 
 template <int SPLIT>
@@ -1408,6 +1411,7 @@ __device__ double md_run(Real4 *gas, double *v, double *f, int n, double T, cons
 // replica-exchange step before this launch.  Then mc_cycles cycles of N
 // displacement attempts, trials 1 .. mc_cycles N with N after trial 0.  Same
 // trial arithmetic as sweep_kernel (one wave per walker).  Single-class contexts.
+template <int MODE>
 __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(SweepArgs a, PaperArgs pa)
 {
     extern __shared__ __align__(32) unsigned char smem[];
@@ -1461,8 +1465,8 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
     gg.rc2 = (Real)a.pot.rc2; gg.hc2 = (Real)a.pot.hc2_gg;
     gs.sig2 = (Real)a.pot.sig2_gs; gs.eps4 = (Real)a.pot.eps4_gs; gs.shift = (Real)a.pot.shift_gs;
     gs.rc2 = gg.rc2; gs.hc2 = (Real)a.pot.hc2_gs;
-    const bool ideal = a.pot.ideal != 0;
-    const SlabView sv = slab_view(C, a, slab);
+    const bool ideal = MODE == kSlabAny && a.pot.ideal != 0;
+    const SlabView sv = slab_view<MODE>(C, a, slab);
     const SlabLane sl = slab_lane<1>(sv, lane, 0);
     const double lx = C.lx, ly = C.ly, zlo = C.zlo, zhi = C.zhi, H = C.zhi - C.zlo;
     const double md = a.max_disp;
@@ -1711,7 +1715,10 @@ hipError_t ENERGY_LAUNCH(const EnergyArgs &a, hipStream_t s)
 hipError_t PAPER_LAUNCH(const SweepArgs &a, const PaperArgs &p, int n_blocks, int waves_per_block, size_t smem,
                         hipStream_t s)
 {
-    hipLaunchKernelGGL(paper_kernel, dim3(n_blocks), dim3(kWave * waves_per_block), smem, s, a, p);
+    const dim3 grid(n_blocks), block(kWave * waves_per_block);
+    if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((paper_kernel<kSlabHalo>), grid, block, smem, s, a, p);
+    else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((paper_kernel<kSlabAll>), grid, block, smem, s, a, p);
+    else hipLaunchKernelGGL((paper_kernel<kSlabAny>), grid, block, smem, s, a, p);
     return hipGetLastError();
 }
 
@@ -1736,9 +1743,13 @@ hipError_t SWEEP_LAUNCH(const SweepArgs &a, int n_blocks, int waves_per_block, i
         else hipLaunchKernelGGL((sweep_kernel<4, false>), grid, block, smem, s, a);
     } else if (split == 2) {
         if (cull) hipLaunchKernelGGL((sweep_kernel<2, true>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_kernel<2, false, kSlabHalo>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_kernel<2, false, kSlabAll>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((sweep_kernel<2, false>), grid, block, smem, s, a);
     } else {
         if (cull) hipLaunchKernelGGL((sweep_kernel<1, true>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_kernel<1, false, kSlabHalo>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_kernel<1, false, kSlabAll>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((sweep_kernel<1, false>), grid, block, smem, s, a);
     }
     return hipGetLastError();

@@ -243,7 +243,6 @@ __device__ __forceinline__ Real bcast_real(Real v, int lane) { return bcast(v, l
 //             first entry.  Deriving it with periodic wraps took about 30 issue slots per
 //             64 candidates, as much as a candidate's pair term;
 //  kSlabWrap  no halo, indices by periodic wrap: for a slab whose halo does not fit LDS.
-enum { kSlabAll = 0, kSlabHalo = 1, kSlabWrap = 2 };
 
 struct SlabView {
     const Real4 *atoms;
@@ -255,11 +254,13 @@ struct SlabView {
     Real top_plus_rc;
 };
 
+// MODE: the launch's slab access where its kernel is made for one (kSlabAny: the class's).
+template <int MODE = kSlabAny>
 __device__ __forceinline__ SlabView slab_view(const ClassDev &C, const SweepArgs &a, const Real4 *atoms)
 {
     SlabView sv;
     sv.atoms = atoms;
-    sv.mode = !C.bins ? kSlabAll : (a.slab_halo ? kSlabHalo : kSlabWrap);
+    sv.mode = MODE != kSlabAny ? MODE : !C.bins ? kSlabAll : (a.slab_halo ? kSlabHalo : kSlabWrap);
     sv.len = C.bins ? 9 * C.cap : C.slab_len;
     sv.ncx = C.ncx; sv.ncy = C.ncy; sv.cap = C.cap;
     sv.row = sv.mode == kSlabHalo ? C.ncx + 2 : C.ncx;
