@@ -119,7 +119,7 @@ __device__ __forceinline__ void grid_sync(const SweepArgs &a)
 // 7.6 ms, 64 walkers in FP64 0.55 -> 0.39 ms, with the same trajectories bit for bit.
 // MODE: how the slab is read, fixed where every class of the launch reads it alike and the
 // gas interacts (kSlabAny: decided as it runs).  A trial's path has about thirty branches, each a few
-// issue slots of the one or two waves that a SIMD has; fixing it takes out a third: MEASURED.
+// issue slots of the one or two waves that a SIMD has; fixing it takes out a third (1024 walkers with N <= 200, 100 sweeps: 17.4 -> 16.1 ms).
 template <int SPLIT, bool CULL, bool PERSIST, int MODE = kSlabAny>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
@@ -211,14 +211,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     const bool all_disp = (a.th_disp >> 32) != 0, all_ins = (a.th_ins >> 32) != 0;
     const uint32_t th_disp = (uint32_t)a.th_disp, th_ins = (uint32_t)a.th_ins;
 
-    struct alignas(8) Part {   // what a wave gives the others: its sum and whether it met a hard core
-        Real de;
-        uint32_t core;
-    };
     uint32_t stat = 0;     // lane k < kNStat holds counter k (kept as masks over a batch until its end)
     uint32_t useful = 0;   // evaluated pairs inside the cutoff
     uint64_t cand = 0;     // candidate pairs of all parts
-    uint32_t xcount = 0;   // exchanges so far: consecutive exchanges use alternate slots
+    uint32_t xcount = 0, xresync = 0;   // exchanges so far: consecutive exchanges use alternate slots
 
     auto flush_counts = [&]() {
         if (lane < kNStat && stat) atomicAdd(a.stats + (size_t)sg * kNStat + lane, (unsigned long long)stat);
@@ -271,6 +267,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             // accept iff dE <= (ln prefactor - ln U) / beta (U <= min(1, A)); a displacement's
             // prefactor is 1
             const double tl = kl == 0 ? (0.0 - lnU) * tinv : lnU;
+            uint32_t cb = 0;                // the batch's candidate pairs
             uint64_t accm = 0, nonem = 0, wallm = 0, corem = 0;    // accepted; at the cap / empty; wall; hard core
             if (SPLIT >= 2) __builtin_amdgcn_s_setprio(2);
             for (int t2 = 0; t2 < 2 * tn; t2 += 2) {
@@ -300,24 +297,20 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         de = (double)pd;
                         return (int64_t)__ballot(de <= thr) < 0;
                     }
-                    // alternate slots: exchange k+2 reuses the slot of exchange k
-                    // only after every wave passed the barrier of exchange k+1
-                    Part *x0 = reinterpret_cast<Part *>(xch) + (xcount & 1) * SPLIT;
-                    if (lane == kWave - 1) x0[part] = Part{pd, core != 0 ? 1u : 0u};
+                    // a hard core makes the sum infinite, so that one test decides.  Alternate slots:
+                    // exchange k+2 reuses the slot of exchange k only after every wave passed the
+                    // barrier of exchange k+1
+                    Real *x0 = reinterpret_cast<Real *>(xch) + (xcount & 1) * SPLIT;
+                    if (can_overlap) pd = core != 0 ? Real(INFINITY) : pd;
+                    if (lane == kWave - 1) x0[part] = pd;
                     ++xcount;
                     __syncthreads();
-                    uint32_t cf = x0[0].core;
-                    de = (double)x0[0].de;
+                    de = (double)x0[0];
 #pragma unroll
-                    for (int q = 1; q < SPLIT; ++q) {
-                        de += (double)x0[q].de;
-                        cf |= x0[q].core;
-                    }
-                    if (can_overlap && uniform(cf != 0)) {
-                        corem |= bit;
-                        return false;
-                    }
-                    return uniform(de <= thr);
+                    for (int q = 1; q < SPLIT; ++q) de += (double)x0[q];
+                    if (uniform(de <= thr)) return true;
+                    if (can_overlap && uniform(de == (double)INFINITY)) corem |= bit;
+                    return false;
                 };
                 // An accepted move.  Every wave of the walker writes the update into the shared
                 // LDS copy itself (the same value), so a wave needs only its own write to be
@@ -330,7 +323,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     accm |= bit;
                     e += de;
                     if (SPLIT > 1 && ideal) __syncthreads();
-                    if (lane == 0) gas[at] = v;
+                    gas[at] = v;                 // (every lane holds the same: no branch for one of them)
                     if (SPLIT == 1 || !ideal) wave_sync(); else __syncthreads();
                 };
                 // several waves per walker: the pair loop at the lowest issue priority, the rest
@@ -354,7 +347,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         pd = lane_delta<true, false, SPLIT, CULL, true>(gas, n, -1, sv, sl, b, gg, gs, lane, part, v.x, v.y,
                                                                         v.z, v.x, v.y, v.z, qgas, qslab, core, useful, near,
                                                                         pre);
-                        cand += (uint32_t)(n + (near ? sv.len : 0));
+                        cb += (uint32_t)(n + (near ? sv.len : 0));
                     }
                     if (!decide(pd, core, thr, true)) continue;
                     accept(n, v);
@@ -378,7 +371,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         pd = lane_delta<false, true, SPLIT, CULL, true>(gas, n, i, sv, sl, b, gg, gs, lane, part, o.x, o.y,
                                                                         o.z, o.x, o.y, o.z, qgas, qslab, core, useful, near,
                                                                         pre);
-                        cand += (uint32_t)(n - 1 + (near ? sv.len : 0));
+                        cb += (uint32_t)(n - 1 + (near ? sv.len : 0));
                     }
                     if (!decide(pd, core, thr, false)) continue;
                     accept(i, last);
@@ -407,11 +400,12 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                     bool near = false;
                     pd = lane_delta<true, true, SPLIT, CULL, true>(gas, n, i, sv, sl, b, gg, gs, lane, part, v.x, v.y, v.z,
                                                                    o.x, o.y, o.z, qgas, qslab, core, useful, near, pre);
-                    cand += 2u * (uint32_t)(n - 1 + (near ? sv.len : 0));
+                    cb += 2u * (uint32_t)(n - 1 + (near ? sv.len : 0));
                 }
                 if (!decide(pd, core, thr, true)) continue;
                 accept(i, v);
             }
+            cand += cb;
             // the batch's events, counter k in lane k
             const uint32_t ev[kNStat] = {(uint32_t)__popcll(is_disp), (uint32_t)__popcll(accm & is_disp), (uint32_t)__popcll(is_ins), (uint32_t)__popcll(accm & is_ins),
                                     (uint32_t)__popcll(is_del), (uint32_t)__popcll(accm & is_del), (uint32_t)__popcll(nonem & is_ins),
@@ -440,14 +434,14 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
             if (SPLIT == 1) {
                 e = pe;
             } else {
-                constexpr int PW = (int)(sizeof(Part) / sizeof(double));
-                double *x0 = reinterpret_cast<double *>(reinterpret_cast<Part *>(xch) + (xcount & 1) * SPLIT);
-                if (lane == 0) x0[PW * part] = pe;
+                // (a slot of its own: past the two of the trials' exchanges)
+                double *x0 = xch + 2 * SPLIT + (xresync & 1) * SPLIT;
+                if (lane == 0) x0[part] = pe;
                 __syncthreads();
                 e = x0[0];
 #pragma unroll
-                for (int q = 1; q < SPLIT; ++q) e += x0[PW * q];
-                ++xcount;
+                for (int q = 1; q < SPLIT; ++q) e += x0[q];
+                ++xresync;
             }
         }
         if (part == 0 && lane == kWave - 1) {
