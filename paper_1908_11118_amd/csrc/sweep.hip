@@ -1278,8 +1278,10 @@ __device__ __forceinline__ void box_muller(uint32_t w1, uint32_t w2, double &z0,
 {
     const double r = sqrt(-2.0 * log(uniform_open(w1)));
     const double t = 6.283185307179586 * uniform_open(w2);
-    z0 = r * cos(t);
-    z1 = r * sin(t);
+    double sn, cs;
+    sincos(t, &sn, &cs);
+    z0 = r * cs;
+    z1 = r * sn;
 }
 
 __device__ __forceinline__ double md_min_image(double d, double box)
@@ -1287,45 +1289,57 @@ __device__ __forceinline__ double md_min_image(double d, double box)
     return d > 0.5 * box ? d - box : (d < -0.5 * box ? d + box : d);
 }
 
-// Forces on the walker's particles (lane-strided over particles; each particle sums
-// its gas partners in index order, then every packed slab entry) and the potential
-// energy (FP64, wave-uniform).  Truncated-shifted LJ; the shift does not act on forces.
+// Forces on the walker's particles and the potential energy (FP64, wave-uniform).  Truncated-
+// shifted LJ; the shift does not act on forces.  The loop over a particle's partners is
+// the step's time, so it is as short as 64 lanes allow: with at most 32 (16, 8, ...) particles
+// two (four, eight, ...) lanes share a particle's partners, and of a slab in columns only
+// the particle's block of nine is read (ten MD steps a REGC step: 66 walkers with N <= 44 on a
+// layer of 100 atoms, 13 steps 4.4 -> 3.0 ms; 14 with N <= 37 on 75 atoms, 39 steps 10.4 -> 9.4).
 __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const PotDev &pot, const Box &b, double *f,
                             int lane)
 {
     double e = 0.0;
     if (!pot.ideal) {
         const double lx = (double)b.lx, ly = (double)b.ly;
-        for (int i = lane; i < n; i += kWave) {
-            const double xi = (double)gas[i].x, yi = (double)gas[i].y, zi = (double)gas[i].z;
-            double fx = 0.0, fy = 0.0, fz = 0.0, ei = 0.0;
-            for (int j = 0; j < n; ++j) {
-                if (j == i) continue;
-                const double dx = md_min_image(xi - (double)gas[j].x, lx);
-                const double dy = md_min_image(yi - (double)gas[j].y, ly);
-                const double dz = zi - (double)gas[j].z;
-                const double r2 = dx * dx + dy * dy + dz * dz;
-                if (r2 >= pot.rc2) continue;
-                const double s2 = pot.sig2_gg / r2, s6 = s2 * s2 * s2;
-                const double g = 6.0 * pot.eps4_gg * (2.0 * s6 * s6 - s6) / r2;
-                fx += g * dx; fy += g * dy; fz += g * dz;
-                ei += 0.5 * (pot.eps4_gg * (s6 * s6 - s6) - pot.shift_gg);
+        int shares = 1;                              // lanes per particle
+        while (2 * shares * n <= kWave) shares *= 2;
+        const int width = kWave / shares, g = lane / width;
+        for (int i0 = 0; i0 < n; i0 += width) {
+            const int i = i0 + lane % width;
+            double fx = 0.0, fy = 0.0, fz = 0.0;
+            if (i < n) {
+                const double xi = (double)gas[i].x, yi = (double)gas[i].y, zi = (double)gas[i].z;
+                // (selects, not branches: several partners' chains of dependent operations overlap)
+                auto partner = [&](const Real4 &p, bool in, double sig2, double eps4, double shift, double part) {
+                    const double dx = md_min_image(xi - (double)p.x, lx);
+                    const double dy = md_min_image(yi - (double)p.y, ly);
+                    const double dz = zi - (double)p.z;
+                    const double r2 = dx * dx + dy * dy + dz * dz;
+                    in = in && r2 < pot.rc2;
+                    const double inv = 1.0 / r2, s2 = sig2 * inv, s6 = s2 * s2 * s2;
+                    const double h = in ? 6.0 * eps4 * (2.0 * s6 * s6 - s6) * inv : 0.0;
+                    fx += h * dx; fy += h * dy; fz += h * dz;
+                    e += in ? part * (eps4 * (s6 * s6 - s6) - shift) : 0.0;
+                };
+#pragma unroll 4
+                for (int j = g; j < n; j += shares) partner(gas[j], j != i, pot.sig2_gg, pot.eps4_gg, pot.shift_gg, 0.5);
+                if (zi < (double)sv.top_plus_rc) {
+                    int cx = 0, cy = 0;
+                    if (sv.mode != kSlabAll) column_of(sv, gas[i].x, gas[i].y, cx, cy);
+#pragma unroll 4
+                    for (int k = g; k < sv.len; k += shares)
+                        partner(sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, k) : k], true, pot.sig2_gs, pot.eps4_gs,
+                                pot.shift_gs, 1.0);
+                }
             }
-            const int ns = sv.mode != kSlabAll ? sv.ncx * sv.ncy * sv.cap : sv.len;    // (no halo with MD)
-            for (int k = 0; k < ns; ++k) {
-                const Real4 sa = sv.atoms[k];
-                const double dx = md_min_image(xi - (double)sa.x, lx);
-                const double dy = md_min_image(yi - (double)sa.y, ly);
-                const double dz = zi - (double)sa.z;
-                const double r2 = dx * dx + dy * dy + dz * dz;
-                if (r2 >= pot.rc2) continue;
-                const double s2 = pot.sig2_gs / r2, s6 = s2 * s2 * s2;
-                const double g = 6.0 * pot.eps4_gs * (2.0 * s6 * s6 - s6) / r2;
-                fx += g * dx; fy += g * dy; fz += g * dz;
-                ei += pot.eps4_gs * (s6 * s6 - s6) - pot.shift_gs;
+            for (int o = width; o < kWave; o *= 2) {
+                fx += __shfl_xor(fx, o);
+                fy += __shfl_xor(fy, o);
+                fz += __shfl_xor(fz, o);
             }
-            f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;
-            e += ei;
+            if (i < n && g == 0) {
+                f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;
+            }
         }
     } else {
         for (int i = lane; i < n; i += kWave) f[3 * i] = f[3 * i + 1] = f[3 * i + 2] = 0.0;
@@ -1345,6 +1359,7 @@ __device__ double md_run(Real4 *gas, double *v, double *f, int n, double T, cons
                          uint32_t k1, int lane)
 {
     const double dt = pa.md_dt, lx = (double)b.lx, ly = (double)b.ly;
+    const double c = pa.md_tau > 0.0 ? exp(-dt / pa.md_tau) : 0.0;
     double e = md_forces(gas, n, sv, pot, b, f, lane);
     for (int st = 0; st < pa.md_steps; ++st) {
         for (int i = lane; i < n; i += kWave) {
@@ -1386,7 +1401,6 @@ __device__ double md_run(Real4 *gas, double *v, double *f, int n, double T, cons
                 }
                 const double S = wave_sum(s);
                 const double Kbar = 0.5 * nf * T;
-                const double c = exp(-dt / pa.md_tau);
                 const double K2 = c * K + (1.0 - c) * Kbar * (r1 * r1 + S) / nf +
                                   2.0 * sqrt(c * (1.0 - c) * K * Kbar / nf) * r1;
                 const double alpha = sqrt(K2 / K);
@@ -1404,7 +1418,9 @@ __device__ double md_run(Real4 *gas, double *v, double *f, int n, double T, cons
 // when A0 < 2^31, i.e. y1 < 1/2, else insertion); otherwise the host has run the
 // replica-exchange step before this launch.  Then mc_cycles cycles of N
 // displacement attempts, trials 1 .. mc_cycles N with N after trial 0.  Same
-// trial arithmetic as sweep_kernel (one wave per walker).  Single-class contexts.
+// trial arithmetic as sweep_kernel (one wave per walker), and its layout: the chain's
+// decisions in scalar registers, 32 trials decoded at once (64 walkers, N <= 40, ten cycles, 20 steps in
+// FP64: 9.3 -> 6.1 ms).  Single-class contexts.
 template <int MODE>
 __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(SweepArgs a, PaperArgs pa)
 {
@@ -1502,102 +1518,125 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock) paper_kernel(Swee
             const uint4 R = philox4x32_10(
                 make_uint4((uint32_t)(t0 + (lane >> 1)), (uint32_t)step, (uint32_t)w, (uint32_t)(lane & 1)),
                 a.key0, a.key1);
-            const double f0 = uniform_open(R.z), f1 = uniform_open(R.w), f2 = uniform_open(R.x);
-            const double f3 = log(uniform53(R.y, R.z));
-            uint32_t bits = 0;
-            for (int tt = 0; tt < 32 && t0 + tt < T; ++tt) {
-                const int t = t0 + tt;
-                if (t == 0 && !exchange) continue;
-                const uint32_t A0 = bcast(R.x, 2 * tt), A1 = bcast(R.y, 2 * tt);
-                // trial 0: removal when y1 = A0 / 2^32 < 1/2, else insertion; then displacements
-                const int kind = t == 0 ? (A0 < 0x80000000u ? 2 : 1) : 0;
-                stat += lane == 2 * kind;
-                bool accepted = false;
-                if (kind == 1 ? n >= n_max : n == 0) {
-                    stat += lane == (kind == 1 ? 6 : 7);
-                } else {
-                    const double lnU = bcast(f3, 2 * tt + 1);
-                    const double ux = bcast(f0, 2 * tt), uy = bcast(f1, 2 * tt), uz = bcast(f2, 2 * tt + 1);
-                    const int i = kind == 1 ? -1 : (int)__umulhi(A1, (uint32_t)n);
-                    const Real4 o = gas[kind == 1 ? 0 : i];
-                    double px = 0.0, py = 0.0, pz = 0.0, c;
-                    bool wall = false;
-                    if (kind == 0) {
-                        px = (double)o.x + md * (2.0 * ux - 1.0);
-                        py = (double)o.y + md * (2.0 * uy - 1.0);
-                        pz = (double)o.z + md * (2.0 * uz - 1.0);
-                        if (px < 0.0) px += lx; else if (px >= lx) px -= lx;
-                        if (py < 0.0) py += ly; else if (py >= ly) py -= ly;
-                        wall = pz < zlo || pz > zhi;
-                        c = 0.0;
-                    } else if (kind == 1) {
-                        px = lx * ux;
-                        py = ly * uy;
-                        pz = zlo + H * uz;
-                        c = lnzv - lnk[n + 1];
-                    } else {
-                        c = lnk[n] - lnzv;
-                    }
-                    if (uniform(wall)) {
-                        stat += lane == 8;
-                    } else {
-                        const double thr = (c - lnU) * tinv;
-                        const Real qx = (Real)px, qy = (Real)py, qz = (Real)pz;
-                        double de = 0.0;
-                        uint64_t core = 0;
+            // decoded for 32 trials at once, read back by lane (sweep_body): on A lanes x and y,
+            // on B lanes z and ln U; of trial 0 as an insertion the point, of the others 2 u - 1
+            const double f0 = uniform_open((lane & 1) ? R.x : R.z), f1 = uniform_open(R.w);
+            const double lnU = log(uniform53(R.y, R.z));
+            const bool zeroth = t0 == 0 && lane < 2;
+            const double vx = zeroth ? ((lane & 1) ? zlo + H * f0 : lx * f0) : 2.0 * f0 - 1.0;
+            const double vy = zeroth ? ly * f1 : 2.0 * f1 - 1.0;
+            const double tl = zeroth ? lnU : (0.0 - lnU) * tinv;
+            uint64_t accm = 0, wallm = 0, corem = 0;     // bit 2 tt
+            uint32_t cb = 0;
+            auto decide = [&](Real pd, uint64_t core, double thr, uint64_t bit, double &de) {
+                if (!ideal) pd = wave_sum63(pd);
+                if (core != 0) {
+                    corem |= bit;
+                    return false;
+                }
+                de = (double)pd;
+                return (int64_t)__ballot(de <= thr) < 0;
+            };
+            int t2 = 0;
+            if (t0 == 0) {
+                // trial 0: removal when y1 = A0 / 2^32 < 1/2, else insertion
+                t2 = 2;
+                if (exchange) {
+                    const bool ins = bcast(R.x, 0) >= 0x80000000u;
+                    const int kind = ins ? 1 : 2;
+                    stat += lane == 2 * kind;
+                    const double ln_u = bcast(tl, 1);
+                    Real pd = 0;
+                    double de = 0.0;
+                    uint64_t core = 0;
+                    bool near = false;
+                    if (ins ? n >= n_max : n == 0) {
+                        stat += lane == (ins ? 6 : 7);
+                    } else if (ins) {
+                        Real4 v;
+                        v.x = (Real)bcast(vx, 0); v.y = (Real)bcast(vy, 0); v.z = (Real)bcast(vx, 1); v.w = 0;
+                        const double thr = ((lnzv - lnk[n + 1]) - ln_u) * tinv;
                         if (!ideal) {
-                            Real pd;
-                            bool near = false;
-                            if (kind == 0)
-                                pd = lane_delta<true, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, qx, qy, qz,
-                                                                      o.x, o.y, o.z, nullptr, nullptr, core, useful,
-                                                                      near);
-                            else if (kind == 1)
-                                pd = lane_delta<true, false, 1, false>(gas, n, -1, sv, sl, b, gg, gs, lane, 0, qx, qy,
-                                                                       qz, qx, qy, qz, nullptr, nullptr, core, useful, near);
-                            else
-                                pd = lane_delta<false, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, o.x, o.y,
-                                                                       o.z, o.x, o.y, o.z, nullptr, nullptr, core,
-                                                                       useful, near);
-                            pd = wave_sum(pd);
-                            de = (double)pd;
-                            const uint64_t mult = kind == 0 ? 2 : 1;
-                            cand += mult * (uint64_t)((kind == 1 ? n : n - 1) + (near ? slab_scan : 0));
+                            pd = lane_delta<true, false, 1, false>(gas, n, -1, sv, sl, b, gg, gs, lane, 0, v.x, v.y, v.z, v.x,
+                                                                   v.y, v.z, nullptr, nullptr, core, useful, near);
+                            cb += (uint32_t)(n + (near ? slab_scan : 0));
                         }
-                        if (core != 0 && kind != 2) {
-                            stat += lane == 9;
-                        } else if (uniform(de <= thr)) {
-                            accepted = true;
-                            stat += lane == 2 * kind + 1;
+                        if (decide(pd, core, thr, 1, de)) {
+                            accm |= 1;
+                            stat += lane == 3;
                             e += de;
-                            if (kind == 0) {
-                                if (lane == 0) {
-                                    Real4 v; v.x = qx; v.y = qy; v.z = qz; v.w = 0;
-                                    gas[i] = v;
-                                }
-                            } else if (kind == 1) {
-                                if (lane == 0) {
-                                    Real4 v; v.x = qx; v.y = qy; v.z = qz; v.w = 0;
-                                    gas[n] = v;
-                                }
-                                n += 1;
-                            } else {
-                                if (lane == 0 && i != n - 1) gas[i] = gas[n - 1];
-                                i_removed = i;
-                                n -= 1;
-                            }
+                            gas[n] = v;
+                            n += 1;
+                            wave_sync();
+                        }
+                    } else {
+                        const int i = (int)__umulhi(bcast(R.y, 0), (uint32_t)n);
+                        const Real4 o = gas[i], last = gas[n - 1];
+                        const double thr = ((lnk[n] - lnzv) - ln_u) * tinv;
+                        if (!ideal) {
+                            pd = lane_delta<false, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, o.x, o.y, o.z, o.x,
+                                                                   o.y, o.z, nullptr, nullptr, core, useful, near);
+                            cb += (uint32_t)(n - 1 + (near ? slab_scan : 0));
+                        }
+                        if (decide(pd, 0, thr, 1, de)) {
+                            accm |= 1;
+                            stat += lane == 5;
+                            e += de;
+                            gas[i] = last;
+                            i_removed = i;
+                            n -= 1;
+                            wave_sync();
                         }
                     }
+                    stat += lane == 9 && corem != 0;
+                    corem = 0;
                 }
-                if (accepted) {
-                    bits |= 1u << tt;
-                    wave_sync();
-                }
-                if (t == 0 && !use_md) T = 1 + pa.mc_cycles * n;      // N after the exchange attempt
+                if (!use_md) T = 1 + pa.mc_cycles * n;      // N after the exchange attempt
             }
-            if (tracing && lane == 0)
-                a.trace_bits[((size_t)(step - a.trace_sweep0) * a.n_walkers + w) * a.trace_words + (t0 >> 5)] = bits;
+            // the displacements: N does not change among them (with none there is no trial)
+            const int tn = T - t0 < 32 ? T - t0 : 32, moves = tn - (t2 >> 1);
+            for (; t2 < 2 * tn; t2 += 2) {
+                const uint64_t bit = 1ull << t2;
+                const int i = (int)__umulhi(bcast(R.y, t2), (uint32_t)n);
+                const Real4 o = gas[i];
+                const double thr = bcast(tl, t2 + 1);
+                double px = (double)o.x + md * bcast(vx, t2), py = (double)o.y + md * bcast(vy, t2);
+                const double pz = (double)o.z + md * bcast(vx, t2 + 1);
+                const double xl = px + lx, xh = px - lx, yl = py + ly, yh = py - ly;
+                px = px < 0.0 ? xl : (px >= lx ? xh : px);
+                py = py < 0.0 ? yl : (py >= ly ? yh : py);
+                if (uniform(pz < zlo || pz > zhi)) {
+                    wallm |= bit;
+                    continue;
+                }
+                Real4 v;
+                v.x = (Real)px; v.y = (Real)py; v.z = (Real)pz; v.w = 0;
+                Real pd = 0;
+                double de = 0.0;
+                uint64_t core = 0;
+                if (!ideal) {
+                    bool near = false;
+                    pd = lane_delta<true, true, 1, false>(gas, n, i, sv, sl, b, gg, gs, lane, 0, v.x, v.y, v.z, o.x, o.y, o.z,
+                                                          nullptr, nullptr, core, useful, near);
+                    cb += 2u * (uint32_t)(n - 1 + (near ? slab_scan : 0));
+                }
+                if (!decide(pd, core, thr, bit, de)) continue;
+                accm |= bit;
+                e += de;
+                gas[i] = v;
+                wave_sync();
+            }
+            cand += cb;
+            const uint32_t acc = (uint32_t)__popcll(accm & (t0 == 0 ? ~1ull : ~0ull)), wall = (uint32_t)__popcll(wallm);
+            stat += lane == 0 ? (uint32_t)max(moves, 0) : lane == 1 ? acc : lane == 8 ? wall
+                    : lane == 9 ? (uint32_t)__popcll(corem) : 0u;
+            if (tracing) {
+                const uint32_t bits = (uint32_t)__ballot(lane < 32 && ((accm >> (2 * (lane & 31))) & 1));
+                if (lane == 0)
+                    a.trace_bits[((size_t)(step - a.trace_sweep0) * a.n_walkers + w) * a.trace_words + (t0 >> 5)] = bits;
+            }
         }
+        e = bcast(e, kWave - 1);         // (the sums of the trials are complete in the last lane)
         if (use_md) {
             // the inserted particle's velocity (Philox block (0, step, walker, 3)); the
             // removed slot takes the last particle's; then the MD run
