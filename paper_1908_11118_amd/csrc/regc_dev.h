@@ -266,6 +266,15 @@ hipError_t launch_balance(const ClassDev *cls, int n_class, const int32_t *n, in
 hipError_t launch_observables(const ObsArgs &a, hipStream_t s);
 hipError_t launch_minima(const MinArgs &a, hipStream_t s);
 hipError_t launch_clock_advance(int64_t *clock, int n, hipStream_t s);
+
+// Device arrays (sizes in 4-byte words) that one launch puts one after the other.
+struct PackArgs {
+    static constexpr int kMax = 5;
+    const uint32_t *src[kMax];
+    uint32_t end[kMax];          // the words up to and with piece k
+    int n;
+};
+hipError_t launch_pack(const PackArgs &a, uint32_t *dst, hipStream_t s);
 hipError_t launch_clock_set(int64_t *clock, int64_t value, hipStream_t s);
 hipError_t launch_energy_f64(const EnergyArgs &a, hipStream_t s);
 hipError_t launch_energy_f32(const EnergyArgs &a, hipStream_t s);

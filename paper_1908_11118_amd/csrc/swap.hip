@@ -27,6 +27,30 @@ __global__ void clock_advance(int64_t *clock, int n)
     if (threadIdx.x == 0 && blockIdx.x == 0) clock[0] += n;
 }
 
+// Small results for the host: what a context's getters return is several arrays of a few
+// kilobytes, and a blocking copy of each costs about 12 us whatever its size.  One launch
+// puts them into pinned host memory instead.
+__global__ void __launch_bounds__(256) pack_kernel(PackArgs a, uint32_t *dst)
+{
+    const uint32_t words = a.end[a.n - 1];
+    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < words; k += gridDim.x * blockDim.x) {
+        uint32_t begin = 0, v = 0;
+#pragma unroll
+        for (int q = 0; q < PackArgs::kMax; ++q) {
+            if (q < a.n && k >= begin && k < a.end[q]) v = a.src[q][k - begin];
+            begin = q < a.n ? a.end[q] : begin;
+        }
+        dst[k] = v;
+    }
+}
+
+hipError_t launch_pack(const PackArgs &a, uint32_t *dst, hipStream_t s)
+{
+    const unsigned blocks = (a.end[a.n - 1] + 255) / 256;
+    hipLaunchKernelGGL(pack_kernel, dim3(blocks < 256 ? blocks : 256), dim3(256), 0, s, a, dst);
+    return hipGetLastError();
+}
+
 hipError_t launch_clock_advance(int64_t *clock, int n, hipStream_t s)
 {
     hipLaunchKernelGGL(clock_advance, dim3(1), dim3(64), 0, s, clock, n);
