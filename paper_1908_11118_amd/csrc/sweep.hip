@@ -502,11 +502,18 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
     }
 }
 
-template <int SPLIT, bool CULL, int MODE = kSlabAny>
+template <int SPLIT, bool CULL>
 __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock, SPLIT != 2 ? kSweepWavesPerSimd : 1)
     sweep_kernel(SweepArgs a)
 {
-    sweep_body<SPLIT, CULL, false, MODE>(a);
+    sweep_body<SPLIT, CULL, false>(a);
+}
+
+template <int SPLIT, int MODE>
+__global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock, SPLIT != 2 ? kSweepWavesPerSimd : 1)
+    sweep_mode_kernel(SweepArgs a)
+{
+    sweep_body<SPLIT, false, false, MODE>(a);
 }
 
 template <int SPLIT>
@@ -1776,13 +1783,13 @@ hipError_t SWEEP_LAUNCH(const SweepArgs &a, int n_blocks, int waves_per_block, i
         else hipLaunchKernelGGL((sweep_kernel<4, false>), grid, block, smem, s, a);
     } else if (split == 2) {
         if (cull) hipLaunchKernelGGL((sweep_kernel<2, true>), grid, block, smem, s, a);
-        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_kernel<2, false, kSlabHalo>), grid, block, smem, s, a);
-        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_kernel<2, false, kSlabAll>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_mode_kernel<2, kSlabHalo>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_mode_kernel<2, kSlabAll>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((sweep_kernel<2, false>), grid, block, smem, s, a);
     } else {
         if (cull) hipLaunchKernelGGL((sweep_kernel<1, true>), grid, block, smem, s, a);
-        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_kernel<1, false, kSlabHalo>), grid, block, smem, s, a);
-        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_kernel<1, false, kSlabAll>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabHalo) hipLaunchKernelGGL((sweep_mode_kernel<1, kSlabHalo>), grid, block, smem, s, a);
+        else if (a.slab_mode == kSlabAll) hipLaunchKernelGGL((sweep_mode_kernel<1, kSlabAll>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((sweep_kernel<1, false>), grid, block, smem, s, a);
     }
     return hipGetLastError();
