@@ -154,14 +154,16 @@ __device__ __forceinline__ int block_argmax(T key, int idx, T *rkey, int *ridx)
 __device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-__device__ __forceinline__ bf16x4 lo4(const uint4 &q)
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ bf16x4 lo4(const u32x4 &q)
 {
     bf16x4 r;
     r[0] = (short)(q.x & 0xFFFFu); r[1] = (short)(q.x >> 16); r[2] = (short)(q.y & 0xFFFFu); r[3] = (short)(q.y >> 16);
     return r;
 }
 
-__device__ __forceinline__ bf16x4 hi4(const uint4 &q)
+__device__ __forceinline__ bf16x4 hi4(const u32x4 &q)
 {
     bf16x4 r;
     r[0] = (short)(q.z & 0xFFFFu); r[1] = (short)(q.z >> 16); r[2] = (short)(q.w & 0xFFFFu); r[3] = (short)(q.w >> 16);
@@ -182,26 +184,26 @@ __device__ __forceinline__ bf16x4 afrag(const bf16 *h, int kk, int lane)
 __device__ __forceinline__ void hidden_mfma(const uint16_t *wp, const float *bias, const bf16 *in, bf16 *out, int wave,
                                             int lane)
 {
+    u32x4 w[2][4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int kp = 0; kp < 4; ++kp)
+            w[q][kp] = reinterpret_cast<const u32x4 *>(wp)[((2 * wave + q) * 4 + kp) * kWave + lane];
     bf16x4 a[8];
 #pragma unroll
     for (int kk = 0; kk < 8; ++kk) a[kk] = afrag(in, kk, lane);
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int tile = 2 * wave + q;
-        const uint4 *bp = reinterpret_cast<const uint4 *>(wp) + (size_t)tile * 4 * kWave + lane;
-        uint4 bq[4];
+    for (int kp = 0; kp < 4; ++kp) {
 #pragma unroll
-        for (int kp = 0; kp < 4; ++kp) bq[kp] = bp[kp * kWave];
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < 2; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp], lo4(w[q][kp]), acc[q], 0, 0, 0);
 #pragma unroll
-        for (int kp = 0; kp < 4; ++kp) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp], lo4(bq[kp]), acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp + 1], hi4(bq[kp]), acc, 0, 0, 0);
-        }
-        if (lane < 16) {
-            const int n = 16 * tile + lane;
-            out[n] = f2bf(act(acc[0] + bias[n]));
-        }
+        for (int q = 0; q < 2; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp + 1], hi4(w[q][kp]), acc[q], 0, 0, 0);
+    }
+    if (lane < 32) {                    // (every row of a product is the same)
+        const int n = 32 * wave + lane;
+        out[n] = f2bf(act((lane & 16 ? acc[1][0] : acc[0][0]) + bias[n]));
     }
 }
 
@@ -266,11 +268,11 @@ __device__ __forceinline__ double block_scan(double v, double *red, int wave, in
 // (thread t owns voxels t + 256 j, summed over j in order).  The voxel draw realises
 // exactly these weights, and the acceptance uses ln P(v) = ln w_v - ln sum, so the
 // proposal density in the acceptance is the one the draw follows up to FP64 rounding.
-__device__ __forceinline__ double weight_total(const NetLds &S, float mx, int tid, int wave, int lane)
+__device__ __forceinline__ double weight_total(const NetLds &S, const float (&x)[kNetNV / kLT], float mx, int wave, int lane)
 {
     double v = 0.0;
 #pragma unroll
-    for (int j = 0; j < kNetNV / kLT; ++j) v += (double)expf(S.logit[tid + kLT * j] - mx);
+    for (int j = 0; j < kNetNV / kLT; ++j) v += (double)expf(x[j] - mx);
     double lo, hi;
     return block_scan(v, S.redd, wave, lane, lo, hi);
 }
@@ -284,6 +286,11 @@ __device__ __forceinline__ double log_prob(const NetLds &S, double lse, int v)
 
 // The network's logits for the occupancy without one particle in voxel `ex`
 // (-1: none) into S.logit; returns the log-normaliser.  Block-wide.
+//
+// FP32 build: what bounds a pass is the output layer's 1 MB of weights through one compute unit
+// (16 to 18 thousand of its 30 thousand cycles, 58 bytes a cycle).  A tile's eight products are a
+// chain, so four tiles' chains run side by side (64 walkers, N <= 40, ten sweeps: 3.6 -> 3.3 ms;
+// the first tiles loaded behind layer 1's rows only delay those: 3.4).
 __device__ double net_forward(const NetDev &net, const NetLds &S, int ex, int tid, int wave, int lane)
 {
     // ascending list of occupied voxels, entries voxel | count << 16
@@ -343,19 +350,19 @@ __device__ double net_forward(const NetDev &net, const NetLds &S, int ex, int ti
             S.h1[tid] = f2bf(act(s));
         }
     } else {
-        // wave w takes entries w, w+4, ...; the four partial sums meet in LDS
+        // wave w takes entries w, w+4, ..., 16 at a time; the four partial sums meet in LDS
         float a0 = 0.f, a1 = 0.f;
         const uint32_t *w1 = reinterpret_cast<const uint32_t *>(net.w1);
-        for (int j0 = wave; j0 < m; j0 += 8 * kLearnWaves) {
-            uint32_t e[8], wv[8];
+        for (int c0 = 0; c0 < m; c0 += 16 * kLearnWaves) {
+            uint32_t e[16], wv[16];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = j0 + u * kLearnWaves;
+            for (int u = 0; u < 16; ++u) {
+                const int j = c0 + wave + u * kLearnWaves;
                 e[u] = j < m ? S.list[j] : 0u;
                 wv[u] = w1[(size_t)(e[u] & 0xFFFFu) * (kNetH / 2) + lane];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 16; ++u) {
                 const float k = (float)(e[u] >> 16);     // 0 for the padding entries
                 a0 += k * lo_bf(wv[u]);
                 a1 += k * hi_bf(wv[u]);
@@ -427,29 +434,33 @@ __device__ double net_forward(const NetDev &net, const NetLds &S, int ex, int ti
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) a[kk] = afrag(S.h3, kk, lane);
         constexpr int TS = 4;
-        const uint4 *wp = reinterpret_cast<const uint4 *>(net.w4) + (size_t)(64 * wave) * 4 * kWave + lane;
-        auto load = [&](uint4 (&b)[TS][4], int t) {
+        const u32x4 *wp = reinterpret_cast<const u32x4 *>(net.w4) + (size_t)(64 * wave) * 4 * kWave + lane;
+        auto load = [&](u32x4 (&b)[TS][4], int t) {
 #pragma unroll
             for (int u = 0; u < TS; ++u)
 #pragma unroll
                 for (int kp = 0; kp < 4; ++kp) b[u][kp] = wp[((size_t)(t + u) * 4 + kp) * kWave];
         };
-        auto compute = [&](const uint4 (&b)[TS][4], int t) {
+        // four tiles' chains of dependent products side by side; every row of a product is the
+        // same, so that lane l takes column l of the four tiles' 64
+        auto compute = [&](const u32x4 (&b)[TS][4], int t) {
+            f32x4 acc[TS];
 #pragma unroll
-            for (int u = 0; u < TS; ++u) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int u = 0; u < TS; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int kp = 0; kp < 4; ++kp) {
-                    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp], lo4(b[u][kp]), acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp + 1], hi4(b[u][kp]), acc, 0, 0, 0);
-                }
-                if (lane < 16) {
-                    const int v = 16 * (64 * wave + t + u) + lane;
-                    S.logit[v] = acc[0] + S.b4[v];
-                }
+            for (int kp = 0; kp < 4; ++kp) {
+#pragma unroll
+                for (int u = 0; u < TS; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp], lo4(b[u][kp]), acc[u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < TS; ++u)
+                    acc[u] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[2 * kp + 1], hi4(b[u][kp]), acc[u], 0, 0, 0);
             }
+            const int v = 16 * (64 * wave + t) + lane;
+            const float lo = lane & 16 ? acc[1][0] : acc[0][0], hi = lane & 16 ? acc[3][0] : acc[2][0];
+            S.logit[v] = (lane & 32 ? hi : lo) + S.b4[v];
         };
-        uint4 bA[TS][4], bB[TS][4];
+        u32x4 bA[TS][4], bB[TS][4];
         load(bA, 0);
         for (int t = 0; t < 64; t += 2 * TS) {
             load(bB, t + TS);
@@ -458,11 +469,13 @@ __device__ double net_forward(const NetDev &net, const NetLds &S, int ex, int ti
             compute(bB, t + TS);
         }
         __syncthreads();
-        float mx = -INFINITY;
+        float x[kNetNV / kLT], mx = -INFINITY;
 #pragma unroll
-        for (int q = 0; q < kNetNV / kLT; ++q) mx = fmaxf(mx, S.logit[tid + kLT * q]);
+        for (int q = 0; q < kNetNV / kLT; ++q) x[q] = S.logit[tid + kLT * q];
+#pragma unroll
+        for (int q = 0; q < kNetNV / kLT; ++q) mx = fmaxf(mx, x[q]);
         mx = block_max(mx, S.redf);
-        const double lsum = log(weight_total(S, mx, tid, wave, lane));
+        const double lsum = log(weight_total(S, x, mx, wave, lane));
         if (tid == 0) {
             S.norm[0] = lsum;
             S.mxf[0] = mx;
