@@ -845,8 +845,11 @@ __global__ void rep_sd(int B, int K, const double *rep, double *sd)
 // X_l = exp(-(beta_l - c)(E - E0)) and their sum with the weights a_l = exp(bracket) stay
 // in range without a maximum per sample, and
 //     sum_{n at N} e^{-beta_l E_n} / D_n = e^{-beta_l E0 - shift} Q_l(N),  Q_l(N) = sum_n X_l / sum_k a_k X_k,
-// is what the new free energies need.  Samples outside that range take mbar_chunk.
-constexpr double kMaxExponent = 300.0;
+// is what the new free energies need.  The solve goes on to kMaxSolveExponent: there a
+// Q_l may overflow, and a solve that does not converge is left to the general iteration.
+// What weights samples by more than that (targets, observables, replicates) stays below kMaxExponent.
+// Samples outside take mbar_chunk.
+constexpr double kMaxExponent = 300.0, kMaxSolveExponent = 350.0;
 
 // exp(x) for |x| <= 708: x = k ln 2 + r (Cody and Waite's reduction, the product fused),
 // the Taylor series of exp(r) to r^13 / 13! (|r| <= 0.35: below 5e-18 relative), 2^k by
@@ -956,10 +959,13 @@ struct SolveState {
     int done, conv, it, plain_left;  // conv: 1 converged, 2 below tol_switch
     int hist, head;                  // differences' history: entries, slot of the oldest
     int gauge, memory;               // first sampled state; at most this many differences
+    int polish;                      // iterations since the residual first came below tol
     double delta, d_prev;
 };
 
 constexpr int kMaxMemory = 8;        // differences the device's least squares holds
+constexpr int kPolish = 12;          // iterations past the tolerance at most (preconditioned: 2)
+constexpr double kFloor = 2e-14;     // a residual that is rounding
 constexpr int kMaxStepStates = 4096; // states it holds (4 per thread of 1024)
 
 struct SolveArgs {
@@ -974,6 +980,7 @@ struct SolveArgs {
     double *shift;                             // [B][nN]
     double *partial;                           // [B][L][rows]
     SolveState *st;                            // [B]
+    int polish;                                // iterations past the tolerance at most
     int method, max_iter;
     double tol, tol_switch;                    // tol_switch > 0: stop below it too (conv = 2)
     const double *y;                           // [B][S] preconditioned residuals, or null
@@ -1196,13 +1203,24 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
         const int slots = st.memory + 1;
         const bool finite = d <= 1e300;
         const bool sw = finite && d < p.tol_switch;
-        if (p.method == 0 || (!finite && it == 1) || (finite && d < p.tol) || sw) {
+        // A residual below tol leaves an error of up to tol |(I - J)^-1|: the iteration goes on
+        // towards the residual's rounding, a few times at most (the preconditioned one, whose
+        // steps are that error, while the residual still halves), and ends with the better of
+        // the last two.
+        int polish = st.polish;
+        const bool under = p.method == 1 && !sw && finite && d < p.tol;
+        const bool last = (polish > 0 && (d < kFloor || polish >= p.polish || (y && !(d < 0.5 * d_prev)))) ||
+                          (under && p.polish == 0);
+        if (polish > 0 || under) ++polish;
+        if (p.method == 0 || (!finite && it == 1) || last || sw) {
             // plain step, or the end: f is the map's value
+            const bool older = last && !(d <= d_prev);
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                if (tid + T * k < p.S) f[tid + T * k] = g[k];
+                if (tid + T * k < p.S) f[tid + T * k] = older ? good[tid + T * k] : g[k];
+            if (older) d = d_prev;
             const bool check = p.method == 1 || it % 10 == 0 || it == p.max_iter;
-            conv = check && finite && d < p.tol ? 1 : (sw ? 2 : 0);
+            conv = check && (last || (finite && d < p.tol)) ? 1 : (sw ? 2 : 0);
             done = check && (conv || !finite);
         } else if (!finite) {
             // back to the last finite map value, plain steps for a while
@@ -1217,7 +1235,7 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
             // the preconditioned map: x + y with y = (I - J)^-1 (g - x).  Near the end the
             // residual is the rounding of g, which (I - J)^-1 amplifies and the plain map
             // does not: where it stops falling, a few plain steps
-            if (y && plain_left == 0 && d < 1e-9 && d > 0.1 * d_prev) {
+            if (y && plain_left == 0 && polish == 0 && d < 1e-9 && d > 0.1 * d_prev) {
                 hist = 0;
                 plain_left = 4;
             }
@@ -1325,11 +1343,14 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
             }
             if (plain_left > 0) --plain_left;
         }
-        if (it >= p.max_iter) done = 1;
+        if (it >= p.max_iter && !done) {
+            done = 1;
+            conv = polish > 0;
+        }
         __syncthreads();              // every thread has read the state
         if (tid == 0) {
             st.done = done; st.conv = conv; st.it = it; st.plain_left = plain_left;
-            st.hist = hist; st.head = head;
+            st.hist = hist; st.head = head; st.polish = polish;
             st.delta = d; st.d_prev = d_prev;
         }
     }
@@ -2243,7 +2264,8 @@ struct regc_mbar {
     // the device-resident iteration
     double beta_c = 0.0, beta_half = 0.0; // middle and half width of the inverse temperatures
     DevBuf<double> mid_d, half_d;         // middle and half width of the energies sampled at each N
-    bool bounded = false;                 // the exponents around them stay below kMaxExponent
+    bool bounded = false;                 // the exponents around them stay below kMaxSolveExponent
+    bool tight = false;                   // and below kMaxExponent
     double half_max = 0.0;                // the largest half width
     DevBuf<double> hinv_d;                // 1 / sum of every sample at the solution
     bool hinv_valid = false;              // hinv_d and shift_d are those of the solution in f_d
@@ -2442,10 +2464,11 @@ extern "C" int regc_mbar_set_samples(regc_mbar *mb, int64_t ns, const double *e,
     std::vector<double> half(mb->nN);
     REGC_HIP(hipMemcpyAsync(half.data(), mb->half_d.p, sizeof(double) * mb->nN, hipMemcpyDeviceToHost, s));
     REGC_HIP(hipStreamSynchronize(s));
-    mb->bounded = true;
+    mb->bounded = mb->tight = true;
     mb->half_max = 0.0;
     for (double h : half) {
-        mb->bounded = mb->bounded && mb->beta_half * h <= kMaxExponent;    // (false on a NaN)
+        mb->bounded = mb->bounded && mb->beta_half * h <= kMaxSolveExponent;    // (false on a NaN)
+        mb->tight = mb->tight && mb->beta_half * h <= kMaxExponent;
         mb->half_max = std::max(mb->half_max, h);
     }
     // blocks per chunk: a few per compute unit (each carries the weights of its N, about as
@@ -2527,6 +2550,7 @@ static SolveArgs solve_args(regc_mbar *mb)
     p.shift = mb->shift_d.p; p.partial = mb->q_d.p; p.st = mb->state_d.p; p.hinv = mb->hinv_d.p;
     p.arrived = mb->arrived_d.p; p.host = mb->progress;
     p.method = mb->method;
+    p.polish = kPolish;
     return p;
 }
 
@@ -2725,6 +2749,7 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int n_sampled, bool *
     if ((rc = start_solve(mb, nullptr, st)) || (rc = factorise(mb, p))) return rc;
     p.tol_switch = 0.0;
     p.max_iter = kPreIter;
+    p.polish = 2;
     p.y = mb->y_d.p;
     if ((rc = run_iterations(mb, 1, kPreIter, [&]() {
              hipError_t e = launch_map(mb, p);
@@ -2869,7 +2894,12 @@ extern "C" int regc_mbar_set_solver(regc_mbar *mb, int method, int memory)
 static int solve_core(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta)
 {
     mb->inverse_valid = mb->hinv_valid = false;
-    if (device_solve(mb)) return solve_on_device(mb, tol, max_iter, start, iters, delta);
+    if (device_solve(mb)) {
+        const int rc = solve_on_device(mb, tol, max_iter, start, iters, delta);
+        if (mb->tight || rc != REGC_ENOCONV) return rc;
+        // (sums of exponents past kMaxExponent may have overflowed)
+        mb->inverse_valid = mb->hinv_valid = false;
+    }
     hipStream_t s = mb->stream;
     if (start) REGC_HIP(hipMemcpyAsync(mb->f_d.p, start, sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
     else REGC_HIP(hipMemsetAsync(mb->f_d.p, 0, sizeof(double) * mb->S, s));
@@ -3001,7 +3031,7 @@ static bool bounded_targets(const regc_mbar *mb, const double *tb, int nT)
 {
     double far = 0.0;
     for (int t = 0; t < nT; ++t) far = std::max(far, std::fabs(tb[t] - mb->beta_c));
-    return mb->bounded && far * mb->half_max <= kMaxExponent;
+    return mb->tight && far * mb->half_max <= kMaxExponent;
 }
 
 // The chunks' sums and the averages at the targets on the handle's stream: on bounded
@@ -3243,6 +3273,7 @@ static int bootstrap_batch(regc_mbar *mb, const TargetDev &T, double tol, int64_
     g.Bp = Bp;
     SolveArgs &p = g.p;
     p = solve_args(mb);
+    p.polish = 0;                 // (a replicate's spread is what is asked for)
     // blocks of a pass are a part of a chunk and a group of columns
     p.sub = (int)std::min<int64_t>(kChunk / 256, std::max<int64_t>(1, (512 + mb->nchunks - 1) / mb->nchunks));
     p.rows = p.nchunks * p.sub;

@@ -178,3 +178,16 @@ def test_averages_at_targets_and_observables(n_tgt, n_mu, n_obs, t0):
     assert np.allclose(np.asarray(mean).reshape(len(tb), n_obs), mean_ref, rtol=1e-8)
     seen = ref["p_n"][::n_mu] > 0                  # (the oracle leaves the others at 0)
     assert np.allclose(np.asarray(cond).reshape(n_tgt, n_max + 1, n_obs)[seen], cond_ref[::n_mu][seen], rtol=1e-8)
+
+
+@pytest.mark.parametrize("shift", [50.0, 58.0, 63.0])
+def test_energies_at_the_edge_of_the_bounded_range(shift):
+    """Exponents of about 280, 315 and 340: below the targets' limit of 300, between it and
+    the solve's of 350, and just inside the latter."""
+    t, mu = W.linear_grid(0.05, 2.0, 5), W.linear_grid(-2.6, -2.4, 3)
+    rng = np.random.default_rng(9)
+    n = rng.integers(0, 6, 1500).astype(np.int32)
+    s = rng.integers(0, 15, 1500).astype(np.int32)
+    e = rng.normal(0.0, 1.0, 1500)
+    e[:40] += shift
+    check_solution(t, mu, 5, e, n, s, tol=1e-9, max_iter=20000)
