@@ -1296,57 +1296,41 @@ __device__ __forceinline__ double md_min_image(double d, double box)
     return d > 0.5 * box ? d - box : (d < -0.5 * box ? d + box : d);
 }
 
-// Forces on the walker's particles and the potential energy (FP64, wave-uniform).  Truncated-
-// shifted LJ; the shift does not act on forces.  The loop over a particle's partners is
-// the step's time, so it is as short as 64 lanes allow: with at most 32 (16, 8, ...) particles
-// two (four, eight, ...) lanes share a particle's partners, and of a slab in columns only
-// the particle's block of nine is read (ten MD steps a REGC step: 66 walkers with N <= 44 on a
-// layer of 100 atoms, 13 steps 4.4 -> 3.0 ms; 14 with N <= 37 on 75 atoms, 39 steps 10.4 -> 9.4).
+// Forces on the walker's particles (lane-strided over particles; each particle sums
+// its gas partners in index order, then every packed slab entry) and the potential
+// energy (FP64, wave-uniform).  Truncated-shifted LJ; the shift does not act on forces.
+// A trajectory amplifies the last bit of a force, so the order of a particle's sum is kept;
+// partners outside the cutoff add 0 instead of being branched around, so that the long
+// chains of several partners' quotients overlap, and a particle above the slab's reach skips it.
 __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const PotDev &pot, const Box &b, double *f,
                             int lane)
 {
     double e = 0.0;
     if (!pot.ideal) {
         const double lx = (double)b.lx, ly = (double)b.ly;
-        int shares = 1;                              // lanes per particle
-        while (2 * shares * n <= kWave) shares *= 2;
-        const int width = kWave / shares, g = lane / width;
-        for (int i0 = 0; i0 < n; i0 += width) {
-            const int i = i0 + lane % width;
-            double fx = 0.0, fy = 0.0, fz = 0.0;
-            if (i < n) {
-                const double xi = (double)gas[i].x, yi = (double)gas[i].y, zi = (double)gas[i].z;
-                // (selects, not branches: several partners' chains of dependent operations overlap)
-                auto partner = [&](const Real4 &p, bool in, double sig2, double eps4, double shift, double part) {
-                    const double dx = md_min_image(xi - (double)p.x, lx);
-                    const double dy = md_min_image(yi - (double)p.y, ly);
-                    const double dz = zi - (double)p.z;
-                    const double r2 = dx * dx + dy * dy + dz * dz;
-                    in = in && r2 < pot.rc2;
-                    const double inv = 1.0 / r2, s2 = sig2 * inv, s6 = s2 * s2 * s2;
-                    const double h = in ? 6.0 * eps4 * (2.0 * s6 * s6 - s6) * inv : 0.0;
-                    fx += h * dx; fy += h * dy; fz += h * dz;
-                    e += in ? part * (eps4 * (s6 * s6 - s6) - shift) : 0.0;
-                };
+        const int ns = sv.mode != kSlabAll ? sv.ncx * sv.ncy * sv.cap : sv.len;    // (no halo with MD)
+        for (int i = lane; i < n; i += kWave) {
+            const double xi = (double)gas[i].x, yi = (double)gas[i].y, zi = (double)gas[i].z;
+            double fx = 0.0, fy = 0.0, fz = 0.0, ei = 0.0;
+            auto partner = [&](const Real4 &p, bool in, double sig2, double eps4, double shift, double part) {
+                const double dx = md_min_image(xi - (double)p.x, lx);
+                const double dy = md_min_image(yi - (double)p.y, ly);
+                const double dz = zi - (double)p.z;
+                const double r2 = dx * dx + dy * dy + dz * dz;
+                in = in && r2 < pot.rc2;
+                const double s2 = sig2 / r2, s6 = s2 * s2 * s2;
+                const double g = 6.0 * eps4 * (2.0 * s6 * s6 - s6) / r2;
+                const double h = in ? g : 0.0, u = in ? part * (eps4 * (s6 * s6 - s6) - shift) : 0.0;
+                fx += h * dx; fy += h * dy; fz += h * dz;
+                ei += u;
+            };
 #pragma unroll 4
-                for (int j = g; j < n; j += shares) partner(gas[j], j != i, pot.sig2_gg, pot.eps4_gg, pot.shift_gg, 0.5);
-                if (zi < (double)sv.top_plus_rc) {
-                    int cx = 0, cy = 0;
-                    if (sv.mode != kSlabAll) column_of(sv, gas[i].x, gas[i].y, cx, cy);
+            for (int j = 0; j < n; ++j) partner(gas[j], j != i, pot.sig2_gg, pot.eps4_gg, pot.shift_gg, 0.5);
+            if (zi < (double)sv.top_plus_rc)
 #pragma unroll 4
-                    for (int k = g; k < sv.len; k += shares)
-                        partner(sv.atoms[sv.mode != kSlabAll ? block_entry(sv, cx, cy, k) : k], true, pot.sig2_gs, pot.eps4_gs,
-                                pot.shift_gs, 1.0);
-                }
-            }
-            for (int o = width; o < kWave; o *= 2) {
-                fx += __shfl_xor(fx, o);
-                fy += __shfl_xor(fy, o);
-                fz += __shfl_xor(fz, o);
-            }
-            if (i < n && g == 0) {
-                f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;
-            }
+                for (int k = 0; k < ns; ++k) partner(sv.atoms[k], true, pot.sig2_gs, pot.eps4_gs, pot.shift_gs, 1.0);
+            f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;
+            e += ei;
         }
     } else {
         for (int i = lane; i < n; i += kWave) f[3 * i] = f[3 * i + 1] = f[3 * i + 2] = 0.0;
