@@ -85,7 +85,7 @@ typedef struct {
 } regc_potential;
 
 /* Surface and gas region.  slab_xyz: n_slab x 3 doubles (x, y, z), copied at
- * create.  Gas region [0,lx) x [0,ly) x [z_lo, z_hi], periodic in x and y,
+ * create; x and y may lie in any periodic image of the cell.  Gas region [0,lx) x [0,ly) x [z_lo, z_hi], periodic in x and y,
  * hard walls in z (Sec. III.A: insertion zone above the topmost surface atoms).
  * lx and ly must be at least 2*rcut (minimum image).  n_max caps N. */
 typedef struct {

@@ -225,6 +225,16 @@ static int validate(const regc_potential *pot, const regc_system *sys, const reg
     return REGC_OK;
 }
 
+// A slab coordinate for the pair terms.  They take the nearest periodic image of a distance
+// of up to one and a half cells (min(d, L - d)), so up to half a cell outside the cell a
+// coordinate stays as it was given, and one farther out is moved into the cell.
+static double in_reach(double x, double box)
+{
+    if (x >= -0.5 * box && x <= 1.5 * box) return x;
+    const double r = std::fmod(x, box);
+    return r < 0.0 ? r + box : r;
+}
+
 static void pack_slab(ClassHost &c, const regc_potential *pot, const regc_opts *o)
 {
     const int ns = c.sys.n_slab;
@@ -540,6 +550,10 @@ static int create_common(int n_class, const regc_potential *pot, const regc_syst
         ClassHost h;
         h.sys = sys[k];
         h.slab.assign(sys[k].slab_xyz, sys[k].slab_xyz + 3 * (size_t)sys[k].n_slab);
+        for (int a = 0; a < sys[k].n_slab; ++a) {
+            h.slab[3 * a] = in_reach(h.slab[3 * a], sys[k].lx);
+            h.slab[3 * a + 1] = in_reach(h.slab[3 * a + 1], sys[k].ly);
+        }
         h.sys.slab_xyz = nullptr;
         h.t.assign(grid[k].t, grid[k].t + grid[k].n_t);
         h.mu.assign(grid[k].mu, grid[k].mu + grid[k].n_mu);

@@ -33,7 +33,8 @@ struct Box {
     Real lx, ly;
 };
 
-// |d| of the nearest periodic image of d (|d| <= L): min(|d|, L - |d|).  Only its square
+// |d| of the nearest periodic image of d, up to its sign: min(|d|, L - |d|), for |d| <= 1.5 L
+// (gas particles lie in the cell, slab atoms at most half a cell outside).  Only its square
 // is used, so the sign is left out: three operations instead of four with a rounded
 // quotient (FP32) and of eight with two compares (FP64, the same value bit for bit).
 __device__ __forceinline__ Real min_image_abs(Real d, Real L)
