@@ -1,0 +1,58 @@
+"""What regc_mbar_solve promises: converged means max |delta f| < tol, whatever iteration the
+limit falls on and however the residual moves about near its rounding."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_11118_amd import regc
+from paper_1908_11118_amd import workloads as W
+from test_gpu_mbar_solve import fluid_samples
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    oracle.build(force=False)
+    torch.cuda.set_device(0)
+
+
+def _loaded(t, mu, n_max, per_state, seed, spread=1.0):
+    e, n, s = fluid_samples(t, mu, n_max, per_state, seed=seed, spread=spread)
+    mb = regc.Mbar(t, mu, n_max)
+    mb.set_samples(e, n, s)
+    return mb, e, n, s
+
+
+# grids of more than 32 temperatures and limits below 64 take the plain iteration, the others
+# the preconditioned one; the residual rises past tol again in the first and last three
+# (tolerances near its rounding, and loose ones)
+@pytest.mark.parametrize("n_t,n_mu,n_max,per_state,spread,cold,seed,tols,limits", [
+    (3, 5, 77, 52, 2.0, False, 11, (3.15e-14, 4.97e-14, 7.84e-14), (63, 400)),
+    (33, 3, 50, 50, 1.0, True, 0, (2e-14, 1e-10, 1e-4), range(100, 160, 3)),
+    (6, 6, 38, 36, 0.5, False, 1, (1e-12, 1e-7, 1e-2), range(1, 80, 4)),
+    (40, 4, 65, 66, 0.5, True, 82, (1e-1,), range(44, 58)),
+    (40, 4, 82, 32, 1.0, True, 18, (3.15e-14, 7.84e-14), (400,)),
+    (3, 5, 87, 30, 1.0, False, 411, (1e-1, 1e-2, 1e-5), (400,))])
+def test_converged_means_below_the_tolerance(n_t, n_mu, n_max, per_state, spread, cold, seed, tols, limits):
+    t = W.linear_grid(0.6, 1.4, n_t) if cold else W.linear_grid(0.8, 1.8, n_t)
+    mu = W.linear_grid(-6.0, -2.0, n_mu) if cold else W.linear_grid(-5.0, -2.5, n_mu)
+    mb, e, n, s = _loaded(t, mu, n_max, per_state, seed, spread)
+    beta, lnz = oracle.state_arrays(W.ideal_gas().replace(t=t, mu=mu, n_max=n_max))
+    omega = np.bincount(s, minlength=len(beta))
+    seen = 0
+    for tol in tols:
+        for limit in limits:
+            f, conv, it, d = mb.solve(tol=tol, max_iter=limit, allow_noconv=True)
+            if conv:
+                seen += 1
+                assert d < tol, (tol, limit, it, d)
+                # (f is a map value; a further step of the map moves it no farther than a few
+                # times the step before, to the rounding of f)
+                g, _ = oracle.mbar_iterate(beta, lnz, omega, e, n, f)
+                assert np.max(np.abs(g - g[0] - f)) < 10 * d + 1e-11, (tol, limit, it, d)
+    mb.close()
+    assert seen
