@@ -362,14 +362,18 @@ int regc_mbar_load_run(regc_mbar *mb, regc_ctx *ctx, int cls, int64_t skip_recor
  * Anderson acceleration with `memory` past iterates (1..32, default 8).  Method 1
  * begins at an estimate from the states' mean E and N and preconditions the iteration
  * with the map's Jacobian, taken once near the solution, on grids of at most 1024 states
- * and 32 temperatures whose samples determine the solution; elsewhere, and in method 0,
- * it begins at f = 0 and iterates the map itself. */
+ * and 32 temperatures whose samples determine the solution.  That attempt needs max_iter
+ * >= 64 and is given up where it is not near after 60 iterations, does not settle in 60
+ * more, or would exceed max_iter.  Then, elsewhere, and in method 0, the solve begins at
+ * f = 0 and iterates the map itself, with all of max_iter. */
 int regc_mbar_set_solver(regc_mbar *mb, int method, int memory);
 
 /* Solves the self-consistent equations (Eq. (9)) for the free energies f_s =
  * -ln c_s of the sampled states, gauge f = 0 at the first sampled state, until
  * max |delta f| < tol or max_iter iterations.  f_out[S] (unsampled states get
- * their reweighted value).  iters/delta may be NULL.  ENOCONV if not converged. */
+ * their reweighted value).  iters (those that led to the result, at most max_iter) and
+ * delta (of the result: below tol when converged) may be NULL.  ENOCONV if not
+ * converged. */
 int regc_mbar_solve(regc_mbar *mb, double tol, int max_iter, double *f_out, int *iters,
                     double *delta);
 
@@ -450,7 +454,7 @@ int regc_batch_means(int64_t ns, const int32_t *state, const int32_t *n, int n_s
                      int on_device, double *mean, double *se, void *stream);
 
 /* Timing of the last solve: milliseconds in the iteration kernels and their
- * iteration count. */
+ * iteration count, those of an attempt given up (regc_mbar_set_solver) included. */
 int regc_mbar_timing(regc_mbar *mb, double *ms_iter_total, int64_t *n_iter);
 
 void regc_mbar_destroy(regc_mbar *mb);

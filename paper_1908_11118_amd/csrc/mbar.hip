@@ -2725,8 +2725,10 @@ static hipError_t launch_newton(regc_mbar *mb, const SolveArgs &p, int B)
 // The preconditioned solve: the plain iteration from the states' means until it is near,
 // H once, then Anderson's iteration on the preconditioned map.  `solved` is left false
 // (and the caller solves from f = 0) when the plain phase takes more than kNearIter
-// iterations, the second more than kPreIter, or the data do not determine the solution.
-static int solve_preconditioned(regc_mbar *mb, double tol, int n_sampled, bool *solved, int *iters, double *delta)
+// iterations, the second more than kPreIter, both together more than max_iter, or the data
+// do not determine the solution.  iters counts every evaluation of the map, H's too.
+static int solve_preconditioned(regc_mbar *mb, double tol, int max_iter, int n_sampled, bool *solved, int *iters,
+                                double *delta)
 {
     constexpr int kNearIter = 60, kPreIter = 60;
     *solved = false;
@@ -2741,21 +2743,22 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int n_sampled, bool *
     const std::vector<double> f0 = mean_estimate(mb);
     if ((rc = start_solve(mb, f0.data(), st))) return rc;
     p.tol_switch = kSwitch;
-    p.max_iter = kNearIter;
-    if ((rc = run_iterations(mb, 1, kNearIter, [&]() {
+    p.max_iter = std::min(kNearIter, max_iter);
+    if ((rc = run_iterations(mb, 1, p.max_iter, [&]() {
              const hipError_t e = launch_map(mb, p);
              return e != hipSuccess ? e : launch_step(mb, p, 1);
          })))
         return rc;
     REGC_HIP(hipMemcpyAsync(&near, mb->state_d.p, sizeof near, hipMemcpyDeviceToHost, mb->stream));
     REGC_HIP(hipStreamSynchronize(mb->stream));
-    if (near.conv == 0) return REGC_OK;
+    *iters = near.it;
+    if (near.conv == 0 || near.it + 1 >= max_iter) return REGC_OK;
     if ((rc = start_solve(mb, nullptr, st)) || (rc = factorise(mb, p))) return rc;
     p.tol_switch = 0.0;
-    p.max_iter = kPreIter;
+    p.max_iter = std::min(kPreIter, max_iter - near.it - 1);
     p.polish = 2;
     p.y = mb->y_d.p;
-    if ((rc = run_iterations(mb, 1, kPreIter, [&]() {
+    if ((rc = run_iterations(mb, 1, p.max_iter, [&]() {
              hipError_t e = launch_map(mb, p);
              if (e == hipSuccess) e = launch_newton(mb, p, 1);
              return e != hipSuccess ? e : launch_step(mb, p, 1);
@@ -2768,7 +2771,7 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int n_sampled, bool *
     const double worst = *std::max_element(norm.begin(), norm.end());
     *solved = st.conv == 1 && worst <= kMaxInverse;
     mb->inverse_valid = *solved;
-    *iters = near.it + st.it;
+    *iters = near.it + 1 + st.it;
     *delta = st.delta;
     return REGC_OK;
 }
@@ -2788,10 +2791,12 @@ static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double
     REGC_HIP(hipEventRecord(e0.e, s));
     SolveState st{};
     bool solved = false;
+    int tried = 0;                        // the iterations of an attempt given up
     if (mb->method == 1 && !start && max_iter >= kNewtonMinIter && mb->S <= kNewtonStates && mb->L <= kNewtonTemps &&
         n >= 3 && !mb->mean_n.empty()) {
-        rc = solve_preconditioned(mb, tol, n, &solved, &st.it, &st.delta);
+        rc = solve_preconditioned(mb, tol, max_iter, n, &solved, &st.it, &st.delta);
         st.conv = 1;
+        if (!solved) tried = st.it;
     }
     SolveArgs p = solve_args(mb);
     if (!rc && !solved) {
@@ -2821,7 +2826,7 @@ static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double
     float ms = 0.f;
     REGC_HIP(hipEventElapsedTime(&ms, e0.e, e1.e));
     mb->ms_iter = ms;
-    mb->n_iter = st.it;
+    mb->n_iter = tried + st.it;
     if (iters) *iters = st.it;
     if (delta) *delta = st.delta;
     mb->solved = true;

@@ -56,3 +56,21 @@ def test_converged_means_below_the_tolerance(n_t, n_mu, n_max, per_state, spread
                 assert np.max(np.abs(g - g[0] - f)) < 10 * d + 1e-11, (tol, limit, it, d)
     mb.close()
     assert seen
+
+
+# (sampled so that the first phase of the preconditioned solve takes long; in the last case it
+# is given up)
+@pytest.mark.parametrize("n_t,n_mu,n_max,per_state,spread,cold,seed", [
+    (10, 3, 151, 67, 1.0994678737814576, 0.7119762452586738, 15), (2, 18, 98, 60, 0.7877822813860588, 0.5167166455213299, 67),
+    (10, 5, 158, 98, 1.352980275804317, 0.5605383714956059, 259), (11, 4, 143, 143, 0.9377045405814164, 0.5293343299291084, 568),
+    (4, 4, 92, 100, 1.0, 0.6, 4)])
+def test_iterations_stay_within_the_limit(n_t, n_mu, n_max, per_state, spread, cold, seed):
+    t, mu = W.linear_grid(cold, 1.6, n_t), W.linear_grid(-6.0, -2.0, n_mu)
+    mb, *_ = _loaded(t, mu, n_max, per_state, seed, spread)
+    for tol in (1e-6, 1e-13):
+        for limit in (64, 65, 70, 90, 119, 1000):
+            f, conv, it, d = mb.solve(tol=tol, max_iter=limit, allow_noconv=True)
+            ms, counted = mb.timing()
+            assert it <= limit and counted >= it
+            assert conv == (d < tol) and (conv or it == limit)
+    mb.close()
