@@ -961,7 +961,7 @@ struct SolveState {
     int gauge, memory;               // first sampled state; at most this many differences
     int polish;                      // iterations since the residual first came below tol
     double delta, d_prev;
-    double best;                     // the smallest residual below tol so far
+    double kept;                     // the latest residual below tol
 };
 
 constexpr int kMaxMemory = 8;        // differences the device's least squares holds
@@ -977,7 +977,7 @@ struct SolveArgs {
     const int *chunk_n, *chunk_b, *chunk_e, *seg_c0, *seg_c1;
     const double *lnomega;                     // [B][S]
     double *f, *fnew, *good;                   // [B][S]
-    double *best;                              // [B][S] the map value with the smallest residual (polish > 0)
+    double *kept;                              // [B][S] the map value with that residual (polish > 0)
     double *hist_r, *hist_g;                   // [B][kMaxMemory + 1][S]
     double *shift;                             // [B][nN]
     double *partial;                           // [B][L][rows]
@@ -1208,24 +1208,24 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
         // A residual below tol leaves an error of up to tol |(I - J)^-1|: the iteration goes on
         // towards the residual's rounding, a few times at most (the preconditioned one, whose
         // steps are that error, while the residual still halves).  The residual may rise again on
-        // the way, so the best map value below tol is kept, and is the result.
+        // the way: the result is the latest map value below tol, or the one below tol before it.
         int polish = st.polish;
         const bool under = p.method == 1 && !sw && finite && d < p.tol;
         const bool last = (polish > 0 && (!finite || d < kFloor || polish >= p.polish || (y && !(d < 0.5 * d_prev)))) ||
                           ((polish > 0 || under) && it >= p.max_iter) || (under && p.polish == 0);
-        const bool better = under && d < st.best;
-        const double best = better ? d : st.best;
+        const bool newest = under && (!last || d <= st.kept);
+        const double kept = newest ? d : st.kept;
         if (polish > 0 || under) ++polish;
-        if (better && !last)
+        if (newest && !last)
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                if (tid + T * k < p.S) p.best[(size_t)b * p.S + tid + T * k] = g[k];
+                if (tid + T * k < p.S) p.kept[(size_t)b * p.S + tid + T * k] = g[k];
         if (p.method == 0 || (!finite && it == 1) || last || sw) {
             // plain step, or the end: f is the map's value
 #pragma unroll
             for (int k = 0; k < R; ++k)
-                if (tid + T * k < p.S) f[tid + T * k] = last && !better ? p.best[(size_t)b * p.S + tid + T * k] : g[k];
-            if (last) d = best;
+                if (tid + T * k < p.S) f[tid + T * k] = last && !newest ? p.kept[(size_t)b * p.S + tid + T * k] : g[k];
+            if (last) d = kept;
             const bool check = p.method == 1 || it % 10 == 0 || it == p.max_iter;
             conv = check && (last || (finite && d < p.tol)) ? 1 : (sw ? 2 : 0);
             done = check && (conv || !finite);
@@ -1355,7 +1355,7 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
         if (tid == 0) {
             st.done = done; st.conv = conv; st.it = it; st.plain_left = plain_left;
             st.hist = hist; st.head = head; st.polish = polish;
-            st.delta = d; st.d_prev = d_prev; st.best = best;
+            st.delta = d; st.d_prev = d_prev; st.kept = kept;
         }
     }
     // the last block of the launch tells the host how far the batch is, in one store
@@ -1796,7 +1796,7 @@ __global__ void __launch_bounds__(256) boot_start(int S, int Bp, int memory, con
         SolveState z{};
         z.gauge = first < S ? first : 0;
         z.memory = min(memory, max(held - 2, 0));
-        z.delta = z.d_prev = z.best = INFINITY;
+        z.delta = z.d_prev = z.kept = INFINITY;
         st[b] = z;
     }
 }
@@ -2274,7 +2274,7 @@ struct regc_mbar {
     DevBuf<double> hinv_d;                // 1 / sum of every sample at the solution
     bool hinv_valid = false;              // hinv_d and shift_d are those of the solution in f_d
     int sub = 1;                          // blocks per chunk of a pass
-    DevBuf<double> shift_d, q_d, hist_r_d, hist_g_d, good_d, best_d;
+    DevBuf<double> shift_d, q_d, hist_r_d, hist_g_d, good_d, kept_d;
     DevBuf<SolveState> state_d;
     DevBuf<unsigned int> arrived_d;
     unsigned long long *progress = nullptr;   // host memory the step kernel writes (SolveArgs::host)
@@ -2549,7 +2549,7 @@ static SolveArgs solve_args(regc_mbar *mb)
     p.chunk_n = mb->chunk_n_d.p; p.chunk_b = mb->chunk_b_d.p; p.chunk_e = mb->chunk_e_d.p;
     p.seg_c0 = mb->seg_c0_d.p; p.seg_c1 = mb->seg_c1_d.p;
     p.lnomega = mb->lnomega_d.p;
-    p.f = mb->f_d.p; p.fnew = mb->fnew_d.p; p.good = mb->good_d.p; p.best = mb->best_d.p;
+    p.f = mb->f_d.p; p.fnew = mb->fnew_d.p; p.good = mb->good_d.p; p.kept = mb->kept_d.p;
     p.hist_r = mb->hist_r_d.p; p.hist_g = mb->hist_g_d.p;
     p.shift = mb->shift_d.p; p.partial = mb->q_d.p; p.st = mb->state_d.p; p.hinv = mb->hinv_d.p;
     p.arrived = mb->arrived_d.p; p.host = mb->progress;
@@ -2565,7 +2565,7 @@ static int solve_workspace(regc_mbar *mb, int B)
     const size_t hist = (size_t)B * (kMaxMemory + 1) * mb->S;
     if ((rc = mb->hinv_d.reserve(mb->ns)) || (rc = mb->shift_d.reserve((size_t)B * mb->nN)) || (rc = mb->q_d.reserve((size_t)B * mb->L * mb->nchunks * mb->sub)) ||
         (rc = mb->hist_r_d.reserve(hist)) || (rc = mb->hist_g_d.reserve(hist)) ||
-        (rc = mb->good_d.reserve((size_t)B * mb->S)) || (rc = mb->best_d.reserve(mb->S)) || (rc = mb->state_d.reserve(B)) || (rc = mb->arrived_d.reserve(2)))
+        (rc = mb->good_d.reserve((size_t)B * mb->S)) || (rc = mb->kept_d.reserve(mb->S)) || (rc = mb->state_d.reserve(B)) || (rc = mb->arrived_d.reserve(2)))
         return rc;
     if (!mb->progress) REGC_HIP(hipHostMalloc((void **)&mb->progress, sizeof(unsigned long long), hipHostMallocDefault));
     return REGC_OK;
@@ -2739,7 +2739,7 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int max_iter, int n_s
     SolveState st{}, near{};
     st.gauge = mb->gauge;
     st.memory = std::min(mb->memory, std::max(n_sampled - 2, 0));
-    st.delta = st.d_prev = st.best = INFINITY;
+    st.delta = st.d_prev = st.kept = INFINITY;
     const std::vector<double> f0 = mean_estimate(mb);
     if ((rc = start_solve(mb, f0.data(), st))) return rc;
     p.tol_switch = kSwitch;
@@ -2805,7 +2805,7 @@ static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double
         st = SolveState{};
         st.gauge = mb->gauge;
         st.memory = std::min(mb->memory, std::max(n - 2, 0));
-        st.delta = st.d_prev = st.best = INFINITY;
+        st.delta = st.d_prev = st.kept = INFINITY;
         const std::vector<double> zero(start ? 0 : mb->S, 0.0);
         if (!(rc = start_solve(mb, start ? start : zero.data(), st)))
             rc = run_iterations(mb, 1, max_iter, [&]() {
@@ -3282,7 +3282,7 @@ static int bootstrap_batch(regc_mbar *mb, const TargetDev &T, double tol, int64_
     g.Bp = Bp;
     SolveArgs &p = g.p;
     p = solve_args(mb);
-    p.polish = 0;                 // (a replicate's spread is what is asked for; and best stays unused)
+    p.polish = 0;                 // (a replicate's spread is what is asked for; and kept stays unused)
     // blocks of a pass are a part of a chunk and a group of columns
     p.sub = (int)std::min<int64_t>(kChunk / 256, std::max<int64_t>(1, (512 + mb->nchunks - 1) / mb->nchunks));
     p.rows = p.nchunks * p.sub;
