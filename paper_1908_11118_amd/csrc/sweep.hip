@@ -297,19 +297,27 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                         de = (double)pd;
                         return (int64_t)__ballot(de <= thr) < 0;
                     }
-                    // a hard core makes the sum infinite, so that one test decides.  Alternate slots:
-                    // exchange k+2 reuses the slot of exchange k only after every wave passed the
-                    // barrier of exchange k+1
+                    // a hard core is sent as a NaN of its own, so that one test decides: no threshold
+                    // lets it pass, not even an infinite one.  Alternate slots: exchange k+2 reuses the
+                    // slot of exchange k only after every wave passed the barrier of exchange k+1
                     Real *x0 = reinterpret_cast<Real *>(xch) + (xcount & 1) * SPLIT;
-                    if (can_overlap) pd = core != 0 ? Real(INFINITY) : pd;
+                    if (can_overlap) pd = core != 0 ? core_mark() : pd;
                     if (lane == kWave - 1) x0[part] = pd;
                     ++xcount;
                     __syncthreads();
-                    de = (double)x0[0];
+                    Real x[SPLIT];
 #pragma unroll
-                    for (int q = 1; q < SPLIT; ++q) de += (double)x0[q];
+                    for (int q = 0; q < SPLIT; ++q) x[q] = x0[q];
+                    de = (double)x[0];
+#pragma unroll
+                    for (int q = 1; q < SPLIT; ++q) de += (double)x[q];
                     if (uniform(de <= thr)) return true;
-                    if (can_overlap && uniform(de == (double)INFINITY)) corem |= bit;
+                    if (can_overlap && uniform(de != de)) {
+                        bool marked = false;
+#pragma unroll
+                        for (int q = 0; q < SPLIT; ++q) marked |= is_core_mark(x[q]);
+                        if (uniform(marked)) corem |= bit;
+                    }
                     return false;
                 };
                 // An accepted move.  Every wave of the walker writes the update into the shared

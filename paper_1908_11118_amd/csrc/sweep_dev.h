@@ -234,6 +234,16 @@ __device__ __forceinline__ float bcast(float v, int lane)
 
 __device__ __forceinline__ Real bcast_real(Real v, int lane) { return bcast(v, lane); }
 
+// What a wave with a new pair inside the hard core sends in the place of its sum: a NaN whose
+// bits no arithmetic makes.
+#if defined(REGC_FP64)
+__device__ __forceinline__ double core_mark() { return __hiloint2double(0x7FF8C0DE, 0); }
+__device__ __forceinline__ bool is_core_mark(double v) { return __double2hiint(v) == 0x7FF8C0DE; }
+#else
+__device__ __forceinline__ float core_mark() { return __int_as_float(0x7FC0C0DE); }
+__device__ __forceinline__ bool is_core_mark(float v) { return __float_as_int(v) == 0x7FC0C0DE; }
+#endif
+
 // Slab access: all atoms, or the 3x3 block of x-y columns around a column
 // (periodic in x and y; column ids row-major, y outer).
 //  kSlabAll   every packed entry (a slab too narrow for columns);

@@ -1,4 +1,5 @@
-"""Sampling where an input leaves the usual range: slab atoms given outside the cell."""
+"""Sampling where an input leaves the usual range: slab atoms given outside the cell, an
+acceptance threshold that overflows, pair terms that do."""
 import numpy as np
 import pytest
 
@@ -7,6 +8,7 @@ from paper_1908_11118_amd import regc
 from paper_1908_11118_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+ACC, CORE = [1, 3, 5], 9                  # accepted moves by kind, hard-core rejections
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -89,3 +91,33 @@ def test_slab_atoms_within_half_a_cell_are_taken_as_given(cells):
         wk = g.walkers()
     assert np.array_equal(bits, r["bits"])
     assert np.allclose(wk["e"], ref.e, rtol=1e-10, atol=1e-9)
+
+
+@pytest.mark.parametrize("precision", [regc.FP32PAIR, regc.FP64])
+@pytest.mark.parametrize("split", [1, 2, 4])
+def test_hard_core_under_an_infinite_threshold(precision, split):
+    """T = 1e308: (ln prefactor - ln U) T overflows, and still no pair comes closer than the
+    hard core."""
+    w = W.small_lj(n_t=1, n_mu=1, n_max=40).replace(t=np.array([1e308]), mu=np.array([0.0]), hc_frac=0.9)
+    with regc.Regc(w, precision=precision, split=split, walkers_per_block=1) as g:
+        g.run(8)
+        wk, st = g.walkers(), g.stats()["stats"]
+    x = wk["xyz"][0, : wk["n"][0]]
+    d = x[:, None] - x[None]
+    d[..., :2] -= np.array([w.lx, w.ly]) * np.rint(d[..., :2] / np.array([w.lx, w.ly]))
+    r = np.sqrt((d ** 2).sum(-1))[np.triu_indices(len(x), 1)]
+    assert len(x) > 5 and st[0, CORE] > 0
+    assert r.min() >= 0.9 * w.sig_gg * (1 - 1e-6)
+
+
+@pytest.mark.parametrize("split", [1, 2, 4])
+def test_infinite_pair_terms_are_not_hard_cores(split):
+    """Without a hard core a pair term past FP32's range is an ordinary rejection."""
+    w = W.small_lj(n_t=1, n_mu=1, n_max=40).replace(t=np.array([1.0]), mu=np.array([4.0]), hc_frac=0.0, sig_gg=1e5,
+                                                    shifted=0, slab=np.zeros((0, 3)))
+    with regc.Regc(w, precision=regc.FP32PAIR, split=split, walkers_per_block=1) as g:
+        g.run(20)
+        wk, st = g.walkers(), g.stats()["stats"]
+    att, acc = st[0, [0, 2, 4]].sum(), st[0, ACC].sum()
+    assert wk["n"][0] > 0 and att > acc + st[0, [6, 7, 8]].sum()      # some were rejected on their energy
+    assert st[0, CORE] == 0
