@@ -680,9 +680,18 @@ static SweepArgs sweep_args(regc_ctx *c, int64_t sweep0, int n, bool use_clock)
     return a;
 }
 
+// Sweeps whose pairs inside the cutoff a wave of the one-trial kernel counts in 32 bits for
+// certain (a displacement looks at every other particle and the slab's candidates twice).
+static int64_t counted_sweeps(const regc_ctx *c)
+{
+    const int64_t per_sweep = 2 * (int64_t)c->kmax * ((int64_t)c->nmax_all + c->max_slab_scan);
+    return (int64_t)UINT32_MAX / per_sweep;
+}
+
 static int launch_sweeps(regc_ctx *c, int64_t sweep0, int n, hipStream_t stream, bool use_clock)
 {
     SweepArgs a = sweep_args(c, sweep0, n, use_clock);
+    a.wide = n > counted_sweeps(c) ? 1 : 0;
     int rc;
     const bool ev = c->timing && !use_clock;
     if (ev && (rc = record_event(c, c->ev_sweep, true))) return rc;
@@ -895,7 +904,9 @@ static int build_graph(regc_ctx *c)
 {
     if (c->gexec) return REGC_OK;
     const regc_opts &o = c->opts;
-    const int spl = o.sweeps_per_launch > 0 ? std::min(o.sweeps_per_launch, o.swap_every) : o.swap_every;
+    const int spl = (int)std::min<int64_t>(
+        o.sweeps_per_launch > 0 ? std::min(o.sweeps_per_launch, o.swap_every) : o.swap_every,
+        std::max<int64_t>(1, counted_sweeps(c)));
     REGC_HIP(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
     REGC_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
     int rc = REGC_OK;
@@ -953,12 +964,13 @@ extern "C" int regc_run(regc_ctx *c, int64_t n_sweeps)
         return REGC_OK;
     }
     int64_t left = n_sweeps;
-    const bool persist = o.persistent > 0 && !learned_on(c) && !c->obs_on && !c->min_on;
+    const int64_t counted = counted_sweeps(c);
+    const bool persist = o.persistent > 0 && !learned_on(c) && !c->obs_on && !c->min_on && counted >= o.swap_every;
     auto eager = [&](int64_t count) -> int {
         int64_t rem = count;
         while (rem > 0) {
             if (persist && c->sweep % o.swap_every == 0 && rem >= o.swap_every) {
-                const int k = (int)std::min<int64_t>(o.persistent, rem / o.swap_every);
+                const int k = (int)std::min<int64_t>(std::min<int64_t>(o.persistent, counted / o.swap_every), rem / o.swap_every);
                 const int rc = launch_persistent(c, c->sweep, k);
                 if (rc) return rc;
                 c->sweep += (int64_t)k * o.swap_every;
@@ -968,7 +980,7 @@ extern "C" int regc_run(regc_ctx *c, int64_t n_sweeps)
             int64_t chunk = rem;
             if (o.swap_every > 0) chunk = std::min<int64_t>(chunk, o.swap_every - c->sweep % o.swap_every);
             const int spl = o.sweeps_per_launch > 0 ? o.sweeps_per_launch : (o.swap_every > 0 ? o.swap_every : 100);
-            chunk = std::min<int64_t>(chunk, spl);
+            chunk = std::min<int64_t>(std::min<int64_t>(chunk, spl), std::max<int64_t>(1, counted));
             if ((c->obs_on || c->min_on) && o.sample_every > 0)
                 chunk = std::min<int64_t>(chunk, o.sample_every - c->sweep % o.sample_every);
             int rc = launch_sweeps(c, c->sweep, (int)chunk, c->stream, false);

@@ -100,6 +100,7 @@ struct SweepArgs {
     int gas_stride;                 // LDS entries per walker (max n_max over classes)
     int max_slab_scan;              // most slab candidates one trial scans (max over classes)
     int resync_every;               // > 0: running energy recomputed after every resync_every-th sweep
+    int wide;                       // one sweep alone can pass 32 bits of pairs inside the cutoff
     int count_pairs;                // batched kernel: count the pair terms inside the cutoff
     // persistent launch: the exchange step inside the launch after every swap_every-th
     // sweep, between two grid-wide barriers (gbar: arrival count, generation; gerr set

@@ -120,7 +120,9 @@ __device__ __forceinline__ void grid_sync(const SweepArgs &a)
 // MODE: how the slab is read, fixed where every class of the launch reads it alike and the
 // gas interacts (kSlabAny: decided as it runs).  A trial's path has about thirty branches, each a few
 // issue slots of the one or two waves that a SIMD has; fixing it takes out a third (1024 walkers with N <= 200, 100 sweeps: 17.4 -> 16.1 ms).
-template <int SPLIT, bool CULL, bool PERSIST, int MODE = kSlabAny>
+// WIDE: a launch whose pairs inside the cutoff can pass 32 bits (within one sweep: launches of
+// more sweeps are kept below that by the host, since the 64-bit count made all of them 1 % slower).
+template <int SPLIT, bool CULL, bool PERSIST, int MODE = kSlabAny, bool WIDE = false>
 __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 {
     extern __shared__ __align__(32) unsigned char smem[];
@@ -414,6 +416,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 accept(i, v);
             }
             cand += cb;
+            if (WIDE && useful >> 31) {      // (a batch adds less than 2^31)
+                if (lane == 0 && a.pairs) atomicAdd(a.pairs + 1, (unsigned long long)useful);
+                useful = 0;
+            }
             // the batch's events, counter k in lane k
             const uint32_t ev[kNStat] = {(uint32_t)__popcll(is_disp), (uint32_t)__popcll(accm & is_disp), (uint32_t)__popcll(is_ins), (uint32_t)__popcll(accm & is_ins),
                                     (uint32_t)__popcll(is_del), (uint32_t)__popcll(accm & is_del), (uint32_t)__popcll(nonem & is_ins),
@@ -515,6 +521,13 @@ __global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock, SPLIT != 2 ? kSwe
     sweep_kernel(SweepArgs a)
 {
     sweep_body<SPLIT, CULL, false>(a);
+}
+
+template <int SPLIT, bool CULL>
+__global__ void __launch_bounds__(kWave * kMaxWalkersPerBlock, SPLIT != 2 ? kSweepWavesPerSimd : 1)
+    sweep_wide_kernel(SweepArgs a)
+{
+    sweep_body<SPLIT, CULL, false, kSlabAny, true>(a);
 }
 
 template <int SPLIT, int MODE>
@@ -1770,6 +1783,11 @@ hipError_t SWEEP_LAUNCH(const SweepArgs &a, int n_blocks, int waves_per_block, i
     } else if (batch == 2) {
         if (a.count_pairs) hipLaunchKernelGGL((batch_kernel<2, true>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((batch_kernel<2, false>), grid, block, smem, s, a);
+    } else if (a.wide) {
+        void (*k)(SweepArgs) = cull ? &sweep_wide_kernel<1, true> : &sweep_wide_kernel<1, false>;
+        if (split == 4) k = cull ? &sweep_wide_kernel<4, true> : &sweep_wide_kernel<4, false>;
+        else if (split == 2) k = cull ? &sweep_wide_kernel<2, true> : &sweep_wide_kernel<2, false>;
+        hipLaunchKernelGGL(k, grid, block, smem, s, a);
     } else if (split == 4) {
         if (cull) hipLaunchKernelGGL((sweep_kernel<4, true>), grid, block, smem, s, a);
         else hipLaunchKernelGGL((sweep_kernel<4, false>), grid, block, smem, s, a);

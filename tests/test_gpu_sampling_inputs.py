@@ -1,5 +1,5 @@
 """Sampling where an input leaves the usual range: slab atoms given outside the cell, an
-acceptance threshold that overflows, pair terms that do."""
+acceptance threshold that overflows, pair terms that do, runs of more pairs than 32 bits count."""
 import numpy as np
 import pytest
 
@@ -121,3 +121,24 @@ def test_infinite_pair_terms_are_not_hard_cores(split):
     att, acc = st[0, [0, 2, 4]].sum(), st[0, ACC].sum()
     assert wk["n"][0] > 0 and att > acc + st[0, [6, 7, 8]].sum()      # some were rejected on their energy
     assert st[0, CORE] == 0
+
+
+@pytest.mark.parametrize("per,sweeps", [(1000, 1000), (1000000, 1)])
+def test_pairs_past_32_bits(per, sweeps):
+    """4000 particles in a layer two cutoffs wide, a million displacements in one call, of
+    many sweeps or of a single one: about 5e9 pairs inside the cutoff, and their share of the
+    candidates is that of a short run."""
+    n = 4000
+    w = W.Workload(name="pairs", slab=np.zeros((0, 3)), lx=5.0, ly=5.0, zlo=0.0, zhi=0.01, t=np.array([1.0]),
+                   mu=np.array([0.0]), n_max=n, eps_gg=0.0, sig_gg=1e-3, hc_frac=0.0, p_disp=1.0, p_ins=0.0,
+                   trials_per_sweep=per, max_disp=0.004, swap_every=0, sample_every=0)
+    x = np.random.default_rng(1).random((n, 3)) * [5.0, 5.0, 0.01]
+    share = []
+    for k, system in ((5, w.replace(trials_per_sweep=1000)), (sweeps, w)):
+        with regc.Regc(system, precision=regc.FP32PAIR, split=1, walkers_per_block=1, sweeps_per_launch=k) as g:
+            g.set_walkers([n], [x])
+            g.run(k)
+            cand, useful = g.pair_counts()
+        share.append(useful / cand)
+    assert 2 ** 32 < useful < cand
+    assert abs(share[1] - share[0]) < 0.02
