@@ -1338,7 +1338,7 @@ __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const P
                 const double dy = md_min_image(yi - (double)p.y, ly);
                 const double dz = zi - (double)p.z;
                 const double r2 = dx * dx + dy * dy + dz * dz;
-                in = in && r2 < pot.rc2;
+                in = in && !(r2 >= pot.rc2);         // (a distance that is no number shows in the energy)
                 const double s2 = sig2 / r2, s6 = s2 * s2 * s2;
                 const double g = 6.0 * eps4 * (2.0 * s6 * s6 - s6) / r2;
                 const double h = in ? g : 0.0, u = in ? part * (eps4 * (s6 * s6 - s6) - shift) : 0.0;
@@ -1347,7 +1347,7 @@ __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const P
             };
 #pragma unroll 4
             for (int j = 0; j < n; ++j) partner(gas[j], j != i, pot.sig2_gg, pot.eps4_gg, pot.shift_gg, 0.5);
-            if (zi < (double)sv.top_plus_rc)
+            if (!(zi >= (double)sv.top_plus_rc))
 #pragma unroll 4
                 for (int k = 0; k < ns; ++k) partner(sv.atoms[k], true, pot.sig2_gs, pot.eps4_gs, pot.shift_gs, 1.0);
             f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;

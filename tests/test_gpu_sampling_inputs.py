@@ -1,5 +1,5 @@
 """Sampling where an input leaves the usual range: slab atoms given outside the cell, an
-acceptance threshold that overflows, pair terms that do, runs of more pairs than 32 bits count."""
+acceptance threshold that overflows, pair terms that do, runs of more pairs than 32 bits count, molecular dynamics that blows up."""
 import numpy as np
 import pytest
 
@@ -142,3 +142,19 @@ def test_pairs_past_32_bits(per, sweeps):
         share.append(useful / cand)
     assert 2 ** 32 < useful < cand
     assert abs(share[1] - share[0]) < 0.02
+
+
+def test_md_that_blows_up_reports_it():
+    """An infinite time step: positions and energy are not numbers, in the oracle as here."""
+    w = W.small_lj(n_t=1, n_mu=1, n_max=10).replace(schedule=1, x0=0.0, md_steps=1, md_dt=float("inf"), sample_every=1)
+    x = W.random_configuration(np.random.default_rng(2), w, 6)
+    ref = oracle.Chain(w)
+    full = np.zeros((1, 10, 3))
+    full[0, :6] = x
+    ref.set_walkers([6], full)
+    ref.run(1)
+    with regc.Regc(w, precision=regc.FP64) as g:
+        g.set_walkers([6], [x])
+        g.run(1)
+        e = g.walkers(xyz=False)["e"][0]
+    assert np.isnan(ref.e[0]) and np.isnan(e)
