@@ -1322,7 +1322,8 @@ __device__ __forceinline__ double md_min_image(double d, double box)
 // energy (FP64, wave-uniform).  Truncated-shifted LJ; the shift does not act on forces.
 // A trajectory amplifies the last bit of a force, so the order of a particle's sum is kept;
 // partners outside the cutoff add 0 instead of being branched around, so that the long
-// chains of several partners' quotients overlap, and a particle above the slab's reach skips it.
+// chains of several partners' quotients overlap, and a particle above the slab's reach skips it
+// (by more than the reach's rounding in FP32: the cutoff is tested in FP64 here in both builds).
 __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const PotDev &pot, const Box &b, double *f,
                             int lane)
 {
@@ -1347,7 +1348,7 @@ __device__ double md_forces(const Real4 *gas, int n, const SlabView &sv, const P
             };
 #pragma unroll 4
             for (int j = 0; j < n; ++j) partner(gas[j], j != i, pot.sig2_gg, pot.eps4_gg, pot.shift_gg, 0.5);
-            if (!(zi >= (double)sv.top_plus_rc))
+            if (!(zi - (double)sv.top_plus_rc >= 1e-3))
 #pragma unroll 4
                 for (int k = 0; k < ns; ++k) partner(sv.atoms[k], true, pot.sig2_gs, pot.eps4_gs, pot.shift_gs, 1.0);
             f[3 * i] = fx; f[3 * i + 1] = fy; f[3 * i + 2] = fz;

@@ -1,5 +1,5 @@
 """Sampling where an input leaves the usual range: slab atoms given outside the cell, an
-acceptance threshold that overflows, pair terms that do, runs of more pairs than 32 bits count, molecular dynamics that blows up."""
+acceptance threshold that overflows, pair terms that do, runs of more pairs than 32 bits count, molecular dynamics that blows up, a particle at the edge of the slab's reach."""
 import numpy as np
 import pytest
 
@@ -158,3 +158,19 @@ def test_md_that_blows_up_reports_it():
         g.run(1)
         e = g.walkers(xyz=False)["e"][0]
     assert np.isnan(ref.e[0]) and np.isnan(e)
+
+
+@pytest.mark.parametrize("precision", [regc.FP32PAIR, regc.FP64])
+def test_md_at_the_edge_of_the_slabs_reach(precision):
+    """A particle right above the slab's atom, closer than the cutoff by less than FP32
+    resolves the cutoff (2.6 in FP32 is 2.5999999)."""
+    z = float(np.float32(2.6))
+    w = W.Workload(name="edge", slab=np.array([[3.0, 3.0, 0.0]]), lx=6.0, ly=6.0, zlo=0.5, zhi=5.0, t=np.array([1.0]),
+                   mu=np.array([-3.0]), n_max=4, rc=2.6, shifted=0, schedule=1, x0=0.0, md_steps=1, md_dt=1e-30,
+                   md_tau=0.0, sample_every=1)
+    with regc.Regc(w, precision=precision) as g:
+        g.set_walkers([1], [np.array([[3.0, 3.0, z]])])
+        g.run(1)
+        e = g.walkers(xyz=False)["e"][0]
+    c6 = z ** -6
+    assert e == pytest.approx(4.0 * (c6 * c6 - c6), rel=1e-5)
