@@ -314,7 +314,10 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
 #pragma unroll
                     for (int q = 1; q < SPLIT; ++q) de += (double)x[q];
                     if (uniform(de <= thr)) return true;
-                    if (can_overlap && uniform(de != de)) {
+                    // (FP32: as if it were rare, so that the search lies out of the way of the other
+                    // trials: 714 walkers with N <= 22 543 -> 533 us a call; in FP64 that costs 2 %)
+                    if (can_overlap &&
+                        __builtin_expect_with_probability(uniform(de != de), 0, sizeof(Real) == 4 ? 0.9995 : 0.5)) {
                         bool marked = false;
 #pragma unroll
                         for (int q = 0; q < SPLIT; ++q) marked |= is_core_mark(x[q]);
