@@ -7,11 +7,10 @@
 #include <cmath>
 #include <cstring>
 #include <string>
-#include <initializer_list>
-#include <mutex>
 #include <vector>
 
 #include "host_util.h"
+#include "stage.h"
 #include "learn_dev.h"
 
 namespace regc {
@@ -110,11 +109,9 @@ struct regc_ctx {
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
 
-    uint32_t *stage = nullptr;    // pinned host memory of kStageBytes for the getters' results
-    std::mutex stage_mutex;
+    Stage stage;                  // the getters' results on their way to the host
     ~regc_ctx()
     {
-        if (stage) (void)hipHostFree(stage);
         if (gexec) (void)hipGraphExecDestroy(gexec);
         if (graph) (void)hipGraphDestroy(graph);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
@@ -369,6 +366,7 @@ static int ctx_alloc_and_init(regc_ctx *c)
     // launch shape: walkers per block, waves per walker, LDS
     int dev = 0;
     REGC_HIP(hipGetDevice(&dev));
+    c->stage.device = dev;
     int lds_max = 0, n_cu = 0, lds_cu = 0;
     REGC_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
     REGC_HIP(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1293,56 +1291,12 @@ extern "C" int regc_aiat_phase(const double *e_min, int n_max, int n_mu, const d
     return REGC_OK;
 }
 
-// What the getters return: device arrays into host arrays (null: not asked for), all in
-// one launch and one wait through pinned memory while they are small (64 walkers, ten records: 12
-// copies 150 us, three launches and waits 25), else a copy each.
-struct Piece {
-    void *dst;
-    const void *src;
-    size_t bytes;                 // a multiple of 4
-};
-
-constexpr size_t kStageBytes = (size_t)256 << 10;
-
-static int fetch(regc_ctx *c, std::initializer_list<Piece> pieces)
-{
-    PackArgs a{};
-    size_t total = 0;
-    for (const Piece &p : pieces)
-        if (p.dst && p.bytes) {
-            total += p.bytes;
-            a.src[a.n] = static_cast<const uint32_t *>(p.src);
-            a.end[a.n++] = (uint32_t)std::min<size_t>(total / 4, UINT32_MAX);
-        }
-    if (!total) {
-        REGC_HIP(hipStreamSynchronize(c->stream));
-        return REGC_OK;
-    }
-    if (total > kStageBytes) {
-        REGC_HIP(hipStreamSynchronize(c->stream));
-        for (const Piece &p : pieces)
-            if (p.dst && p.bytes) REGC_HIP(hipMemcpy(p.dst, p.src, p.bytes, hipMemcpyDeviceToHost));
-        return REGC_OK;
-    }
-    std::lock_guard<std::mutex> lock(c->stage_mutex);
-    if (!c->stage) REGC_HIP(hipHostMalloc((void **)&c->stage, kStageBytes, hipHostMallocDefault));
-    REGC_HIP(launch_pack(a, c->stage, c->stream));
-    REGC_HIP(hipStreamSynchronize(c->stream));
-    const char *from = reinterpret_cast<const char *>(c->stage);
-    for (const Piece &p : pieces)
-        if (p.dst && p.bytes) {
-            std::memcpy(p.dst, from, p.bytes);
-            from += p.bytes;
-        }
-    return REGC_OK;
-}
-
 extern "C" int regc_get_observables(regc_ctx *c, uint32_t *obs, int64_t cap_records, int64_t *n_out)
 {
     REGC_CHECK(c && obs && n_out, REGC_EINVAL, "null argument");
     REGC_CHECK(c->obs_d.p && c->n_obs > 0, REGC_ESTATE, "no observables recorded");
     const int64_t k = std::min(cap_records, c->n_rec);
-    const int rc = fetch(c, {{obs, c->obs_d.p, sizeof(uint32_t) * (size_t)k * c->W * c->n_obs}});
+    const int rc = fetch(c->stage, c->stream, {{obs, c->obs_d.p, sizeof(uint32_t) * (size_t)k * c->W * c->n_obs}});
     if (rc) return rc;
     *n_out = k;
     return REGC_OK;
@@ -1390,11 +1344,11 @@ extern "C" int regc_get_walkers(regc_ctx *c, int32_t *n, double *e, int32_t *lab
     REGC_CHECK(c, REGC_EINVAL, "null context");
     std::vector<int32_t> nn(xyz ? c->W : 0);
     const size_t W = c->W;
-    const int rc = fetch(c, {{e, c->e_d.p, sizeof(double) * W},
-                             {xyz, c->xyz_d.p, sizeof(double) * W * c->nmax_all * 3},
-                             {n, c->n_d.p, sizeof(int32_t) * W},
-                             {label, c->label_d.p, sizeof(int32_t) * W},
-                             {xyz ? nn.data() : nullptr, c->n_d.p, sizeof(int32_t) * W}});
+    const int rc = fetch(c->stage, c->stream, {{e, c->e_d.p, sizeof(double) * W},
+                                               {xyz, c->xyz_d.p, sizeof(double) * W * c->nmax_all * 3},
+                                               {n, c->n_d.p, sizeof(int32_t) * W},
+                                               {label, c->label_d.p, sizeof(int32_t) * W},
+                                               {xyz ? nn.data() : nullptr, c->n_d.p, sizeof(int32_t) * W}});
     if (rc) return rc;
     if (xyz)
         for (int w = 0; w < c->W; ++w)
@@ -1484,9 +1438,9 @@ extern "C" int regc_get_samples(regc_ctx *c, double *e, int32_t *n, int32_t *sta
     REGC_CHECK(c && n_out, REGC_EINVAL, "null argument");
     const int64_t cnt = std::min<int64_t>(cap, c->n_rec * c->W);
     const size_t have = (size_t)std::max<int64_t>(cnt, 0);
-    const int rc = fetch(c, {{e, c->samp_e.p, sizeof(double) * have},
-                             {n, c->samp_n.p, sizeof(int32_t) * have},
-                             {state, c->samp_s.p, sizeof(int32_t) * have}});
+    const int rc = fetch(c->stage, c->stream, {{e, c->samp_e.p, sizeof(double) * have},
+                                               {n, c->samp_n.p, sizeof(int32_t) * have},
+                                               {state, c->samp_s.p, sizeof(int32_t) * have}});
     if (rc) return rc;
     *n_out = cnt;
     return REGC_OK;
@@ -1519,9 +1473,9 @@ extern "C" int regc_get_stats(regc_ctx *c, int64_t *stats, int64_t *swap_att, in
 {
     REGC_CHECK(c, REGC_EINVAL, "null context");
     const size_t W = c->W;
-    return fetch(c, {{stats, c->stats_d.p, sizeof(int64_t) * W * kNStat},
-                     {swap_att, c->att_d.p, sizeof(int64_t) * 4 * W},
-                     {swap_acc, c->acc_d.p, sizeof(int64_t) * 4 * W}});
+    return fetch(c->stage, c->stream, {{stats, c->stats_d.p, sizeof(int64_t) * W * kNStat},
+                                       {swap_att, c->att_d.p, sizeof(int64_t) * 4 * W},
+                                       {swap_acc, c->acc_d.p, sizeof(int64_t) * 4 * W}});
 }
 
 extern "C" int regc_count_pairs(regc_ctx *c, int on)
