@@ -1968,9 +1968,10 @@ __global__ void __launch_bounds__(kFnewThreads) boot_fnew(BootArgs g)
 }
 
 // <N> and the heat capacity of replicate blockIdx.y at target temperature blockIdx.x: G(N)
-// and the moments of E at each N from the sums, then a wave per chemical potential.
-__global__ void __launch_bounds__(256) boot_target_eval(BootArgs g, int nT, int nMu, const double *tb, const double *tlnz,
-                                                     double *rep_n, double *rep_c)
+// and the moments of E at each N from the sums, then a wave per chemical potential.  nT: the
+// temperatures of this pass, nK: targets of a replicate in rep_n and rep_c.
+__global__ void __launch_bounds__(256) boot_target_eval(BootArgs g, int nT, int nMu, int nK, const double *tb,
+                                                     const double *tlnz, double *rep_n, double *rep_c)
 {
     extern __shared__ double sh[];
     const SolveArgs &p = g.p;
@@ -2013,7 +2014,7 @@ __global__ void __launch_bounds__(256) boot_target_eval(BootArgs g, int nT, int 
         se = wave_total(se);
         se2 = wave_total(se2);
         if (lane == 0) {
-            const size_t k = (size_t)b * nT * nMu + t * nMu + m;
+            const size_t k = (size_t)b * nK + t * nMu + m;
             const double e1 = se / s0;
             rep_n[k] = sn / s0;
             rep_c[k] = tb[t] * tb[t] * (se2 / s0 - e1 * e1);
@@ -3266,26 +3267,68 @@ extern "C" int regc_mbar_timing(regc_mbar *mb, double *ms_iter_total, int64_t *n
 extern "C" void regc_mbar_destroy(regc_mbar *mb) { delete mb; }
 
 // ---------------------------------------------------------------------------
+// The batch's workspace: replicates of a batch and target temperatures of a pass over them,
+// such that it stays below kBootBytes (a chunk's partial sums are 8 max(L, 3 temperatures)
+// bytes per replicate, so that 1e8 samples would take 8 GB for 64 temperatures at once).
+// Fewer temperatures at once cost little (a pass reads the samples for 16 of them either way),
+// fewer replicates cost whole solves: those go last.  The workspace stays with the handle up to
+// kBootKept, which holds it for 1e6 samples and 64 temperatures.
+constexpr size_t kBootBytes = (size_t)1 << 30, kBootKept = (size_t)256 << 20;
+
+struct BootPlan {
+    int batch = 0, temps = 0;        // multiples of 16; batch 0: nothing fits
+    int sub = 1, rows = 0, outs = 0;
+    size_t bytes = 0;
+};
+
+static BootPlan boot_plan(const regc_mbar *mb, int64_t R, int B, int nT)
+{
+    BootPlan q;
+    // blocks of a pass are a part of a chunk and a group of columns
+    q.sub = (int)std::min<int64_t>(kChunk / 256, std::max<int64_t>(1, (512 + mb->nchunks - 1) / mb->nchunks));
+    q.rows = mb->nchunks * q.sub;
+    const double fixed = (double)R * 4 + 8.0 * mb->nN * mb->L + mb->S * (4.0 + 8.0 * (6 + 2 * (kMaxMemory + 1)));
+    for (int batch = std::min(kBootMax, (B + 15) & ~15); batch > 0; batch -= 16)
+        for (int temps = (nT + 15) & ~15; temps > 0; temps = temps > 16 ? std::max(16, temps / 2 & ~15) : 0) {
+            const int outs = std::max(mb->L, 3 * std::min(temps, nT));
+            const double bytes = batch * (fixed + 8.0 * outs * ((double)q.rows + mb->nN));
+            if (bytes > (double)kBootBytes) continue;
+            q.batch = batch;
+            q.temps = temps;
+            q.outs = outs;
+            q.bytes = (size_t)bytes;
+            return q;
+        }
+    return q;
+}
+
+static void release_boot(regc_mbar *mb)
+{
+    mb->b_rec_d.release(); mb->b_mult_d.release(); mb->b_omega_d.release();
+    mb->b_lnomega_d.release(); mb->b_f_d.release(); mb->b_fnew_d.release(); mb->b_good_d.release();
+    mb->b_hr_d.release(); mb->b_hg_d.release(); mb->b_shift_d.release();
+    mb->b_a_d.release(); mb->b_part_d.release(); mb->b_sum_d.release(); mb->b_state_d.release();
+}
+
 // All bootstrap replicates b0 .. b0 + B - 1 together: their solutions from the full one
 // (f_d) by Anderson's iteration preconditioned with the full data's inverse Jacobian, then
 // <N> and the heat capacity at the targets into rep_n, rep_c [B][targets] (device).  `ok`
-// is left false where a replicate does not settle.
-static int bootstrap_batch(regc_mbar *mb, const TargetDev &T, double tol, int64_t R, int64_t rs, int64_t blk, uint64_t seed,
-                           int b0, int B, double *rep_n, double *rep_c, bool *ok)
+// is left false where a replicate does not settle, or where memory for them lacks.
+static int bootstrap_batch(regc_mbar *mb, const BootPlan &plan, const TargetDev &T, double tol, int64_t R, int64_t rs,
+                           int64_t blk, uint64_t seed, int b0, int B, double *rep_n, double *rep_c, bool *ok)
 {
     constexpr int kBootIter = 80;
     *ok = false;
     hipStream_t s = mb->stream;
-    const int Bp = (B + 15) & ~15, S = mb->S, L = mb->L, outs = std::max(L, 3 * T.nT);
+    const int Bp = (B + 15) & ~15, S = mb->S, L = mb->L, outs = plan.outs;
     BootArgs g{};
     g.B = B;
     g.Bp = Bp;
     SolveArgs &p = g.p;
     p = solve_args(mb);
     p.polish = 0;                 // (a replicate's spread is what is asked for; and kept stays unused)
-    // blocks of a pass are a part of a chunk and a group of columns
-    p.sub = (int)std::min<int64_t>(kChunk / 256, std::max<int64_t>(1, (512 + mb->nchunks - 1) / mb->nchunks));
-    p.rows = p.nchunks * p.sub;
+    p.sub = plan.sub;
+    p.rows = plan.rows;
     int rc;
     const size_t hist = (size_t)B * (kMaxMemory + 1) * S;
     if ((rc = mb->b_rec_d.reserve(mb->ns)) || (rc = mb->b_mult_d.reserve((size_t)R * Bp)) ||
@@ -3294,8 +3337,11 @@ static int bootstrap_batch(regc_mbar *mb, const TargetDev &T, double tol, int64_
         (rc = mb->b_good_d.reserve((size_t)B * S)) || (rc = mb->b_hr_d.reserve(hist)) || (rc = mb->b_hg_d.reserve(hist)) ||
         (rc = mb->b_shift_d.reserve((size_t)B * mb->nN)) || (rc = mb->b_a_d.reserve((size_t)mb->nN * L * Bp)) ||
         (rc = mb->b_part_d.reserve((size_t)p.rows * outs * Bp)) || (rc = mb->b_sum_d.reserve((size_t)mb->nN * outs * Bp)) ||
-        (rc = mb->b_state_d.reserve(B)) || (rc = mb->y_d.reserve((size_t)B * S)))
-        return rc;
+        (rc = mb->b_state_d.reserve(B)) || (rc = mb->y_d.reserve((size_t)B * S))) {
+        (void)hipGetLastError();
+        release_boot(mb);
+        return rc == REGC_ENOMEM ? REGC_OK : rc;
+    }
     p.lnomega = mb->b_lnomega_d.p;
     p.f = mb->b_f_d.p; p.fnew = mb->b_fnew_d.p; p.good = mb->b_good_d.p;
     p.hist_r = mb->b_hr_d.p; p.hist_g = mb->b_hg_d.p;
@@ -3338,11 +3384,14 @@ static int bootstrap_batch(regc_mbar *mb, const TargetDev &T, double tol, int64_
         if (x.conv != 1) return REGC_OK;
     // the averages at the targets, on the solutions' weights
     hipLaunchKernelGGL(boot_weights_log, dim3(p.nN, B), dim3(kMbarThreads), 0, s, g, 1);
-    const dim3 target_grid(pass_grid.x, pass_grid.y, (T.nT + 15) / 16);
-    hipLaunchKernelGGL((boot_pass<true>), target_grid, dim3(kMbarThreads), pass_lds, s, g, T.tb_d.p, T.nT);
-    hipLaunchKernelGGL(boot_sum, dim3(p.nN, 8), dim3(256), 0, s, g, 3 * T.nT);
-    hipLaunchKernelGGL(boot_target_eval, dim3(T.nT, B), dim3(256), sizeof(double) * 3 * p.nN, s, g, T.nT, T.nMu, T.tb_d.p,
-                       T.tz_d.p, rep_n, rep_c);
+    for (int t0 = 0; t0 < T.nT; t0 += plan.temps) {
+        const int nt = std::min(plan.temps, T.nT - t0), k0 = t0 * T.nMu;
+        hipLaunchKernelGGL((boot_pass<true>), dim3(pass_grid.x, pass_grid.y, (nt + 15) / 16), dim3(kMbarThreads), pass_lds, s,
+                           g, T.tb_d.p + t0, nt);
+        hipLaunchKernelGGL(boot_sum, dim3(p.nN, 8), dim3(256), 0, s, g, 3 * nt);
+        hipLaunchKernelGGL(boot_target_eval, dim3(nt, B), dim3(256), sizeof(double) * 3 * p.nN, s, g, nt, T.nMu, T.nK,
+                           T.tb_d.p + t0, T.tz_d.p + k0, rep_n + k0, rep_c + k0);
+    }
     REGC_HIP(hipGetLastError());
     *ok = true;
     return REGC_OK;
@@ -3584,13 +3633,19 @@ extern "C" int regc_reweight(regc_mbar *mb, const regc_grid *targets, double tol
     bool together = mb->inverse_valid && solve_rc == REGC_OK && max_iter >= kNewtonMinIter && R < INT32_MAX &&
                     mb->nN <= kBootNs &&
                     bounded_targets(mb, T.tb.data(), T.nT);
-    for (int b0 = 0; b0 < B && together; b0 += kBootMax) {
-        rc = bootstrap_batch(mb, T, tol, R, rs, blk, o.seed, b0, std::min(kBootMax, B - b0), rep_n.p + (size_t)b0 * nK,
-                             rep_c.p + (size_t)b0 * nK, &together);
+    const BootPlan plan = together ? boot_plan(mb, R, B, T.nT) : BootPlan{};
+    together = together && plan.batch > 0;
+    for (int b0 = 0; b0 < B && together; b0 += plan.batch) {
+        rc = bootstrap_batch(mb, plan, T, tol, R, rs, blk, o.seed, b0, std::min(plan.batch, B - b0),
+                             rep_n.p + (size_t)b0 * nK, rep_c.p + (size_t)b0 * nK, &together);
         if (rc) {
             (void)hipStreamSynchronize(s);
             return rc;
         }
+    }
+    if (plan.bytes > kBootKept) {
+        REGC_HIP(hipStreamSynchronize(s));
+        release_boot(mb);
     }
     for (int b = 0; b < B && boot_rc == REGC_OK && !together; ++b) {
         hipLaunchKernelGGL(fill_i32, dim3((unsigned)std::min<int64_t>((R + 255) / 256, 4096)), dim3(256), 0, s, R, 0,
