@@ -1736,20 +1736,19 @@ struct BootArgs {
     double *sum;                     // [nN][outputs][Bp]
 };
 
-// mult[r][b]: how often record r occurs in replicate b: block j (of ceil(R / block))
+// mult[r][b]: how often record r occurs in replicate b (block row y): block j (of ceil(R / block))
 // starts at record floor(w (R - block + 1) / 2^32), w = word 0 of Philox block
-// (j, b, 0xFFFFFFFE, 7), the concatenation cut to R records.
-__global__ void boot_mult_all(int64_t R, int64_t block, int b0, int B, int Bp, uint32_t k0, uint32_t k1, int32_t *mult)
+// (j, b, 0xFFFFFFFE, 7), the concatenation cut to R records.  A thread per record of the
+// concatenation: a workgroup that takes a replicate's blocks in turn needs half a microsecond
+// for each (2e6 records in blocks of one, 100 replicates: 1190 -> 30 ms).
+__global__ void boot_mult_all(int64_t R, int64_t block, int b0, int Bp, uint32_t k0, uint32_t k1, int32_t *mult)
 {
-    const int b = blockIdx.x;
-    if (b >= B) return;
-    const int64_t nb = (R + block - 1) / block;
-    for (int64_t j = 0; j < nb; ++j) {
+    const int b = blockIdx.y;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < R; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t j = (int64_t)((uint32_t)i / (uint32_t)block);        // (R below 2^31)
         const uint4 w = philox4x32_10(make_uint4((uint32_t)j, (uint32_t)(b0 + b), 0xFFFFFFFEu, 7u), k0, k1);
         const int64_t start = (int64_t)(((uint64_t)w.x * (uint64_t)(R - block + 1)) >> 32);
-        // (one block of threads per replicate; the records of one j are distinct)
-        for (int64_t k = threadIdx.x; k < block && j * block + k < R; k += blockDim.x) mult[(start + k) * Bp + b] += 1;
-        __syncthreads();
+        atomicAdd(mult + (start + i - j * block) * Bp + b, 1);
     }
 }
 
@@ -3355,8 +3354,8 @@ static int bootstrap_batch(regc_mbar *mb, const BootPlan &plan, const TargetDev 
                        mb->b_mult_d.p);
     hipLaunchKernelGGL(fill_i32, dim3((unsigned)((S * Bp + 255) / 256)), dim3(256), 0, s, (int64_t)S * Bp, 0,
                        (int32_t *)mb->b_omega_d.p);
-    hipLaunchKernelGGL(boot_mult_all, dim3(B), dim3(256), 0, s, R, blk, b0, B, Bp, (uint32_t)seed, (uint32_t)(seed >> 32),
-                       mb->b_mult_d.p);
+    hipLaunchKernelGGL(boot_mult_all, dim3((unsigned)std::min<int64_t>((R + 255) / 256, 1024), B), dim3(256), 0, s, R, blk, b0,
+                       Bp, (uint32_t)seed, (uint32_t)(seed >> 32), mb->b_mult_d.p);
     hipLaunchKernelGGL(boot_records, dim3(grid), dim3(256), 0, s, mb->ns, rs, mb->perm_d.p, mb->b_rec_d.p);
     hipLaunchKernelGGL(boot_omega, dim3(2048), dim3(256), 0, s, mb->ns, rs, mb->s_orig_d.p, mb->b_mult_d.p, Bp,
                        mb->b_omega_d.p);

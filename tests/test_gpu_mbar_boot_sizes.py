@@ -75,3 +75,45 @@ def test_batches_and_values_of_n(n_boot, n_max, centre):
     assert ok and conv and got["converged"]
     assert np.allclose(got["se_n"], se_n, rtol=1e-5, atol=0)
     assert np.allclose(got["se_heat_cap"], se_c, rtol=1e-4, atol=0)
+
+
+@pytest.mark.parametrize("record_size,block,recs", [(1, 1, 20), (1, 7, 20), (2, 1, 30), (6, 30, 30), (6, 29, 30), (1, 0, 300)])
+def test_records_and_blocks(record_size, block, recs):
+    """Blocks of one record, of all records, and with a remainder."""
+    t, mu = W.linear_grid(1.28, 1.32, 2), W.linear_grid(-3.12, -3.08, 3)
+    e, n, s = _records(t, mu, 30, 12.0, recs, block)
+    w = W.ideal_gas().replace(t=t, mu=mu, n_max=30)
+    tt, tm = [1.3], [-3.11, -3.09]
+    mb = regc.Mbar(t, mu, 30)
+    mb.set_samples(e, n, s)
+    got = mb.reweight(tt, tm, tol=1e-12, n_boot=9, record_size=record_size, block_records=block, seed=11)
+    mb.close()
+    beta, lnz = oracle.state_arrays(w)
+    f, _, ok, _, _ = oracle.mbar_solve(beta, lnz, np.bincount(s, minlength=6), e, n, tol=1e-12, max_iter=100000)
+    tb, tz = np.repeat(1.0 / np.array(tt), 2), np.array([oracle.state_lnz(tt[0], b) for b in tm])
+    R = len(e) // record_size
+    se_n, se_c, _, _, conv = oracle.mbar_bootstrap(beta, lnz, e, n, s, record_size, block or max(1, R // 20), 9, 11, f, tb, tz,
+                                                  30, tol=1e-12)
+    assert ok and conv and got["converged"]
+    assert np.allclose(got["se_n"], se_n, rtol=1e-5, atol=1e-12)
+    assert np.allclose(got["se_heat_cap"], se_c, rtol=1e-4, atol=1e-12)
+
+
+def test_many_blocks_take_no_longer_than_few():
+    """2e6 records: the blocks' draws, one by one, took a second for blocks of one record and
+    20 ms for blocks of 10 000."""
+    import time
+    t, mu = W.linear_grid(1.2, 1.4, 8), W.linear_grid(-3.2, -3.0, 8)
+    e, n, s = _records(t, mu, 24, 9.0, 31250, 2)
+    mb = regc.Mbar(t, mu, 24)
+    mb.set_samples(e, n, s)
+    took = {}
+    for block in (10000, 1):
+        runs = []
+        for _ in range(3):
+            t0 = time.perf_counter()
+            mb.reweight([1.25, 1.3], [-3.1], tol=1e-10, n_boot=100, record_size=1, block_records=block)
+            runs.append(time.perf_counter() - t0)
+        took[block] = min(runs)
+    mb.close()
+    assert took[1] < 5 * took[10000] + 0.05
