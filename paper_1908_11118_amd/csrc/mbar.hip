@@ -960,6 +960,7 @@ struct SolveState {
     int hist, head;                  // differences' history: entries, slot of the oldest
     int gauge, memory;               // first sampled state; at most this many differences
     int polish;                      // iterations since the residual first came below tol
+    int lost;                        // a map value was not finite
     double delta, d_prev;
     double kept;                     // the latest residual below tol
 };
@@ -1355,6 +1356,7 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
         if (tid == 0) {
             st.done = done; st.conv = conv; st.it = it; st.plain_left = plain_left;
             st.hist = hist; st.head = head; st.polish = polish;
+            if (!finite) st.lost = 1;
             st.delta = d; st.d_prev = d_prev; st.kept = kept;
         }
     }
@@ -2778,7 +2780,8 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int max_iter, int n_s
 
 // solve_core on the device: the preconditioned solve where it applies, else (or where it
 // does not settle) the iteration and the decisions of the host's.
-static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta)
+static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double *start, int *iters, double *delta,
+                           bool *lost)
 {
     hipStream_t s = mb->stream;
     int rc;
@@ -2830,6 +2833,7 @@ static int solve_on_device(regc_mbar *mb, double tol, int max_iter, const double
     if (iters) *iters = st.it;
     if (delta) *delta = st.delta;
     mb->solved = true;
+    *lost = st.lost != 0;
     if (!st.conv) {
         set_error("reweighting did not converge: max |delta f| = %g after %d iterations", st.delta, st.it);
         return REGC_ENOCONV;
@@ -2904,9 +2908,12 @@ static int solve_core(regc_mbar *mb, double tol, int max_iter, const double *sta
 {
     mb->inverse_valid = mb->hinv_valid = false;
     if (device_solve(mb)) {
-        const int rc = solve_on_device(mb, tol, max_iter, start, iters, delta);
-        if (mb->tight || rc != REGC_ENOCONV) return rc;
-        // (sums of exponents past kMaxExponent may have overflowed)
+        bool lost = false;
+        const int rc = solve_on_device(mb, tol, max_iter, start, iters, delta, &lost);
+        // sums of exponents past kMaxExponent may have overflowed, which a map value shows; without
+        // that the general iteration would come no farther (its second run took half as long
+        // again: 60 iterations of 1024 states 17.7 -> 6.5 ms)
+        if (mb->tight || rc != REGC_ENOCONV || !lost) return rc;
         mb->inverse_valid = mb->hinv_valid = false;
     }
     hipStream_t s = mb->stream;

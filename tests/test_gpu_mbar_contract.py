@@ -74,3 +74,30 @@ def test_iterations_stay_within_the_limit(n_t, n_mu, n_max, per_state, spread, c
             assert it <= limit and counted >= it
             assert conv == (d < tol) and (conv or it == limit)
     mb.close()
+
+
+def test_a_limit_reached_on_wide_energies_is_not_run_twice():
+    """Exponents between 300 and 350, where a sum may overflow: a solve that ends at the limit
+    without a map value that is not finite is final (its time is that of the same samples with
+    narrow energies; the general iteration after it took as long again and more)."""
+    import time
+    t, mu = W.linear_grid(0.05, 2.0, 32), W.linear_grid(-2.6, -2.4, 32)
+    rng = np.random.default_rng(9)
+    ns = 400000
+    n = rng.integers(0, 6, ns).astype(np.int32)
+    s = rng.integers(0, 1024, ns).astype(np.int32)
+    took = {}
+    for shift in (20.0, 58.0):
+        e = rng.normal(0.0, 1.0, ns)
+        e[:40] += shift
+        mb = regc.Mbar(t, mu, 5)
+        mb.set_samples(e, n, s)
+        runs = []
+        for _ in range(4):
+            t0 = time.perf_counter()
+            _, conv, it, _ = mb.solve(tol=1e-30, max_iter=60, allow_noconv=True)
+            runs.append(time.perf_counter() - t0)
+            assert not conv and it == 60
+        took[shift] = min(runs)
+        mb.close()
+    assert took[58.0] < 1.5 * took[20.0]
