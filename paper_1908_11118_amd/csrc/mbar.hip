@@ -1651,14 +1651,15 @@ __global__ void __launch_bounds__(256) mbar_gj_update(int n, int kb, double *A, 
     }
 }
 
-// Row sums of |H^-1 W|; a NaN counts as infinite.
-__global__ void __launch_bounds__(64) mbar_inverse_norm(int S, int n, const double *Hi, const double *W, double *norm)
+// Row sums of |H^-1 W|: one above kMaxInverse (or no number) ends the attempt, before its
+// iterations.
+__global__ void __launch_bounds__(64) mbar_inverse_norm(int S, int n, const double *Hi, const double *W, SolveState *st)
 {
     double v = 0.0;
     for (int j = threadIdx.x; j < S; j += 64) v += fabs(Hi[(size_t)blockIdx.x * n + j] * W[j]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (threadIdx.x == 0) norm[blockIdx.x] = v == v ? v : INFINITY;
+    if (threadIdx.x == 0 && !(v <= kMaxInverse)) st->done = 1;      // (with conv 0; every row stores the same)
 }
 
 // y = H^-1 W (fnew - f) of one problem: the vector in LDS, a wave per row.
@@ -2282,7 +2283,7 @@ struct regc_mbar {
     unsigned long long *progress = nullptr;   // host memory the step kernel writes (SolveArgs::host)
     // the preconditioned iteration
     std::vector<double> mean_n, mean_e;   // of the samples of each state (empty: not known)
-    DevBuf<double> cpart_d, lw_d, csum_d, share_d, hess_d, w_d, row_d, col_d, norm_d, y_d;
+    DevBuf<double> cpart_d, lw_d, csum_d, share_d, hess_d, w_d, row_d, col_d, y_d;
     bool inverse_valid = false;           // hess_d holds the inverse of the solution's solve
     // the bootstrap's batch
     DevBuf<int32_t> b_rec_d, b_mult_d;
@@ -2689,7 +2690,7 @@ static int factorise(regc_mbar *mb, const SolveArgs &p)
     if ((rc = mb->cpart_d.reserve((size_t)p.rows * tiles * 256)) || (rc = mb->lw_d.reserve((size_t)p.nN * p.L)) ||
         (rc = mb->csum_d.reserve((size_t)p.L * p.L * nK)) || (rc = mb->share_d.reserve((size_t)nK * p.S)) ||
         (rc = mb->hess_d.reserve((size_t)n * n)) || (rc = mb->w_d.reserve(n)) || (rc = mb->row_d.reserve((size_t)kGj * n)) ||
-        (rc = mb->col_d.reserve((size_t)kGj * n)) || (rc = mb->norm_d.reserve(p.S)) || (rc = mb->y_d.reserve(p.S)))
+        (rc = mb->col_d.reserve((size_t)kGj * n)) || (rc = mb->y_d.reserve(p.S)))
         return rc;
     if (G == 1) hipLaunchKernelGGL((mbar_pass_c<1>), dim3(p.rows), dim3(kMbarThreads), 0, s, p, mb->cpart_d.p, mb->lw_d.p);
     else hipLaunchKernelGGL((mbar_pass_c<2>), dim3(p.rows), dim3(kMbarThreads), 0, s, p, mb->cpart_d.p, mb->lw_d.p);
@@ -2706,7 +2707,7 @@ static int factorise(regc_mbar *mb, const SolveArgs &p)
         hipLaunchKernelGGL(mbar_gj_update, dim3(n / kGj, n / kGj), dim3(256), 0, s, n, kb, mb->hess_d.p, mb->row_d.p,
                            mb->col_d.p);
     }
-    hipLaunchKernelGGL(mbar_inverse_norm, dim3(p.S), dim3(64), 0, s, p.S, n, mb->hess_d.p, mb->w_d.p, mb->norm_d.p);
+    hipLaunchKernelGGL(mbar_inverse_norm, dim3(p.S), dim3(64), 0, s, p.S, n, mb->hess_d.p, mb->w_d.p, p.st);
     REGC_HIP(hipGetLastError());
     return REGC_OK;
 }
@@ -2766,12 +2767,9 @@ static int solve_preconditioned(regc_mbar *mb, double tol, int max_iter, int n_s
              return e != hipSuccess ? e : launch_step(mb, p, 1);
          })))
         return rc;
-    std::vector<double> norm(mb->S);
     REGC_HIP(hipMemcpyAsync(&st, mb->state_d.p, sizeof st, hipMemcpyDeviceToHost, mb->stream));
-    REGC_HIP(hipMemcpyAsync(norm.data(), mb->norm_d.p, sizeof(double) * mb->S, hipMemcpyDeviceToHost, mb->stream));
     REGC_HIP(hipStreamSynchronize(mb->stream));
-    const double worst = *std::max_element(norm.begin(), norm.end());
-    *solved = st.conv == 1 && worst <= kMaxInverse;
+    *solved = st.conv == 1;
     mb->inverse_valid = *solved;
     *iters = near.it + 1 + st.it;
     *delta = st.delta;

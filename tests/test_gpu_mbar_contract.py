@@ -101,3 +101,17 @@ def test_a_limit_reached_on_wide_energies_is_not_run_twice():
         took[shift] = min(runs)
         mb.close()
     assert took[58.0] < 1.5 * took[20.0]
+
+
+def test_an_undetermined_solution_is_found_out_before_the_iterations():
+    """Too few states to connect the samples: the attempt with the inverse ends with the inverse
+    (its iterations, up to 60 of them, were run first), and the solve goes on from f = 0."""
+    t, mu = W.linear_grid(0.8, 1.6, 15), W.linear_grid(-7.0, -2.0, 2)
+    mb, e, n, s = _loaded(t, mu, 115, 16, 0, 1.74)
+    f, conv, it, d = mb.solve(tol=1e-6, max_iter=10000)
+    tried = mb.timing()[1] - it
+    mb.close()
+    beta, lnz = oracle.state_arrays(W.ideal_gas().replace(t=t, mu=mu, n_max=115))
+    g, _ = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=30), e, n, f)
+    assert conv and np.max(np.abs(g - g[0] - f)) < 1e-6
+    assert 0 < tried < 30
