@@ -106,8 +106,8 @@ def test_a_limit_reached_on_wide_energies_is_not_run_twice():
 def test_an_undetermined_solution_is_found_out_before_the_iterations():
     """Too few states to connect the samples: the attempt with the inverse ends with the inverse
     (its iterations, up to 60 of them, were run first), and the solve goes on from f = 0."""
-    t, mu = W.linear_grid(0.8, 1.6, 15), W.linear_grid(-7.0, -2.0, 2)
-    mb, e, n, s = _loaded(t, mu, 115, 16, 0, 1.74)
+    t, mu = W.linear_grid(0.8046809556261122, 1.1828264986833577, 15), W.linear_grid(-7.0, -2.0, 2)
+    mb, e, n, s = _loaded(t, mu, 115, 16, 90, 1.7399255687101833)
     f, conv, it, d = mb.solve(tol=1e-6, max_iter=10000)
     tried = mb.timing()[1] - it
     mb.close()
