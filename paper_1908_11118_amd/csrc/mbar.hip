@@ -2640,7 +2640,7 @@ static int start_solve(regc_mbar *mb, const double *f, const SolveState &st)
 {
     hipStream_t s = mb->stream;
     __atomic_store_n(mb->progress, 0ull, __ATOMIC_RELAXED);
-    const unsigned int none[2] = {0u, 0u};
+    static const unsigned int none[2] = {0u, 0u};        // (the copies may end after this function)
     if (f) {
         REGC_HIP(hipMemcpyAsync(mb->f_d.p, f, sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
         REGC_HIP(hipMemcpyAsync(mb->good_d.p, f, sizeof(double) * mb->S, hipMemcpyHostToDevice, s));
