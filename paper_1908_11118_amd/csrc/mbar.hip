@@ -968,7 +968,7 @@ struct SolveState {
 constexpr int kMaxMemory = 8;        // differences the device's least squares holds
 constexpr int kPolish = 12;          // iterations past the tolerance at most (preconditioned: 2)
 constexpr double kFloor = 2e-14;     // a residual that is rounding
-constexpr int kMaxStepStates = 4096; // states it holds (4 per thread of 1024)
+constexpr int kMaxStepStates = 4096; // states it holds (16 per thread of 256)
 
 struct SolveArgs {
     int L, M, S, nN, nchunks, sub, rows;       // rows = nchunks * sub partial sums per temperature
@@ -1157,7 +1157,9 @@ __device__ __forceinline__ void block_sums(double (&v)[NV], double (*red)[NV], i
 // iterate -- the map's value (method 0), or Anderson's mixture of the last map values
 // (method 1; see solve_core).  One block of T threads with R states each: the least
 // squares is a modified Gram-Schmidt whose columns stay in registers, one block-wide
-// reduction per column.  On the host it cost a copy each way, a synchronisation and the
+// reduction per column.  Four waves hold them at every size: sixteen waves have a quarter of
+// the registers each, and the columns of 1056 states in scratch made an iteration 295 us (33 x 32
+// states to 1e-6: 7.2 -> 1.7 ms, 3.0 with the host's).  On the host it cost a copy each way, a synchronisation and the
 // host's own sums every iteration (70 us of 230 at 1024 states).
 template <int T, int R>
 __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
@@ -2595,7 +2597,8 @@ static hipError_t launch_step(regc_mbar *mb, const SolveArgs &p, int B)
     if (p.S <= 64) hipLaunchKernelGGL((mbar_step<64, 1>), dim3(B), dim3(64), 0, mb->stream, p);
     else if (p.S <= 256) hipLaunchKernelGGL((mbar_step<256, 1>), dim3(B), dim3(256), 0, mb->stream, p);
     else if (p.S <= 1024) hipLaunchKernelGGL((mbar_step<256, 4>), dim3(B), dim3(256), 0, mb->stream, p);
-    else hipLaunchKernelGGL((mbar_step<1024, 4>), dim3(B), dim3(1024), 0, mb->stream, p);
+    else if (p.S <= 2048) hipLaunchKernelGGL((mbar_step<256, 8>), dim3(B), dim3(256), 0, mb->stream, p);
+    else hipLaunchKernelGGL((mbar_step<256, 16>), dim3(B), dim3(256), 0, mb->stream, p);
     return hipGetLastError();
 }
 

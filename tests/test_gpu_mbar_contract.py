@@ -115,3 +115,25 @@ def test_an_undetermined_solution_is_found_out_before_the_iterations():
     g, _ = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=30), e, n, f)
     assert conv and np.max(np.abs(g - g[0] - f)) < 1e-6
     assert 0 < tried < 30
+
+
+@pytest.mark.parametrize("n_mu", [32, 62, 63, 124])
+def test_an_iteration_of_more_states_takes_little_longer(n_mu):
+    """33 x 31 states (1023) against grids whose step holds more states per thread: the step's
+    columns have to stay in registers."""
+    per = []
+    for m in (31, n_mu):
+        t, mu = W.linear_grid(1.0, 1.6, 33), W.linear_grid(-3.6, -3.0, m)
+        rng = np.random.default_rng(m)
+        s = np.tile(np.arange(33 * m, dtype=np.int32), 20)
+        n = rng.integers(10, 40, len(s)).astype(np.int32)
+        mb = regc.Mbar(t, mu, 60)
+        mb.set_samples(-0.5 * n + rng.normal(0.0, 1.0, len(s)), n, s)
+        best = np.inf
+        for _ in range(3):
+            mb.solve(tol=1e-30, max_iter=40, allow_noconv=True)
+            ms, it = mb.timing()
+            best = min(best, ms / it)
+        per.append(best)
+        mb.close()
+    assert per[1] < 3.0 * per[0]
