@@ -2085,8 +2085,10 @@ __global__ void __launch_bounds__(kMbarThreads) mbar_target_pass(SolveArgs p, in
 
 // The averages at target temperature blockIdx.x from the chunks' sums: G(N) and the
 // moments of E at each N (threads), then a wave per chemical potential (a thread each and
-// every p(N) in turn: 90 us for 64 x 64 targets and 512 N; 46 us).
-constexpr int kEvalThreads = 512;
+// every p(N) in turn: 90 us for 64 x 64 targets and 512 N; 46 us).  A block takes kEvalMu of the
+// chemical potentials (blockIdx.y), each with its own copy of G and the moments: all 700 of one
+// temperature in one block were 88 in turn for a wave (2 x 700 targets and 41 N 180 -> 345 us; now 166).
+constexpr int kEvalThreads = 512, kEvalMu = 64;
 
 __global__ void __launch_bounds__(kEvalThreads) mbar_target_eval_q(SolveArgs p, int nT, int nMu, const double *tb,
                                                                 const double *tpart, const double *tlnz, double *f,
@@ -2109,7 +2111,9 @@ __global__ void __launch_bounds__(kEvalThreads) mbar_target_eval_q(SolveArgs p, 
     }
     __syncthreads();
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int m = wave; m < nMu; m += kEvalThreads / 64) {
+    // (kEvalMu is a multiple of the waves, so that a wave's next one after them is the next group's)
+    for (int m = blockIdx.y * kEvalMu + wave; m < nMu;
+         m += m % kEvalMu + kEvalThreads / 64 < kEvalMu ? kEvalThreads / 64 : kEvalThreads / 64 + ((int)gridDim.y - 1) * kEvalMu) {
         const int k = t * nMu + m;
         const double lz = tlnz[k];
         double mx = -INFINITY;
@@ -3068,8 +3072,8 @@ static hipError_t launch_targets(regc_mbar *mb, int nT, int nMu, const double *t
         else
             hipLaunchKernelGGL((mbar_target_pass<8>), dim3(mb->nchunks, (nT + 31) / 32), dim3(kMbarThreads), 0, s, p, nT,
                                tb_d, part);
-        hipLaunchKernelGGL(mbar_target_eval_q, dim3(nT), dim3(kEvalThreads), lds, s, p, nT, nMu, tb_d, part, tz_d, f, mn, me,
-                           me2, pn, ph);
+        hipLaunchKernelGGL(mbar_target_eval_q, dim3(nT, std::min((nMu + kEvalMu - 1) / kEvalMu, 4096)), dim3(kEvalThreads), lds,
+                           s, p, nT, nMu, tb_d, part, tz_d, f, mn, me, me2, pn, ph);
     } else {
         hipLaunchKernelGGL(mbar_target_chunk, dim3(mb->nchunks), dim3(kMbarThreads), 0, s, nT, tb_d, mb->e_d.p,
                            mb->logd_d.p, mb->chunk_b_d.p, mb->chunk_e_d.p, part, mb->weighted ? mb->wgt_d.p : nullptr);

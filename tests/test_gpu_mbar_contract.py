@@ -137,3 +137,47 @@ def test_an_iteration_of_more_states_takes_little_longer(n_mu):
         per.append(best)
         mb.close()
     assert per[1] < 3.0 * per[0]
+
+
+@pytest.mark.parametrize("n_tgt,n_mu", [(1, 63), (2, 64), (3, 65), (1, 700)])
+def test_targets_of_many_chemical_potentials(n_tgt, n_mu):
+    """Groups of 64 chemical potentials and their remainders against the oracle, and the same
+    values as one by one."""
+    t, mu = W.linear_grid(1.0, 1.4, 4), W.linear_grid(-3.4, -3.0, 3)
+    mb, e, n, s = _loaded(t, mu, 40, 100, 5)
+    f, conv, _, _ = mb.solve(tol=1e-11)
+    tt, tm = W.linear_grid(1.05, 1.35, n_tgt), W.linear_grid(-3.5, -2.9, n_mu)
+    got, static = mb.targets(tt, tm), mb.targets_static(tt, tm)
+    for k in (0, n_mu - 1):
+        one = mb.targets(tt, tm[k: k + 1])
+        for name in got:
+            assert np.array_equal(got[name].reshape(n_tgt, n_mu, -1)[:, k], one[name].reshape(n_tgt, -1)), name
+    mb.close()
+    beta, lnz = oracle.state_arrays(W.ideal_gas().replace(t=t, mu=mu, n_max=40))
+    _, logd = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=12), e, n, f)
+    ref = oracle.mbar_targets(np.repeat(1.0 / np.array(tt), n_mu),
+                              np.array([oracle.state_lnz(a, b) for a in tt for b in tm]), e, n, logd, 40)
+    assert conv
+    for name in static:
+        assert np.array_equal(static[name], got[name]), name
+    assert np.allclose(got["mean_n"], ref["mean_n"], rtol=1e-8) and np.allclose(got["p_n"], ref["p_n"], atol=1e-10)
+    assert np.array_equal(got["phase"], ref["phase"])
+
+
+def test_many_chemical_potentials_take_no_longer_than_many_temperatures():
+    """2 x 700 targets took 390 us in one block per temperature (350 x 4: 150)."""
+    import time
+    t, mu = W.linear_grid(1.0, 1.4, 4), W.linear_grid(-3.4, -3.0, 3)
+    mb, *_ = _loaded(t, mu, 40, 100, 5)
+    mb.solve(tol=1e-11)
+    took = []
+    for a, b in ((350, 4), (2, 700)):
+        tt, tm = W.linear_grid(1.05, 1.35, a), W.linear_grid(-3.5, -2.9, b)
+        runs = []
+        for _ in range(20):
+            t0 = time.perf_counter()
+            mb.targets(tt, tm)
+            runs.append(time.perf_counter() - t0)
+        took.append(min(runs))
+    mb.close()
+    assert took[1] < 1.5 * took[0]
