@@ -314,32 +314,54 @@ __global__ void __launch_bounds__(128 * kRows) hidden_forward(Batch bt, Source s
     ac.h3[o] = f2bf(gelu(v));
 }
 
-// The examples' entries of W1's gradient: f(b, j, voxel) for every particle j != excl[b] of
-// the part's share of the batch (blocks of four waves, an example per wave).
-template <typename F>
-__device__ __forceinline__ void each_entry(const Batch &bt, int part, int parts, F f)
+// The examples' entries of W1's gradient, one for every particle j != excl[b], of the part's
+// share of the batch: four examples at a time (a wave each), up to 256 particles of each.  The
+// block counts its entries of a voxel in LDS (`tally`, whose words are cleared by the entries
+// that use them) and makes one addition to the voxel's counter in memory: an addition per entry takes
+// its turn at the counter's cache line (512 examples of 150 particles in 16 voxels: 0.2 ms for
+// each of the two kernels that do it).  claim(voxel, count): that addition, its result the
+// voxel's first place; PLACE: then place(b, j, place) of every entry.
+template <bool PLACE, typename C, typename F>
+__device__ __forceinline__ void block_entries(const Batch &bt, int part, int parts, uint32_t *tally, C claim, F place)
 {
-    for (int b = part * 4 + (int)threadIdx.x / 64; b < bt.B; b += parts * 4) {
-        const int nb = bt.n[b], ex = bt.excl[b];
-        for (int j = threadIdx.x % 64; j < nb; j += 64)
-            if (j != ex) f(b, j - (j > ex), (int)bt.vox[(size_t)b * bt.nmax + j]);
+    constexpr int kEach = 4;
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    for (int b0 = part * 4; b0 < bt.B; b0 += parts * 4) {
+        const int b = b0 + wave, nb = bt.n[b], ex = bt.excl[b];
+        const int most = max(max(bt.n[b0], bt.n[b0 + 1]), max(bt.n[b0 + 2], bt.n[b0 + 3]));
+        for (int j0 = 0; j0 < most; j0 += 64 * kEach) {
+            int v[kEach];
+            uint32_t old[kEach];
+#pragma unroll
+            for (int q = 0; q < kEach; ++q) {
+                const int j = j0 + 64 * q + lane;
+                v[q] = j < nb && j != ex ? (int)bt.vox[(size_t)b * bt.nmax + j] : -1;
+            }
+#pragma unroll
+            for (int q = 0; q < kEach; ++q)
+                if (v[q] >= 0) tally[v[q]] = 0u;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kEach; ++q)
+                if (v[q] >= 0) old[q] = atomicAdd(tally + v[q], 1u);
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kEach; ++q)
+                if (v[q] >= 0 && old[q] == 0u) {
+                    const uint32_t first = claim(v[q], tally[v[q]]);
+                    if (PLACE) tally[v[q]] = first;
+                }
+            if (PLACE) {
+                __syncthreads();
+#pragma unroll
+                for (int q = 0; q < kEach; ++q) {
+                    const int j = j0 + 64 * q + lane;
+                    if (v[q] >= 0) place(b, j - (j > ex), tally[v[q]] + old[q]);
+                }
+            }
+            if (j0 + 64 * kEach < most || b0 + parts * 4 < bt.B) __syncthreads();     // the words are used again
+        }
     }
-}
-
-// The part's entries of every voxel, counted in LDS, and done(voxel, count) for those that
-// occur: one addition to the voxel's counter in memory per block.  (An addition per entry takes its turn at
-// the counter's cache line: 512 examples of 150 particles in 16 voxels, 0.2 ms for each of the
-// two kernels that do it.)
-template <typename F>
-__device__ __forceinline__ void block_entries(const Batch &bt, int part, int parts, uint32_t *tally, F done)
-{
-    for (int v = threadIdx.x; v < NV; v += 256) tally[v] = 0u;
-    __syncthreads();
-    each_entry(bt, part, parts, [&](int, int, int v) { atomicAdd(tally + v, 1u); });
-    __syncthreads();
-#pragma unroll 4
-    for (int v = threadIdx.x; v < NV; v += 256)
-        if (tally[v]) done(v, tally[v]);
 }
 
 // The last (NV / 64) (B / 64) blocks: the logits, 64 x 64 each.  The first count the entries
@@ -350,8 +372,8 @@ __global__ void __launch_bounds__(256) logits_forward(Batch bt, const bf16 *p16,
     __shared__ Stage st;
     const int parts = gridDim.x - (NV / 64) * (bt.B / 64), tile = (int)blockIdx.x - parts;
     if (tile < 0) {
-        block_entries(bt, blockIdx.x, parts, reinterpret_cast<uint32_t *>(&st),
-                      [&](int v, uint32_t c) { atomicAdd(count + v, c); });
+        block_entries<false>(bt, blockIdx.x, parts, reinterpret_cast<uint32_t *>(&st),
+                      [&](int v, uint32_t c) { atomicAdd(count + v, c); return 0u; }, [](int, int, uint32_t) {});
         return;
     }
     const int m0 = tile / (NV / 64) * 64, n0 = tile % (NV / 64) * 64;
@@ -464,12 +486,10 @@ __global__ void __launch_bounds__(256) output_backward(Batch bt, const bf16 *p16
     const int dh = (B / 64) * (H / 64) * kSplitK;
     const int parts = gridDim.x - dh - kDw4Blocks - kDb4Blocks;
     if (blk < parts) {
-        // the block's places in the voxels' lists, then an entry to each (first, for it takes longest)
-        uint32_t *at = reinterpret_cast<uint32_t *>(&st);
-        block_entries(bt, blk, parts, at, [&](int v, uint32_t c) { at[v] = atomicAdd(ls.cursor + v, c); });
-        __syncthreads();
-        each_entry(bt, blk, parts,
-                   [&](int b, int j, int v) { ls.entry[atomicAdd(at + v, 1u)] = (uint64_t)j << 32 | (uint32_t)b; });
+        // (first, for it takes longest)
+        block_entries<true>(bt, blk, parts, reinterpret_cast<uint32_t *>(&st),
+                      [&](int v, uint32_t c) { return atomicAdd(ls.cursor + v, c); },
+                      [&](int b, int j, uint32_t at) { ls.entry[at] = (uint64_t)j << 32 | (uint32_t)b; });
         return;
     }
     blk -= parts;
