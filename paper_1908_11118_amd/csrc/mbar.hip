@@ -1263,7 +1263,7 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
         // the way: the result is the latest map value below tol, or the one below tol before it.
         int polish = st.polish;
         const bool under = p.method == 1 && !sw && finite && d < p.tol;
-        const bool last = (polish > 0 && (!finite || d < kFloor || polish >= p.polish || (y && !(d < 0.5 * d_prev)))) ||
+        const bool last = (polish > 0 && (!finite || polish >= p.polish || (y && !(d < 0.5 * d_prev)))) || (under && d < kFloor) ||
                           ((polish > 0 || under) && it >= p.max_iter) || (under && p.polish == 0);
         const bool newest = under && (!last || d <= st.kept);
         const double kept = newest ? d : st.kept;
