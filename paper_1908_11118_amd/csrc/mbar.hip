@@ -2262,10 +2262,12 @@ __global__ void __launch_bounds__(256) mbar_obs_cond(SolveArgs p, int nT, int n_
     const size_t stride = (size_t)nT * (n_obs + 1);
     const double *src = part + (size_t)t * (n_obs + 1);
     double s0 = 0.0;
+#pragma unroll 8
     for (int c = c0; c < c1; ++c) s0 += src[c * stride + n_obs];
     if (threadIdx.x == 0) G[(size_t)t * p.nN + N] = s0 > 0.0 ? log(s0) - tb[t] * p.mid[N] - p.shift[N] : -INFINITY;
     for (int k = threadIdx.x; k < n_obs; k += blockDim.x) {
         double a = 0.0;
+#pragma unroll 8
         for (int c = c0; c < c1; ++c) a += src[c * stride + k];
         cond[((size_t)t * p.nN + N) * n_obs + k] = s0 > 0.0 ? a / s0 : 0.0;
     }
@@ -3281,7 +3283,10 @@ extern "C" int regc_mbar_observables(regc_mbar *mb, const regc_grid *targets, do
     SolveArgs p{};
     if (fast) {
         p = solve_args(mb);
-        // parts of chunks while their sums stay below 64 MiB
+        // parts of chunks while they hold some 16 samples and their sums stay below 64 MiB (an
+        // allocation above 2 MB costs 25 us: 200 samples, 300 observables, 20 temperatures in 8 parts
+        // 147 us instead of 127)
+        p.sub = (int)std::min<int64_t>(p.sub, std::max<int64_t>(1, mb->ns / ((int64_t)mb->nchunks * 16)));
         const size_t row = sizeof(double) * (size_t)nT * (no + 1) * p.nchunks;
         p.sub = (int)std::min<size_t>(p.sub, std::max<size_t>(1, ((size_t)64 << 20) / row));
         p.rows = p.nchunks * p.sub;
