@@ -364,16 +364,16 @@ __device__ __forceinline__ void block_entries(const Batch &bt, int part, int par
     }
 }
 
-// The last (NV / 64) (B / 64) blocks: the logits, 64 x 64 each.  The first count the entries
-// of every voxel.
+// Blocks 0 .. (NV / 64) (B / 64) - 1: the logits, 64 x 64 each.  The others count the
+// entries of every voxel.
 __global__ void __launch_bounds__(256) logits_forward(Batch bt, const bf16 *p16, const float *p, const bf16 *h3,
                                                    float *logits, uint32_t *count)
 {
     __shared__ Stage st;
-    const int parts = gridDim.x - (NV / 64) * (bt.B / 64), tile = (int)blockIdx.x - parts;
-    if (tile < 0) {
-        block_entries<false>(bt, blockIdx.x, parts, reinterpret_cast<uint32_t *>(&st),
-                      [&](int v, uint32_t c) { atomicAdd(count + v, c); return 0u; }, [](int, int, uint32_t) {});
+    const int tiles = (NV / 64) * (bt.B / 64), tile = blockIdx.x;
+    if (tile >= tiles) {
+        block_entries<false>(bt, tile - tiles, gridDim.x - tiles, reinterpret_cast<uint32_t *>(&st),
+                             [&](int v, uint32_t c) { atomicAdd(count + v, c); return 0u; }, [](int, int, uint32_t) {});
         return;
     }
     const int m0 = tile / (NV / 64) * 64, n0 = tile % (NV / 64) * 64;
@@ -472,9 +472,9 @@ __device__ __forceinline__ float colsum64(int M, int N, const float *X, int col0
     return ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
 }
 
-// By block: the lists of the voxels' examples, and the output layer's gradients: dh3 = d W4 as
-// kSplitK partial products of 256 k each (part [kSplitK][B][H]), dW4 = d^T h3, db4 = column sums
-// of d.
+// The output layer's gradients, by block: dh3 = d W4 as kSplitK partial products of 256 k
+// each (part [kSplitK][B][H]), dW4 = d^T h3, db4 = column sums of d, and the lists of the
+// voxels' examples.
 constexpr int kDw4Blocks = (NV / 64) * (H / 64), kDb4Blocks = NV / 64;
 
 __global__ void __launch_bounds__(256) output_backward(Batch bt, const bf16 *p16, const bf16 *h3, const float *d32,
@@ -485,14 +485,6 @@ __global__ void __launch_bounds__(256) output_backward(Batch bt, const bf16 *p16
     int blk = blockIdx.x;
     const int dh = (B / 64) * (H / 64) * kSplitK;
     const int parts = gridDim.x - dh - kDw4Blocks - kDb4Blocks;
-    if (blk < parts) {
-        // (first, for it takes longest)
-        block_entries<true>(bt, blk, parts, reinterpret_cast<uint32_t *>(&st),
-                      [&](int v, uint32_t c) { return atomicAdd(ls.cursor + v, c); },
-                      [&](int b, int j, uint32_t at) { ls.entry[at] = (uint64_t)j << 32 | (uint32_t)b; });
-        return;
-    }
-    blk -= parts;
     if (blk < dh) {
         const int z = blk % kSplitK, tile = blk / kSplitK;
         const int m0 = tile / (H / 64) * 64, n0 = tile % (H / 64) * 64;
@@ -509,8 +501,14 @@ __global__ void __launch_bounds__(256) output_backward(Batch bt, const bf16 *p16
         return;
     }
     blk -= kDw4Blocks;
-    const float s = colsum64(B, NV, d32, 64 * blk);
-    if (threadIdx.x < 64) g[OFF_B4 + 64 * blk + threadIdx.x] = s;
+    if (blk < kDb4Blocks) {
+        const float s = colsum64(B, NV, d32, 64 * blk);
+        if (threadIdx.x < 64) g[OFF_B4 + 64 * blk + threadIdx.x] = s;
+        return;
+    }
+    block_entries<true>(bt, blk - kDb4Blocks, parts, reinterpret_cast<uint32_t *>(&st),
+                        [&](int v, uint32_t c) { return atomicAdd(ls.cursor + v, c); },
+                        [&](int b, int j, uint32_t at) { ls.entry[at] = (uint64_t)j << 32 | (uint32_t)b; });
 }
 
 // Hidden layers 3, 2, 1 backwards for four examples: dh3 from the partial products (z in
