@@ -2652,6 +2652,7 @@ static hipError_t launch_step(regc_mbar *mb, const SolveArgs &p, int B)
     if (p.S <= 64) hipLaunchKernelGGL((mbar_step<64, 1>), dim3(B), dim3(64), 0, mb->stream, p);
     else if (p.S <= 256) hipLaunchKernelGGL((mbar_step<256, 1>), dim3(B), dim3(256), 0, mb->stream, p);
     else if (p.S <= 1024) hipLaunchKernelGGL((mbar_step<256, 4>), dim3(B), dim3(256), 0, mb->stream, p);
+    else if (p.method == 0) hipLaunchKernelGGL((mbar_step<1024, 4>), dim3(B), dim3(1024), 0, mb->stream, p);   // (no columns)
     else if (p.S <= 2048) hipLaunchKernelGGL((mbar_step<256, 8>), dim3(B), dim3(256), 0, mb->stream, p);
     else hipLaunchKernelGGL((mbar_step<256, 16>), dim3(B), dim3(256), 0, mb->stream, p);
     return hipGetLastError();
