@@ -63,6 +63,24 @@ def measured_traffic():
     return float(fields["bytes_per_launch"])
 
 
+def short_line(x, longest=8):
+    """x without its lists of more than `longest` entries (values by state) and with seven
+    digits a number, so that the printed line stays a few kilobytes; --detail has them all."""
+    if isinstance(x, dict):
+        return {k: short_line(v, longest) for k, v in x.items()
+                if not (isinstance(v, (dict, list)) and v and not kept(v, longest))}
+    if isinstance(x, list):
+        return [short_line(v, longest) for v in x]
+    return float(f"{x:.7g}") if isinstance(x, float) else x
+
+
+def kept(x, longest):
+    """Whether anything of x is left in the short line."""
+    if isinstance(x, list):
+        return len(x) <= longest
+    return any(not isinstance(v, (dict, list)) or not v or kept(v, longest) for v in x.values())
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -107,6 +125,7 @@ def main():
     ap.add_argument("--fs-tmin", type=float, default=0.88,
                     help="full stack: lowest temperature of the restricted reweighting (below it the states "
                          "on either side of the condensation do not exchange configurations)")
+    ap.add_argument("--detail", default="", help="also write the result with its values by state to this file")
     args = ap.parse_args()
     if args.gpus != 1:
         print(json.dumps({"error": "this benchmark runs on one GPU only; multi-GPU sharding is described in the "
@@ -211,7 +230,7 @@ def main():
                      "traffic": measured_traffic() if (args.workload == "c2" and prec == regc.FP32PAIR and not graph)
                      else None,
                      "traffic_unit": "HBM bytes per launch (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, copy-calibrated)",
-                     "kernel": "sweep_kernel_f32" if prec == regc.FP32PAIR else "sweep_kernel_f64",
+                     "kernel": "sweep_mode_kernel, FP32" if prec == regc.FP32PAIR else "sweep_mode_kernel, FP64",
                      "kernel_ms_avg": ms_kernel, "launches": tm["n_sweep"],
                      "timed_unit": "graph replay (sweeps + exchange)" if graph else "sweep-kernel launch",
                      "candidate_pairs_per_launch": cand / max(tm["n_sweep"], 1),
@@ -345,7 +364,10 @@ def main():
         result["learned"] = learned_leg(args)
     if args.full_stack:
         result["full_stack"] = full_stack_leg(args)
-    print(json.dumps(result))
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(result, f)
+    print(json.dumps(short_line(result), separators=(",", ":")))
 
 
 def production_leg(args, w, wk, prec):
@@ -402,7 +424,7 @@ def production_leg(args, w, wk, prec):
                           "errors": "bootstrap over 100 replicates of blocks of records (targets), batch means of "
                                     "20 batches (sampled states)",
                           "estimates_with_errors_seconds": t_rw, "estimates_converged": bool(rw["converged"])}
-    say(f"[production] {out}")
+    say(f"[production] reweighting {iters} iterations, {t_mb:.3f} s; with errors {t_rw:.2f} s")
     return out
 
 
@@ -745,7 +767,7 @@ def full_stack_leg(args):
                                    "reweighted_restricted": [None if np.isnan(x) else float(x) for x in mbar_hi],
                                    "heat_capacity_oracle": heat_or.tolist(),
                                    "heat_capacity_restricted": [None if np.isnan(x) else float(x) for x in heat_hi]}
-    say(f"[full stack] oracle subset: {out['oracle_subset']}")
+    say(f"[full stack] oracle subset: {args.fs_oracle_sweeps} sweeps, {t_or:.1f} s")
     return out
 
 

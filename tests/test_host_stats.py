@@ -46,3 +46,16 @@ def test_bench_reports_traffic_only_for_the_profiled_sources(tmp_path, monkeypat
     assert bench.measured_traffic() is None
     monkeypatch.setattr(bench, "TRAFFIC_PROFILE", str(tmp_path / "missing.md"))
     assert bench.measured_traffic() is None
+
+
+def test_bench_line_leaves_out_values_by_state():
+    """The printed line keeps every number and short list and leaves long lists out: the
+    reader of a run keeps the last few kilobytes of its output only."""
+    import json
+    import bench
+    full = {"value": 1.5, "none": None, "leg": {"se_by_state": [0.1] * 1024, "launch": [4, 2],
+                                                "rows": [{"mu": [0.0] * 64, "seconds": 1 / 3}] * 4},
+            "by_state": {"a": [1.0] * 9, "b": [2.0] * 9}}
+    assert bench.short_line(full) == {"value": 1.5, "none": None,
+                                      "leg": {"launch": [4, 2], "rows": [{"seconds": 0.3333333}] * 4}}
+    assert len(full["leg"]["se_by_state"]) == 1024 and json.dumps(bench.short_line(full))
