@@ -329,8 +329,6 @@ static int ctx_alloc_and_init(regc_ctx *c)
         ClassHost &h = c->cls[k];
         ClassDev &d = cd[k];
         d.lx = h.sys.lx; d.ly = h.sys.ly; d.zlo = h.sys.z_lo; d.zhi = h.sys.z_hi;
-        d.half_lx = 0.5 * h.sys.lx; d.half_ly = 0.5 * h.sys.ly;
-        d.inv_lx = 1.0 / h.sys.lx; d.inv_ly = 1.0 / h.sys.ly;
         d.lnv = std::log(h.sys.lx * h.sys.ly * (h.sys.z_hi - h.sys.z_lo));
         double top = -1.0e30;
         for (int a = 0; a < h.sys.n_slab; ++a) top = std::max(top, h.slab[3 * a + 2]);

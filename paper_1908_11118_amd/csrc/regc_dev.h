@@ -13,7 +13,6 @@ constexpr int kMaxWalkersPerBlock = 8;
 // Per-class constants (one class = one REGC simulation: slab, box, grid).
 struct ClassDev {
     double lx, ly, zlo, zhi;
-    double half_lx, half_ly, inv_lx, inv_ly;
     double lnv;              // ln V, V = lx * ly * (zhi - zlo)
     double slab_top;         // highest slab z (slab skipped above slab_top + rcut)
     int n_max;
