@@ -168,9 +168,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
         // one wave per walker and several walkers per SIMD (the walker order by cost is
         // on): the more atoms the walker holds relative to its class's cap, the higher its
         // wave's issue priority, so that the longest chains of trials, which end the
-        // launch, do not wait behind shorter ones (config 3: 10.89 -> 10.08 ms per launch;
-        // 4096 walkers of config 2's system: 3.57 -> 3.41 ms).  With two waves per walker
-        // the same rule made config 2 2.3 % slower, so it stays with one.
+        // launch, do not wait behind shorter ones (when it was taken, ten sweeps of 4096 uneven
+        // walkers with N <= 500: 10.89 -> 10.08 ms; of 4096 with N <= 200: 3.57 -> 3.41 ms).  With
+        // two waves per walker the same rule made 1024 walkers 2.3 % slower, so it stays with one.
         const int pn = (4 * n) / (C.n_max + 1);
         if (pn >= 3) __builtin_amdgcn_s_setprio(3);
         else if (pn == 2) __builtin_amdgcn_s_setprio(2);
@@ -234,7 +234,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                              sweep >= a.trace_sweep0;
         for (int t0 = 0; t0 < K; t0 += 32) {
             // (several waves per walker: the batch's random numbers, bulk vector work, at
-            // the lowest issue priority like the pair loop; config 2: 2.39 -> 2.36 ms)
+            // the lowest issue priority like the pair loop; 1024 walkers: 2.39 -> 2.36 ms)
             if (SPLIT >= 2) __builtin_amdgcn_s_setprio(0);
             // lane-parallel Philox: lane 2j -> block A of trial t0+j, lane 2j+1 -> block B
             const uint4 R = philox4x32_10(
@@ -342,7 +342,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs &a)
                 // several waves per walker: the pair loop at the lowest issue priority, the rest
                 // of the trial (the reduction, the exchange between the waves, the decision, the
                 // update and the next proposal) at a higher one, so that where two walkers share a
-                // SIMD the one on its serial path issues first (config 2: 2.43 -> 2.38 ms per
+                // SIMD the one on its serial path issues first (1024 walkers: 2.43 -> 2.38 ms per
                 // launch; four waves per walker: 2.93 -> 2.71 ms)
                 if (is_ins & bit) {
                     if (n >= n_max) {
