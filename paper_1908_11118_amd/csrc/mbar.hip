@@ -1016,7 +1016,10 @@ struct SolveState {
 
 constexpr int kMaxMemory = 8;        // differences the device's least squares holds
 constexpr int kPolish = 12;          // iterations past the tolerance at most (preconditioned: 2)
-constexpr double kFloor = 2e-14;     // a residual that is rounding
+// A residual that is rounding.  It is absolute: where f is in the hundreds an iteration cannot reach
+// it and takes all the kPolish ones, which is what brought a solution with |(I - J)^-1| of 1e4
+// from 1e-8 of the 64-bit one to 2e-10 (a floor that grew with |f| stopped short of that).
+constexpr double kFloor = 2e-14;
 constexpr int kMaxStepStates = 4096; // states it holds (16 per thread of 256)
 
 struct SolveArgs {
@@ -1437,6 +1440,9 @@ __global__ void __launch_bounds__(T) mbar_step(SolveArgs p)
 // come below kSwitch, converges to 1e-12 in about ten steps where the plain one takes
 // hundreds (its slowest errors shrink by a per cent or less per step).
 constexpr double kSwitch = 0.1;
+// More states or temperatures keep the plain iteration: the vector of mbar_newton_one and the
+// products of mbar_pass_c hold so many in LDS, and larger inversions were not measured.  Fewer
+// allowed iterations than kNewtonMinIter do too, as an attempt that fails takes up to 60.
 constexpr int kNewtonStates = 1024, kNewtonTemps = 32, kNewtonMinIter = 64;
 // Largest row sum of |(I - J)^-1| at which the solution counts as determined by the data:
 // stopping at tol leaves an error of up to tol times it.  Above it the samples hardly
@@ -2274,7 +2280,7 @@ __global__ void __launch_bounds__(256) mbar_obs_cond(SolveArgs p, int nT, int n_
 }
 
 // mean[t][mu][k] = sum_N p(N) cond[t][N][k], block (mu, t) (a block per t with mu in turn:
-// 6.4 ms for 16 x 16 targets x 221; 16 x 16 blocks: 30 us).
+// 6.4 ms for 16 temperatures x 64 mu x 221 counts; 16 x 64 blocks: 30 us).
 __global__ void __launch_bounds__(256) mbar_obs_mean(int nMu, int nN, int n_obs, const double *G, const double *tlnz,
                                                   const double *cond, double *mean)
 {
