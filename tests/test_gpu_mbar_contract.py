@@ -181,3 +181,29 @@ def test_many_chemical_potentials_take_no_longer_than_many_temperatures():
         took.append(min(runs))
     mb.close()
     assert took[1] < 1.5 * took[0]
+
+
+@pytest.mark.parametrize("burn,records", [(300, 100), (1000, 300)])
+def test_samples_of_a_run_across_the_condensation(burn, records):
+    """The sampler's own samples, energies of a gas and a liquid at the same N: at and beyond the
+    exponents' limits.  The solution is a fixed point of the oracle's map and the averages at
+    targets are the oracle's with it."""
+    w = W.config2().replace(mu=W.linear_grid(-8.0, -2.0, 8), sample_every=10)
+    with regc.Regc(w, precision=regc.FP32PAIR, sample_capacity=(burn // 10 + records) * w.n_states) as g:
+        g.run(burn + 10 * records)
+        e, n, s = (g.samples()[k][burn // 10 * w.n_states:] for k in ("e", "n", "state"))
+    mb = regc.Mbar(w.t, w.mu, w.n_max)
+    mb.set_samples(e, n, s)
+    f, conv, it, d = mb.solve(tol=1e-8, max_iter=20000)
+    assert conv and d < 1e-8
+    beta, lnz = oracle.state_arrays(w)
+    g, logd = oracle.mbar_iterate(beta, lnz, np.bincount(s, minlength=len(beta)), e, n, f)
+    assert np.max(np.abs(g - g[0] - f)) < 1e-7
+    tt, tm = W.linear_grid(0.45, 2.1, 9), W.linear_grid(-8.5, -1.5, 11)
+    tz = np.array([oracle.state_lnz(T, u, w.lambda1) for T in tt for u in tm])
+    ref = oracle.mbar_targets(np.repeat(1.0 / tt, len(tm)), tz, e, n, logd, w.n_max)
+    got = mb.targets(tt, tm)
+    # (log D is of the solution to some times its residual)
+    assert np.allclose(got["mean_n"], ref["mean_n"], rtol=1e-6, atol=1e-6)
+    assert np.allclose(got["mean_e"], ref["mean_e"], rtol=1e-6, atol=1e-6)
+    mb.close()
